@@ -678,83 +678,107 @@ __global__ void scatter_kernel(const int32_t* __restrict__ assign, int32_t* __re
     if (ok[q]) mem[base[z[q]] + pos[q]] = kb * kScatterKeys + q * 256 + tid;
 }
 
-// One wave per (slice, cluster): mean of the member keys, float64 sum.
-// A key row is read as 16-byte pieces: kLpr lanes per row, so one wave load
-// covers kRpl rows and four loads are in flight; each lane accumulates its
-// dims in float64 and the row groups are summed across lanes at the end.
+// Mean of a cluster's member keys, float64 sum; kSplit waves per (slice,
+// cluster).  A key row is read as 16-byte pieces: kLpr lanes per row, so one
+// wave load covers kRpl rows and kUnroll loads are in flight, the next batch's
+// member ids with them; each lane accumulates its dims in float64, the row
+// groups are summed across lanes and the waves' parts through LDS at the end.
+// One wave a cluster reads the rows at the rate HBM gives them once there are
+// clusters enough to fill the chip; below that the longest member list is the
+// kernel's time, and a block's waves share it.
 // With frag given, the wave also writes the next iteration's matrix operand
 // for this centroid (-2 op(c) in A-fragment order, and ||op(c)||^2), the work
 // prep_operand_kernel does for the first iteration; with zero_counts it
 // clears the cluster's count for the next assignment.
-template <class T>
-__global__ void centroid_update_kernel(const T* __restrict__ keys, const int32_t* __restrict__ members,
-                                       const int32_t* __restrict__ offsets, int32_t* __restrict__ counts,
-                                       const float* centroids_in, float* centroids_out, int stride, int n_tokens,
-                                       int n_clusters, int64_t n_rows, uint4* __restrict__ frag,
-                                       float* __restrict__ cnorm, int n_ctiles, int zero_counts,
-                                       int32_t* __restrict__ dirty, int skip_clean) {
+template <class T, int kSplit>
+__global__ __launch_bounds__((kSplit > 4 ? 64 * kSplit : 256))
+void centroid_update_kernel(const T* __restrict__ keys, const int32_t* __restrict__ members,
+                            const int32_t* __restrict__ offsets, int32_t* __restrict__ counts,
+                            const float* centroids_in, float* centroids_out, int stride, int n_tokens,
+                            int n_clusters, int64_t n_rows, uint4* __restrict__ frag,
+                            float* __restrict__ cnorm, int n_ctiles, int zero_counts,
+                            int32_t* __restrict__ dirty, int skip_clean) {
   constexpr int kDims = 16 / sizeof(T);          // dims per 16-byte piece (8 bf16, 4 fp32)
   constexpr int kLpr = kHeadDim / kDims;         // lanes per row
   constexpr int kRpl = kWave / kLpr;             // rows per wave load
-  constexpr int kUnroll = 4;
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  constexpr int kUnroll = sizeof(T) == 2 ? 4 : 8;
+  constexpr int kBatch = kRpl * kUnroll;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t row = kSplit > 1 ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * 4 + w;
+  const int part = kSplit > 1 ? w : 0;
   if (row >= n_rows) return;
   const int lane = threadIdx.x & 63;
   const int64_t s = row / n_clusters;
   const int c = (int)(row - s * n_clusters);
   const int n = counts[s * n_clusters + c];
+  const int off = offsets[s * (n_clusters + 1) + c];
   float* dst = centroids_out + ((size_t)s * stride + c) * kHeadDim;
+  const int was_dirty = dirty ? dirty[row] : 1;
+  if constexpr (kSplit > 1) __syncthreads();   // every wave has read the count and the flag before one clears them
   if (dirty) {
     // a cluster that no key entered or left keeps its members, hence its
     // mean and the operand prepared from it; the flag is cleared for the
     // next assignment either way
-    const int was_dirty = dirty[row];
-    if (lane == 0) dirty[row] = 0;
+    if (lane == 0 && part == 0) dirty[row] = 0;
     if (skip_clean && !was_dirty) {
-      if (zero_counts && lane == 0) counts[s * n_clusters + c] = 0;
+      if (zero_counts && lane == 0 && part == 0) counts[s * n_clusters + c] = 0;
       return;
     }
   }
   if (n == 0) {
     // empty: the centroid (and its operand from the previous preparation) stay
-    if (centroids_in != centroids_out) {
+    if (centroids_in != centroids_out && part == 0) {
       const float* src = centroids_in + ((size_t)s * stride + c) * kHeadDim;
       dst[2 * lane] = src[2 * lane];
       dst[2 * lane + 1] = src[2 * lane + 1];
     }
     return;
   }
-  const int off = offsets[s * (n_clusters + 1) + c];
   const int32_t* mem = members + (size_t)s * n_tokens + off;
   const T* kslice = keys + (size_t)s * n_tokens * kHeadDim;
   const int sub = lane % kLpr, grp = lane / kLpr;
   double acc[kDims];
 #pragma unroll
   for (int e = 0; e < kDims; ++e) acc[e] = 0.0;
-  for (int m0 = 0; m0 < n; m0 += kWave) {
-    const int mine = (m0 + lane < n) ? mem[m0 + lane] : 0;
-    const int cnt = min(kWave, n - m0);
-    for (int q = 0; q < cnt; q += kRpl * kUnroll) {
-      uint4 x[kUnroll];
+  int tok[kUnroll];
 #pragma unroll
-      for (int u = 0; u < kUnroll; ++u) {
-        const int r = q + u * kRpl + grp;
-        const int tok = __shfl(mine, r & (kWave - 1), kWave);
-        x[u] = r < cnt ? reinterpret_cast<const uint4*>(kslice + (size_t)tok * kHeadDim)[sub]
-                       : make_uint4(0, 0, 0, 0);
-      }
+  for (int u = 0; u < kUnroll; ++u) {
+    const int r = part * kBatch + u * kRpl + grp;
+    tok[u] = r < n ? mem[r] : -1;
+  }
+  for (int m0 = part * kBatch; m0 < n; m0 += kSplit * kBatch) {
+    uint4 x[kUnroll];
 #pragma unroll
-      for (int u = 0; u < kUnroll; ++u) {
-        const T* v = reinterpret_cast<const T*>(&x[u]);
+    for (int u = 0; u < kUnroll; ++u)
+      x[u] = tok[u] >= 0 ? reinterpret_cast<const uint4*>(kslice + (size_t)tok[u] * kHeadDim)[sub]
+                         : make_uint4(0, 0, 0, 0);
 #pragma unroll
-        for (int e = 0; e < kDims; ++e) acc[e] += (double)load_as_f32(v, e);
-      }
+    for (int u = 0; u < kUnroll; ++u) {
+      const int r = m0 + kSplit * kBatch + u * kRpl + grp;
+      tok[u] = r < n ? mem[r] : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+      const T* v = reinterpret_cast<const T*>(&x[u]);
+#pragma unroll
+      for (int e = 0; e < kDims; ++e) acc[e] += (double)load_as_f32(v, e);
     }
   }
 #pragma unroll
   for (int o = kLpr; o < kWave; o <<= 1)
 #pragma unroll
     for (int e = 0; e < kDims; ++e) acc[e] += __shfl_xor(acc[e], o, kWave);
+  if constexpr (kSplit > 1) {
+    __shared__ double s_part[kSplit - 1][kHeadDim];
+    if (part > 0 && grp == 0)
+#pragma unroll
+      for (int e = 0; e < kDims; ++e) s_part[part - 1][kDims * sub + e] = acc[e];
+    __syncthreads();
+    if (part > 0) return;
+    for (int q = 0; q < kSplit - 1; ++q)
+#pragma unroll
+      for (int e = 0; e < kDims; ++e) acc[e] += s_part[q][kDims * sub + e];
+  }
   if (grp != 0) return;
   // lanes 0..kLpr-1 hold dims kDims*lane ..
   float mean[kDims];
@@ -793,13 +817,28 @@ __global__ void centroid_update_kernel(const T* __restrict__ keys, const int32_t
   if (sub == 0) cnorm[(size_t)s * n_ctiles * kTileC + c] = (float)nrm;
 }
 
-// One wave per (slice, cluster): member ids sorted ascending into perm (rank =
-// number of smaller ids, ids are distinct), and the unit-table entry.
-__global__ void finalize_kernel(const int32_t* __restrict__ members, const int32_t* __restrict__ offsets,
-                                const int32_t* __restrict__ counts, int32_t* __restrict__ perm,
-                                int32_t* __restrict__ unit_start, int32_t* __restrict__ unit_size,
-                                int units_cap, int n_tokens, int n_clusters, int64_t n_rows) {
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+// One wave per (slice, cluster): member ids sorted ascending into perm, and the
+// unit-table entry.  Up to 64 members sit in one register a lane and a member's
+// rank is the number of smaller ids (a readlane and a compare for each member;
+// ids are distinct).  Larger clusters go through a bitmap of kFinalIds token
+// ids in the wave's LDS, window by window: a set bit's position among the set
+// bits is its rank, so the cost is the members plus a pass over the bitmap
+// whatever the cluster's size.  Ranks counted through ds_bpermute, and above
+// 64 members with a global load per pair of members, took 151 us for 8 slices
+// of 4096 float32 keys in 64 clusters (now 9.6), 40 us for 8 of 32768 bf16 keys
+// in 1024 (9.7) and 232 us for 256 such slices (112).
+constexpr int kFinalIds = 16384;                 // ids per window: 2 KiB of LDS a wave
+constexpr int kFinalWords = kFinalIds / 32;
+constexpr int kFinalPerLane = kFinalWords / 64;   // consecutive words a lane emits
+
+__global__ __launch_bounds__(256)
+void finalize_kernel(const int32_t* __restrict__ members, const int32_t* __restrict__ offsets,
+                     const int32_t* __restrict__ counts, int32_t* __restrict__ perm,
+                     int32_t* __restrict__ unit_start, int32_t* __restrict__ unit_size, int units_cap, int n_tokens,
+                     int n_clusters, int64_t n_rows) {
+  __shared__ uint32_t s_bits[4][kFinalWords];
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t row = (int64_t)blockIdx.x * 4 + w;
   if (row >= n_rows) return;
   const int lane = threadIdx.x & 63;
   const int64_t s = row / n_clusters;
@@ -812,18 +851,50 @@ __global__ void finalize_kernel(const int32_t* __restrict__ members, const int32
   }
   const int32_t* mem = members + (size_t)s * n_tokens + off;
   int32_t* out = perm + (size_t)s * n_tokens + off;
-  if (n <= 64) {
+  if (n <= kWave) {
     const int mine = lane < n ? mem[lane] : 0x7fffffff;
     int rank = 0;
-    for (int q = 0; q < n; ++q) rank += __shfl(mine, q, kWave) < mine;
+    for (int q = 0; q < n; ++q) rank += __builtin_amdgcn_readlane(mine, q) < mine;
     if (lane < n) out[rank] = mine;
     return;
   }
-  for (int i = lane; i < n; i += 64) {
-    const int mine = mem[i];
-    int rank = 0;
-    for (int q = 0; q < n; ++q) rank += mem[q] < mine;
-    out[rank] = mine;
+  // the wave's own slot, so no block barrier: a wave's LDS operations complete
+  // in order, the fences keep the compiler from reordering them
+  uint32_t* bits = s_bits[w];
+  int done = 0;   // members of the windows before this one
+  for (int base = 0; base < n_tokens; base += kFinalIds) {
+#pragma unroll
+    for (int i = 0; i < kFinalPerLane; ++i) bits[i * 64 + lane] = 0u;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    for (int i = lane; i < n; i += kWave) {
+      const int id = mem[i] - base;
+      if (id >= 0 && id < kFinalIds) atomicOr(&bits[id >> 5], 1u << (id & 31));
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    uint32_t word[kFinalPerLane];
+    int cnt = 0;
+#pragma unroll
+    for (int i = 0; i < kFinalPerLane; ++i) {
+      word[i] = bits[lane * kFinalPerLane + i];
+      cnt += __popc(word[i]);
+    }
+    int incl = cnt;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int y = __shfl_up(incl, o, kWave);
+      if (lane >= o) incl += y;
+    }
+    int at = done + incl - cnt;
+    done += __shfl(incl, kWave - 1, kWave);
+#pragma unroll
+    for (int i = 0; i < kFinalPerLane; ++i) {
+      uint32_t x = word[i];
+      while (x) {
+        out[at++] = base + (lane * kFinalPerLane + i) * 32 + __builtin_ctz(x);
+        x &= x - 1;
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   }
 }
 
@@ -932,6 +1003,15 @@ Ws carve(void* base, int64_t n_slices, int n_tokens, int n_clusters, int dtype) 
 }
 
 constexpr size_t kMaxHistLds = 64 * 1024;
+// Waves per cluster of the update, by the clusters of the whole call: one
+// each fills the chip from kSplit4Clusters on; below that the four waves of a
+// block share a cluster's members.  Below kSplit16Clusters sixteen do where a
+// cluster has kSplit16Members on average, so that most of them have rows to
+// read (512 clusters of 64 float32 keys: 47 us with one wave, 19 with four,
+// 12.6 with sixteen; 128 clusters of 31 bf16 keys: 6.2, 4.7 and 6.0).
+constexpr int64_t kSplit4Clusters = 4096;
+constexpr int64_t kSplit16Clusters = 1024;
+constexpr int kSplit16Members = 64;
 
 int launch_prep(const float* reps, int stride, int64_t S, int C, int dtype, const Ws& w, bool zero_counts,
                 hipStream_t st) {
@@ -994,19 +1074,26 @@ int launch_scan_scatter(const int32_t* assign, int64_t S, int N, int C, const Ws
 int launch_sum(const void* keys, int dtype, int64_t S, int N, int C, const Ws& w, const float* cin, float* cout,
                int stride, bool prep_next, hipStream_t st, int dirty_mode = 0) {
   const int64_t rows = S * C;
-  const int grid = (int)((rows + 3) / 4);
   const int n_ctiles = n_ctiles_for(C, dtype);
   uint4* frag = prep_next ? w.frag : nullptr;
   int32_t* dirty = dirty_mode ? w.dirty : nullptr;
   const int skip = dirty_mode == 2 ? 1 : 0;
-  if (dtype == LOUISKV_BF16)
-    centroid_update_kernel<uint16_t><<<grid, 256, 0, st>>>(static_cast<const uint16_t*>(keys), w.members,
-                                                            w.offsets, w.counts, cin, cout, stride, N, C, rows, frag,
-                                                            w.cnorm, n_ctiles, prep_next ? 1 : 0, dirty, skip);
-  else
-    centroid_update_kernel<float><<<grid, 256, 0, st>>>(static_cast<const float*>(keys), w.members, w.offsets,
-                                                         w.counts, cin, cout, stride, N, C, rows, frag, w.cnorm,
-                                                         n_ctiles, prep_next ? 1 : 0, dirty, skip);
+#define LKV_UPDATE(T, SPLIT)                                                                                    \
+  centroid_update_kernel<T, SPLIT><<<(unsigned)(SPLIT > 1 ? rows : (rows + 3) / 4), SPLIT > 4 ? 64 * SPLIT : 256, \
+                                     0, st>>>(static_cast<const T*>(keys), w.members, w.offsets, w.counts, cin,   \
+                                              cout, stride, N, C, rows, frag, w.cnorm, n_ctiles,                  \
+                                              prep_next ? 1 : 0, dirty, skip)
+#define LKV_UPDATE_T(T)                            \
+  if (rows < kSplit16Clusters && N / C >= kSplit16Members) LKV_UPDATE(T, 16); \
+  else if (rows < kSplit4Clusters) LKV_UPDATE(T, 4); \
+  else LKV_UPDATE(T, 1)
+  if (dtype == LOUISKV_BF16) {
+    LKV_UPDATE_T(uint16_t);
+  } else {
+    LKV_UPDATE_T(float);
+  }
+#undef LKV_UPDATE_T
+#undef LKV_UPDATE
   LKV_CHECK_LAUNCH();
   return LOUISKV_OK;
 }

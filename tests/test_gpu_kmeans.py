@@ -180,6 +180,33 @@ def test_cluster_prefill_matches_oracle_end_to_end():
            bound=max(2, S * P * wl.n_iters // 10000), of="assignment near-ties")
 
 
+@pytest.mark.parametrize("dtype,S,N,C", [
+    (torch.bfloat16, 1, 40000, 3),       # clusters past one 16384-id window, sixteen waves a cluster
+    (torch.float32, 2, 2048, 32),        # 64 members on average: sixteen waves
+    (torch.float32, 2, 2047, 32),        # one fewer: four waves
+    (torch.bfloat16, 1, 130, 2),         # around 64 members: the two ways of ordering them
+    (torch.bfloat16, 16, 8192, 256),     # 4096 clusters: one wave each
+])
+def test_member_order_and_means(dtype, S, N, C):
+    """perm is the stable order of the assignment and the centroids are the
+    float64 means of their members, whatever the clusters' sizes."""
+    L = _L()
+    keys = _keys(S, N, dtype, seed=17 * N + C)
+    reps = torch.empty(S, C, 128, device=DEV)
+    ustart = torch.empty(S, C, dtype=torch.int32, device=DEV)
+    usize = torch.empty_like(ustart)
+    assign = torch.empty(S, N, dtype=torch.int32, device=DEV)
+    perm = torch.empty_like(assign)
+    L.cluster_prefill(keys, C, 2, _init(S, N, C, seed=3), reps, ustart, usize, assign, perm)
+    torch.cuda.synchronize()
+    zg = to_np(assign)
+    for s in range(S):
+        assert np.array_equal(to_np(perm)[s], np.argsort(zg[s], kind="stable"))
+        ref, cnt = oracle.kmeans_update(to64(keys[s]), zg[s], to64(reps[s]))
+        assert np.array_equal(to_np(usize)[s], cnt)
+        assert np.array_equal(to64(reps)[s], ref), "centroids are not bit-exact"
+
+
 def test_empty_cluster_keeps_centroid():
     L = _L()
     S, N, C = 2, 512, 8
