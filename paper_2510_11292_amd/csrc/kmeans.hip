@@ -90,7 +90,8 @@ __global__ void init_centroids_kernel(const T* __restrict__ keys, const int32_t*
 template <bool kBf16>
 __global__ void prep_operand_kernel(const float* __restrict__ reps, int units_cap, int n_clusters,
                                     int n_ctiles, uint4* __restrict__ frag, float* __restrict__ cnorm,
-                                    int32_t* __restrict__ counts, int64_t n_rows) {
+                                    int32_t* __restrict__ counts, int32_t* __restrict__ cursor,
+                                    int32_t* __restrict__ dirty, int64_t n_rows) {
   const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= n_rows) return;
   const int lane = threadIdx.x & 63;
@@ -127,7 +128,11 @@ __global__ void prep_operand_kernel(const float* __restrict__ reps, int units_ca
   }
   if (lane == 0) {
     cnorm[(size_t)s * cpad + c] = real ? (float)nrm : __builtin_inff();
-    if (real && counts) counts[(size_t)s * n_clusters + c] = 0;
+    if (real && counts) {
+      counts[(size_t)s * n_clusters + c] = 0;
+      cursor[(size_t)s * n_clusters + c] = 0;
+      dirty[(size_t)s * n_clusters + c] = 0;
+    }
   }
 }
 
@@ -488,13 +493,19 @@ void assign_bf16_kernel(const uint16_t* __restrict__ keys, const uint4* __restri
     zi[kt] = bidx[kt];
     zv[kt] = (h == 0) && key < n_tokens;
     if (zv[kt]) assign[(size_t)slice * n_tokens + key] = bidx[kt];
-    // a key that changed cluster marks both clusters for the update
+    // a key that changed cluster marks both clusters for the update and moves
+    // from one's count to the other's
     if (dirty && zv[kt] && bidx[kt] != zp[kt]) {
-      dirty[(size_t)slice * n_clusters + bidx[kt]] = 1;
-      if (zp[kt] >= 0 && zp[kt] < n_clusters) dirty[(size_t)slice * n_clusters + zp[kt]] = 1;
+      const size_t base = (size_t)slice * n_clusters;
+      dirty[base + bidx[kt]] = 1;
+      atomicAdd(&counts[base + bidx[kt]], 1);
+      if (zp[kt] >= 0 && zp[kt] < n_clusters) {
+        dirty[base + zp[kt]] = 1;
+        atomicSub(&counts[base + zp[kt]], 1);
+      }
     }
   }
-  if (counts) {
+  if (counts && !dirty) {
     __syncthreads();
     block_histogram(reinterpret_cast<int*>(s_ring0), hist_in_lds, n_clusters,
                     counts + (size_t)slice * n_clusters, zi, zv, kBf16KeyTiles);
@@ -596,7 +607,8 @@ __global__ void count_kernel(const int32_t* __restrict__ assign, int32_t* __rest
                   counts + (size_t)slice * n_clusters, zi, zv, 4);
 }
 
-// Per slice: offsets[c] = sum of counts[<c], offsets[C] = total; cursor = offsets.
+// Per slice: offsets[c] = sum of counts[<c], offsets[C] = total; cursor =
+// offsets.  Only for more clusters than scatter_kernel scans in LDS.
 __global__ __launch_bounds__(1024)
 void scan_kernel(const int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
                  int32_t* __restrict__ cursor, int n_clusters) {
@@ -635,47 +647,124 @@ void scan_kernel(const int32_t* __restrict__ counts, int32_t* __restrict__ offse
   if (tid == 0) off[n_clusters] = s_carry;
 }
 
-constexpr int kScatterKeys = 1024;
+constexpr int kScatterKeys = 1024;   // keys per block (scatter_kernel: 256 * its kPer)
 
-// members[s][offsets[z] + k] = i for the keys i of each cluster z, k unique per key.
-__global__ void scatter_kernel(const int32_t* __restrict__ assign, int32_t* __restrict__ cursor,
-                               int32_t* __restrict__ members, int n_tokens, int n_clusters,
-                               int blocks_per_slice, int lds_ok) {
+// members[s][cursor[z]++] = i for every key i, with cursors from scan_kernel.
+__global__ void scatter_global_kernel(const int32_t* __restrict__ assign, int32_t* __restrict__ cursor,
+                                      int32_t* __restrict__ members, int n_tokens, int n_clusters,
+                                      int blocks_per_slice) {
+  const int slice = blockIdx.x / blocks_per_slice;
+  const int kb = blockIdx.x - slice * blocks_per_slice;
+  int32_t* cur = cursor + (size_t)slice * n_clusters;
+  int32_t* mem = members + (size_t)slice * n_tokens;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int i = kb * kScatterKeys + q * 256 + threadIdx.x;
+    const int z = i < n_tokens ? assign[(size_t)slice * n_tokens + i] : -1;
+    if (z >= 0 && z < n_clusters) mem[atomicAdd(&cur[z], 1)] = i;   // same keys as the count
+  }
+}
+
+// Exclusive block-wide scan of one value per thread (256 threads); returns
+// the total.  s_w: 4 ints of LDS.
+__device__ __forceinline__ int block256_scan(int v, int* s_w, int& excl) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  int x = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(x, o, kWave);
+    if (lane >= o) x += y;
+  }
+  __syncthreads();   // s_w of an earlier scan has been read
+  if (lane == 63) s_w[w] = x;
+  __syncthreads();
+  int before = 0, total = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int t = s_w[q];
+    before += q < w ? t : 0;
+    total += t;
+  }
+  excl = before + x - v;
+  return total;
+}
+
+// CSR offsets and member lists in one launch: every block scans its slice's
+// counts in LDS (C ints from L2; a launch of its own for the scan cost 3-5 us
+// an iteration), then places its 1024 keys: members[s][offsets[z] + k] = i, k
+// unique per key (an LDS count per block, one global atomic per block and
+// cluster on `cursor`, which is zero before the launch and cleared again by
+// the update).  Block 0 of a slice writes the offsets.
+// With `dirty` only the keys of flagged clusters are placed, the ones the
+// update reads, and block 0 writes the list of those clusters in ascending
+// order and its length.
+template <int kPer>
+__global__ __launch_bounds__(256)
+void scatter_kernel(const int32_t* __restrict__ assign, const int32_t* __restrict__ counts,
+                    int32_t* __restrict__ cursor, int32_t* __restrict__ offsets, int32_t* __restrict__ members,
+                    int n_tokens, int n_clusters, int blocks_per_slice, const int32_t* __restrict__ dirty,
+                    int32_t* __restrict__ dlist, int32_t* __restrict__ ndirty, int place_all) {
   extern __shared__ __align__(16) char smem[];
+  __shared__ int s_w[4];
   int* hist = reinterpret_cast<int*>(smem);
   int* base = hist + n_clusters;
   const int slice = blockIdx.x / blocks_per_slice;
   const int kb = blockIdx.x - slice * blocks_per_slice;
   const int tid = threadIdx.x;
-  int32_t* cur = cursor + (size_t)slice * n_clusters;
+  const size_t crow = (size_t)slice * n_clusters;
+  const int32_t* dr = dirty ? dirty + crow : nullptr;
   int32_t* mem = members + (size_t)slice * n_tokens;
-  int z[4], pos[4];
-  bool ok[4];
+  int z[kPer], pos[kPer];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int i = kb * kScatterKeys + q * 256 + tid;
-    ok[q] = i < n_tokens;
-    z[q] = ok[q] ? assign[(size_t)slice * n_tokens + i] : 0;
-    ok[q] = ok[q] && z[q] >= 0 && z[q] < n_clusters;   // same keys as the count
-    if (!ok[q]) z[q] = 0;
+  for (int q = 0; q < kPer; ++q) {
+    const int i = kb * (256 * kPer) + q * 256 + tid;
+    z[q] = i < n_tokens ? assign[(size_t)slice * n_tokens + i] : -1;
+    if (z[q] >= n_clusters) z[q] = -1;   // same keys as the count
   }
-  if (!lds_ok) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      if (ok[q]) mem[atomicAdd(&cur[z[q]], 1)] = kb * kScatterKeys + q * 256 + tid;
-    return;
-  }
-  for (int i = tid; i < n_clusters; i += 256) hist[i] = 0;
+  for (int i = tid; i < n_clusters; i += 256) hist[i] = counts[crow + i];
   __syncthreads();
+  // a thread's run of consecutive clusters
+  const int per = (n_clusters + 255) / 256;
+  const int c0 = min(tid * per, n_clusters), c1 = min(c0 + per, n_clusters);
+  int sum = 0;
+  for (int c = c0; c < c1; ++c) sum += hist[c];
+  int at;
+  const int total = block256_scan(sum, s_w, at);
+  for (int c = c0; c < c1; ++c) {
+    const int n = hist[c];
+    base[c] = at;
+    hist[c] = 0;
+    at += n;
+  }
+  __syncthreads();
+  if (kb == 0) {
+    int32_t* off = offsets + (size_t)slice * (n_clusters + 1);
+    for (int i = tid; i < n_clusters; i += 256) off[i] = base[i];
+    if (tid == 0) off[n_clusters] = total;
+    if (dr) {
+      int nd = 0;
+      for (int c = c0; c < c1; ++c) nd += dr[c] != 0;
+      int k;
+      const int all = block256_scan(nd, s_w, k);
+      for (int c = c0; c < c1; ++c)
+        if (dr[c]) dlist[crow + k++] = c;
+      if (tid == 0) ndirty[slice] = all;
+    }
+  }
+  if (dr && !place_all) {
 #pragma unroll
-  for (int q = 0; q < 4; ++q) pos[q] = ok[q] ? atomicAdd(&hist[z[q]], 1) : 0;
+    for (int q = 0; q < kPer; ++q)
+      if (z[q] >= 0 && !dr[z[q]]) z[q] = -1;
+  }
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) pos[q] = z[q] >= 0 ? atomicAdd(&hist[z[q]], 1) : 0;
   __syncthreads();
   for (int i = tid; i < n_clusters; i += 256)
-    if (hist[i]) base[i] = atomicAdd(&cur[i], hist[i]);
+    if (hist[i]) base[i] += atomicAdd(&cursor[crow + i], hist[i]);
   __syncthreads();
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
-    if (ok[q]) mem[base[z[q]] + pos[q]] = kb * kScatterKeys + q * 256 + tid;
+  for (int q = 0; q < kPer; ++q)
+    if (z[q] >= 0) mem[base[z[q]] + pos[q]] = kb * (256 * kPer) + q * 256 + tid;
 }
 
 // Mean of a cluster's member keys, float64 sum; kSplit waves per (slice,
@@ -686,135 +775,151 @@ __global__ void scatter_kernel(const int32_t* __restrict__ assign, int32_t* __re
 // One wave a cluster reads the rows at the rate HBM gives them once there are
 // clusters enough to fill the chip; below that the longest member list is the
 // kernel's time, and a block's waves share it.
+// With dirty only the flagged clusters are recomputed (a cluster that no key
+// entered or left keeps its members, hence its mean and the operand prepared
+// from it) and their flags cleared for the next assignment; with dlist (many
+// clusters in all) each wave takes every `stride_e`-th cluster of the slice's
+// list, without it a wave or block per cluster looks at its flag, which is one
+// dependent load less (8192 clusters: 13.3 us against 16.7).
 // With frag given, the wave also writes the next iteration's matrix operand
 // for this centroid (-2 op(c) in A-fragment order, and ||op(c)||^2), the work
-// prep_operand_kernel does for the first iteration; with zero_counts it
-// clears the cluster's count for the next assignment.
+// prep_operand_kernel does for the first iteration.  The clusters' scatter
+// cursors, and with zero_counts their counts, are cleared for the next
+// iteration.
+template <class T>
+struct UpdateArgs {
+  const T* keys;
+  const int32_t *members, *offsets;
+  int32_t *counts, *cursor;
+  const float* cin;
+  float* cout;
+  int stride, n_tokens, n_clusters;
+  int blocks_per_slice, stride_e;      // entries (clusters) a slice's waves or blocks take at once
+  uint4* frag;
+  float* cnorm;
+  int n_ctiles, zero_counts;
+  int32_t *dirty, *dlist, *ndirty;
+};
+
 template <class T, int kSplit>
 __global__ __launch_bounds__((kSplit > 4 ? 64 * kSplit : 256))
-void centroid_update_kernel(const T* __restrict__ keys, const int32_t* __restrict__ members,
-                            const int32_t* __restrict__ offsets, int32_t* __restrict__ counts,
-                            const float* centroids_in, float* centroids_out, int stride, int n_tokens,
-                            int n_clusters, int64_t n_rows, uint4* __restrict__ frag,
-                            float* __restrict__ cnorm, int n_ctiles, int zero_counts,
-                            int32_t* __restrict__ dirty, int skip_clean) {
+void centroid_update_kernel(const UpdateArgs<T> a) {
   constexpr int kDims = 16 / sizeof(T);          // dims per 16-byte piece (8 bf16, 4 fp32)
   constexpr int kLpr = kHeadDim / kDims;         // lanes per row
   constexpr int kRpl = kWave / kLpr;             // rows per wave load
   constexpr int kUnroll = sizeof(T) == 2 ? 4 : 8;
   constexpr int kBatch = kRpl * kUnroll;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t row = kSplit > 1 ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * 4 + w;
+  const int64_t s = blockIdx.x / a.blocks_per_slice;
+  const int blk = (int)(blockIdx.x - s * a.blocks_per_slice);
   const int part = kSplit > 1 ? w : 0;
-  if (row >= n_rows) return;
   const int lane = threadIdx.x & 63;
-  const int64_t s = row / n_clusters;
-  const int c = (int)(row - s * n_clusters);
-  const int n = counts[s * n_clusters + c];
-  const int off = offsets[s * (n_clusters + 1) + c];
-  float* dst = centroids_out + ((size_t)s * stride + c) * kHeadDim;
-  const int was_dirty = dirty ? dirty[row] : 1;
-  if constexpr (kSplit > 1) __syncthreads();   // every wave has read the count and the flag before one clears them
-  if (dirty) {
-    // a cluster that no key entered or left keeps its members, hence its
-    // mean and the operand prepared from it; the flag is cleared for the
-    // next assignment either way
-    if (lane == 0 && part == 0) dirty[row] = 0;
-    if (skip_clean && !was_dirty) {
-      if (zero_counts && lane == 0 && part == 0) counts[s * n_clusters + c] = 0;
-      return;
-    }
-  }
-  if (n == 0) {
-    // empty: the centroid (and its operand from the previous preparation) stay
-    if (centroids_in != centroids_out && part == 0) {
-      const float* src = centroids_in + ((size_t)s * stride + c) * kHeadDim;
-      dst[2 * lane] = src[2 * lane];
-      dst[2 * lane + 1] = src[2 * lane + 1];
-    }
-    return;
-  }
-  const int32_t* mem = members + (size_t)s * n_tokens + off;
-  const T* kslice = keys + (size_t)s * n_tokens * kHeadDim;
   const int sub = lane % kLpr, grp = lane / kLpr;
-  double acc[kDims];
+  const int n_entries = a.dlist ? a.ndirty[s] : a.n_clusters;
+  const bool track = a.dirty != nullptr;
+  const size_t crow = (size_t)s * a.n_clusters;
+  for (int e = kSplit > 1 ? blk : blk * 4 + w; e < n_entries; e += a.stride_e) {
+    const int c = a.dlist ? a.dlist[crow + e] : e;
+    const int n = a.counts[crow + c];
+    const int off = a.offsets[(size_t)s * (a.n_clusters + 1) + c];
+    const bool clean = track && !a.dlist && a.dirty[crow + c] == 0;
+    float* dst = a.cout + ((size_t)s * a.stride + c) * kHeadDim;
+    if constexpr (kSplit > 1) __syncthreads();   // every wave has read the count and the flag before one clears them
+    if (clean) continue;
+    if (lane == 0 && part == 0) {
+      if (track) a.dirty[crow + c] = 0;
+      if (a.cursor) a.cursor[crow + c] = 0;
+      if (a.zero_counts) a.counts[crow + c] = 0;
+    }
+    if (n == 0) {
+      // empty: the centroid (and its operand from the previous preparation) stay
+      if (a.cin != a.cout && part == 0) {
+        const float* src = a.cin + ((size_t)s * a.stride + c) * kHeadDim;
+        dst[2 * lane] = src[2 * lane];
+        dst[2 * lane + 1] = src[2 * lane + 1];
+      }
+      continue;
+    }
+    const int32_t* mem = a.members + (size_t)s * a.n_tokens + off;
+    const T* kslice = a.keys + (size_t)s * a.n_tokens * kHeadDim;
+    double acc[kDims];
 #pragma unroll
-  for (int e = 0; e < kDims; ++e) acc[e] = 0.0;
-  int tok[kUnroll];
-#pragma unroll
-  for (int u = 0; u < kUnroll; ++u) {
-    const int r = part * kBatch + u * kRpl + grp;
-    tok[u] = r < n ? mem[r] : -1;
-  }
-  for (int m0 = part * kBatch; m0 < n; m0 += kSplit * kBatch) {
-    uint4 x[kUnroll];
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u)
-      x[u] = tok[u] >= 0 ? reinterpret_cast<const uint4*>(kslice + (size_t)tok[u] * kHeadDim)[sub]
-                         : make_uint4(0, 0, 0, 0);
+    for (int d = 0; d < kDims; ++d) acc[d] = 0.0;
+    int tok[kUnroll];
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
-      const int r = m0 + kSplit * kBatch + u * kRpl + grp;
+      const int r = part * kBatch + u * kRpl + grp;
       tok[u] = r < n ? mem[r] : -1;
     }
+    for (int m0 = part * kBatch; m0 < n; m0 += kSplit * kBatch) {
+      uint4 x[kUnroll];
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      const T* v = reinterpret_cast<const T*>(&x[u]);
+      for (int u = 0; u < kUnroll; ++u)
+        x[u] = tok[u] >= 0 ? reinterpret_cast<const uint4*>(kslice + (size_t)tok[u] * kHeadDim)[sub]
+                           : make_uint4(0, 0, 0, 0);
 #pragma unroll
-      for (int e = 0; e < kDims; ++e) acc[e] += (double)load_as_f32(v, e);
+      for (int u = 0; u < kUnroll; ++u) {
+        const int r = m0 + kSplit * kBatch + u * kRpl + grp;
+        tok[u] = r < n ? mem[r] : -1;
+      }
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) {
+        const T* v = reinterpret_cast<const T*>(&x[u]);
+#pragma unroll
+        for (int d = 0; d < kDims; ++d) acc[d] += (double)load_as_f32(v, d);
+      }
     }
-  }
 #pragma unroll
-  for (int o = kLpr; o < kWave; o <<= 1)
+    for (int o = kLpr; o < kWave; o <<= 1)
 #pragma unroll
-    for (int e = 0; e < kDims; ++e) acc[e] += __shfl_xor(acc[e], o, kWave);
-  if constexpr (kSplit > 1) {
-    __shared__ double s_part[kSplit - 1][kHeadDim];
-    if (part > 0 && grp == 0)
+      for (int d = 0; d < kDims; ++d) acc[d] += __shfl_xor(acc[d], o, kWave);
+    if constexpr (kSplit > 1) {
+      __shared__ double s_part[kSplit - 1][kHeadDim];
+      if (part > 0 && grp == 0)
 #pragma unroll
-      for (int e = 0; e < kDims; ++e) s_part[part - 1][kDims * sub + e] = acc[e];
-    __syncthreads();
-    if (part > 0) return;
-    for (int q = 0; q < kSplit - 1; ++q)
+        for (int d = 0; d < kDims; ++d) s_part[part - 1][kDims * sub + d] = acc[d];
+      __syncthreads();
+      if (part > 0) continue;
+      for (int q = 0; q < kSplit - 1; ++q)
 #pragma unroll
-      for (int e = 0; e < kDims; ++e) acc[e] += s_part[q][kDims * sub + e];
-  }
-  if (grp != 0) return;
-  // lanes 0..kLpr-1 hold dims kDims*lane ..
-  float mean[kDims];
-#pragma unroll
-  for (int e = 0; e < kDims; ++e) mean[e] = (float)(acc[e] / (double)n);
-  float4* d4 = reinterpret_cast<float4*>(dst + kDims * sub);
-#pragma unroll
-  for (int e = 0; e < kDims; e += 4) d4[e / 4] = make_float4(mean[e], mean[e + 1], mean[e + 2], mean[e + 3]);
-  if (zero_counts && sub == 0) counts[s * n_clusters + c] = 0;
-  if (!frag) return;
-  // next iteration's operand: same layout and values as prep_operand_kernel
-  const int t = c / kTileC, ci = c % kTileC;
-  const int d0 = kDims * sub, hh = d0 >> 6;
-  const int flane = hh * 32 + ci;
-  double nrm = 0.0;
-  if (sizeof(T) == 2) {
-    uint32_t w[4];
-#pragma unroll
-    for (int e = 0; e < 8; e += 2) {
-      const float o0 = bf16_to_f32(f32_to_bf16(mean[e])), o1 = bf16_to_f32(f32_to_bf16(mean[e + 1]));
-      nrm += (double)o0 * o0 + (double)o1 * o1;
-      w[e / 2] = (uint32_t)f32_to_bf16(-2.f * o0) | ((uint32_t)f32_to_bf16(-2.f * o1) << 16);
+        for (int d = 0; d < kDims; ++d) acc[d] += s_part[q][kDims * sub + d];
     }
-    const int step = (d0 & 63) >> 3;
-    frag[((size_t)s * n_ctiles + t) * kBf16TileU4 + step * 64 + flane] = make_uint4(w[0], w[1], w[2], w[3]);
-  } else {
+    if (grp != 0) continue;
+    // lanes 0..kLpr-1 hold dims kDims*lane ..
+    float mean[kDims];
 #pragma unroll
-    for (int e = 0; e < kDims; ++e) nrm += (double)mean[e] * mean[e];
-    const int step = d0 & 63;   // 4 consecutive steps, one float4 of the fp32 layout
-    float* f = reinterpret_cast<float*>(frag + ((size_t)s * n_ctiles + t) * kF32TileU4);
-    *reinterpret_cast<float4*>(f + ((size_t)(step >> 2) * 64 + flane) * 4) =
-        make_float4(-2.f * mean[0], -2.f * mean[1], -2.f * mean[2], -2.f * mean[3]);
+    for (int d = 0; d < kDims; ++d) mean[d] = (float)(acc[d] / (double)n);
+    float4* d4 = reinterpret_cast<float4*>(dst + kDims * sub);
+#pragma unroll
+    for (int d = 0; d < kDims; d += 4) d4[d / 4] = make_float4(mean[d], mean[d + 1], mean[d + 2], mean[d + 3]);
+    if (!a.frag) continue;
+    // next iteration's operand: same layout and values as prep_operand_kernel
+    const int t = c / kTileC, ci = c % kTileC;
+    const int d0 = kDims * sub, hh = d0 >> 6;
+    const int flane = hh * 32 + ci;
+    double nrm = 0.0;
+    if (sizeof(T) == 2) {
+      uint32_t wd[4];
+#pragma unroll
+      for (int d = 0; d < 8; d += 2) {
+        const float o0 = bf16_to_f32(f32_to_bf16(mean[d])), o1 = bf16_to_f32(f32_to_bf16(mean[d + 1]));
+        nrm += (double)o0 * o0 + (double)o1 * o1;
+        wd[d / 2] = (uint32_t)f32_to_bf16(-2.f * o0) | ((uint32_t)f32_to_bf16(-2.f * o1) << 16);
+      }
+      const int step = (d0 & 63) >> 3;
+      a.frag[((size_t)s * a.n_ctiles + t) * kBf16TileU4 + step * 64 + flane] = make_uint4(wd[0], wd[1], wd[2], wd[3]);
+    } else {
+#pragma unroll
+      for (int d = 0; d < kDims; ++d) nrm += (double)mean[d] * mean[d];
+      const int step = d0 & 63;   // 4 consecutive steps, one float4 of the fp32 layout
+      float* f = reinterpret_cast<float*>(a.frag + ((size_t)s * a.n_ctiles + t) * kF32TileU4);
+      *reinterpret_cast<float4*>(f + ((size_t)(step >> 2) * 64 + flane) * 4) =
+          make_float4(-2.f * mean[0], -2.f * mean[1], -2.f * mean[2], -2.f * mean[3]);
+    }
+#pragma unroll
+    for (int o = 1; o < kLpr; o <<= 1) nrm += __shfl_xor(nrm, o, kWave);
+    if (sub == 0) a.cnorm[(size_t)s * a.n_ctiles * kTileC + c] = (float)nrm;
   }
-#pragma unroll
-  for (int o = 1; o < kLpr; o <<= 1) nrm += __shfl_xor(nrm, o, kWave);
-  if (sub == 0) cnorm[(size_t)s * n_ctiles * kTileC + c] = (float)nrm;
 }
 
 // One wave per (slice, cluster): member ids sorted ascending into perm, and the
@@ -971,7 +1076,9 @@ struct Ws {
   int32_t* offsets;
   int32_t* cursor;
   int32_t* members;
-  int32_t* dirty;   // per cluster: a key entered or left it in the last assignment
+  int32_t* dirty;    // per cluster: a key entered or left it in the last assignment
+  int32_t* dlist;    // the flagged clusters of a slice, ascending
+  int32_t* ndirty;   // their number
   uint4* kswz;   // bf16 key operands in B-operand order (kswz_mode of the assignment)
   size_t bytes;
 };
@@ -995,6 +1102,8 @@ Ws carve(void* base, int64_t n_slices, int n_tokens, int n_clusters, int dtype) 
   w.cursor = cv.take<int32_t>((size_t)n_slices * n_clusters);
   w.members = cv.take<int32_t>((size_t)n_slices * n_tokens);
   w.dirty = cv.take<int32_t>((size_t)n_slices * n_clusters);
+  w.dlist = cv.take<int32_t>((size_t)n_slices * n_clusters);
+  w.ndirty = cv.take<int32_t>((size_t)n_slices);
   w.kswz = dtype == LOUISKV_BF16
                ? cv.take<uint4>((size_t)n_slices * ceil_div(n_tokens, kBf16KeysPerBlock) * kBf16KeysPerBlock * 16)
                : nullptr;
@@ -1012,18 +1121,25 @@ constexpr size_t kMaxHistLds = 64 * 1024;
 constexpr int64_t kSplit4Clusters = 4096;
 constexpr int64_t kSplit16Clusters = 1024;
 constexpr int kSplit16Members = 64;
+// From this many clusters on a wave takes four of the listed clusters in turn:
+// late iterations list a few percent of them, and waves that find nothing to
+// do are then a quarter as many.
+constexpr int64_t kShareClusters = 65536;
+// Scatter blocks of 4096 keys instead of 1024 once that leaves the chip full.
+constexpr int64_t kWideScatterBlocks = 4096;
 
-int launch_prep(const float* reps, int stride, int64_t S, int C, int dtype, const Ws& w, bool zero_counts,
+// clear: the counts, scatter cursors and flags of a new clustering start at zero.
+int launch_prep(const float* reps, int stride, int64_t S, int C, int dtype, const Ws& w, bool clear,
                 hipStream_t st) {
   const int n_ctiles = n_ctiles_for(C, dtype);
   const int64_t rows = S * n_ctiles * kTileC;
   const int grid = (int)((rows + 3) / 4);
   if (dtype == LOUISKV_BF16)
     prep_operand_kernel<true><<<grid, 256, 0, st>>>(reps, stride, C, n_ctiles, w.frag, w.cnorm,
-                                                     zero_counts ? w.counts : nullptr, rows);
+                                                     clear ? w.counts : nullptr, w.cursor, w.dirty, rows);
   else
     prep_operand_kernel<false><<<grid, 256, 0, st>>>(reps, stride, C, n_ctiles, w.frag, w.cnorm,
-                                                      zero_counts ? w.counts : nullptr, rows);
+                                                      clear ? w.counts : nullptr, w.cursor, w.dirty, rows);
   LKV_CHECK_LAUNCH();
   return LOUISKV_OK;
 }
@@ -1055,47 +1171,83 @@ int launch_assign(const void* keys, int dtype, int64_t S, int N, int C, const Ws
   return LOUISKV_OK;
 }
 
-int launch_scan_scatter(const int32_t* assign, int64_t S, int N, int C, const Ws& w, hipStream_t st) {
-  scan_kernel<<<(unsigned)S, 1024, 0, st>>>(w.counts, w.offsets, w.cursor, C);
-  LKV_CHECK_LAUNCH();
+// Whether the scatter scans the counts in LDS (two ints a cluster); above,
+// the scan is a launch of its own and every cluster is updated every time.
+bool scatter_in_lds(int C) { return (size_t)C * 8 <= kMaxHistLds; }
+
+// list: only the flagged clusters' members are placed and the list of those
+// clusters is written (all: every key is placed all the same).
+int launch_scan_scatter(const int32_t* assign, int64_t S, int N, int C, const Ws& w, bool list, bool all,
+                        hipStream_t st) {
   const int bps = ceil_div(N, kScatterKeys);
-  const bool lds_ok = (size_t)C * 8 <= kMaxHistLds;
-  scatter_kernel<<<(unsigned)(S * bps), 256, lds_ok ? (size_t)C * 8 : 0, st>>>(assign, w.cursor, w.members, N, C,
-                                                                              bps, lds_ok ? 1 : 0);
+  if (scatter_in_lds(C)) {
+#define LKV_SCATTER(PER)                                                                                           \
+  scatter_kernel<PER><<<(unsigned)(S * ceil_div(N, 256 * PER)), 256, (size_t)C * 8, st>>>(                          \
+      assign, w.counts, w.cursor, w.offsets, w.members, N, C, ceil_div(N, 256 * PER), list ? w.dirty : nullptr,      \
+      w.dlist, w.ndirty, all ? 1 : 0)
+    if (S * bps >= kWideScatterBlocks) {
+      LKV_SCATTER(16);
+    } else {
+      LKV_SCATTER(4);
+    }
+#undef LKV_SCATTER
+  } else {
+    scan_kernel<<<(unsigned)S, 1024, 0, st>>>(w.counts, w.offsets, w.cursor, C);
+    LKV_CHECK_LAUNCH();
+    scatter_global_kernel<<<(unsigned)(S * bps), 256, 0, st>>>(assign, w.cursor, w.members, N, C, bps);
+  }
   LKV_CHECK_LAUNCH();
   return LOUISKV_OK;
 }
 
-// Centroid update; with prep_next, also the next iteration's operand and
-// cleared counts (the work of launch_prep for the iterations after the first).
-// dirty_mode: 0 no flags (every cluster), 1 every cluster and clear the
-// flags, 2 only the flagged clusters (the others keep centroid and operand)
-// and clear the flags.
-int launch_sum(const void* keys, int dtype, int64_t S, int N, int C, const Ws& w, const float* cin, float* cout,
-               int stride, bool prep_next, hipStream_t st, int dirty_mode = 0) {
+// Centroid update; with prep_next, also the next iteration's operand (the
+// work of launch_prep for the iterations after the first).  zero_counts: the
+// next assignment counts from zero.  list: only the clusters listed by the
+// scatter (the others keep centroid and operand).
+template <class T>
+int launch_sum_t(const void* keys, int64_t S, int N, int C, int n_ctiles, const Ws& w, const float* cin, float* cout,
+                 int stride, bool prep_next, bool zero_counts, bool list, hipStream_t st) {
+  UpdateArgs<T> a{};
+  a.keys = static_cast<const T*>(keys);
+  a.members = w.members;
+  a.offsets = w.offsets;
+  a.counts = w.counts;
+  a.cursor = scatter_in_lds(C) ? w.cursor : nullptr;
+  a.cin = cin;
+  a.cout = cout;
+  a.stride = stride;
+  a.n_tokens = N;
+  a.n_clusters = C;
+  a.frag = prep_next ? w.frag : nullptr;
+  a.cnorm = w.cnorm;
+  a.n_ctiles = n_ctiles;
+  a.zero_counts = zero_counts ? 1 : 0;
+  a.dirty = list ? w.dirty : nullptr;
+  a.ndirty = w.ndirty;
   const int64_t rows = S * C;
-  const int n_ctiles = n_ctiles_for(C, dtype);
-  uint4* frag = prep_next ? w.frag : nullptr;
-  int32_t* dirty = dirty_mode ? w.dirty : nullptr;
-  const int skip = dirty_mode == 2 ? 1 : 0;
-#define LKV_UPDATE(T, SPLIT)                                                                                    \
-  centroid_update_kernel<T, SPLIT><<<(unsigned)(SPLIT > 1 ? rows : (rows + 3) / 4), SPLIT > 4 ? 64 * SPLIT : 256, \
-                                     0, st>>>(static_cast<const T*>(keys), w.members, w.offsets, w.counts, cin,   \
-                                              cout, stride, N, C, rows, frag, w.cnorm, n_ctiles,                  \
-                                              prep_next ? 1 : 0, dirty, skip)
-#define LKV_UPDATE_T(T)                            \
-  if (rows < kSplit16Clusters && N / C >= kSplit16Members) LKV_UPDATE(T, 16); \
-  else if (rows < kSplit4Clusters) LKV_UPDATE(T, 4); \
-  else LKV_UPDATE(T, 1)
-  if (dtype == LOUISKV_BF16) {
-    LKV_UPDATE_T(uint16_t);
+  if (rows < kSplit4Clusters) {
+    a.blocks_per_slice = a.stride_e = C;
+    if (rows < kSplit16Clusters && N / C >= kSplit16Members)
+      centroid_update_kernel<T, 16><<<(unsigned)rows, 1024, 0, st>>>(a);
+    else
+      centroid_update_kernel<T, 4><<<(unsigned)rows, 256, 0, st>>>(a);
   } else {
-    LKV_UPDATE_T(float);
+    const int per = rows >= kShareClusters ? 4 : 1;   // clusters a wave takes when all are listed
+    a.dlist = list && per > 1 ? w.dlist : nullptr;
+    a.blocks_per_slice = ceil_div(C, 4 * per);
+    a.stride_e = 4 * a.blocks_per_slice;
+    centroid_update_kernel<T, 1><<<(unsigned)(S * a.blocks_per_slice), 256, 0, st>>>(a);
   }
-#undef LKV_UPDATE_T
-#undef LKV_UPDATE
   LKV_CHECK_LAUNCH();
   return LOUISKV_OK;
+}
+
+int launch_sum(const void* keys, int dtype, int64_t S, int N, int C, const Ws& w, const float* cin, float* cout,
+               int stride, bool prep_next, bool zero_counts, bool list, hipStream_t st) {
+  const int n_ctiles = n_ctiles_for(C, dtype);
+  return dtype == LOUISKV_BF16
+             ? launch_sum_t<uint16_t>(keys, S, N, C, n_ctiles, w, cin, cout, stride, prep_next, zero_counts, list, st)
+             : launch_sum_t<float>(keys, S, N, C, n_ctiles, w, cin, cout, stride, prep_next, zero_counts, list, st);
 }
 
 // Prompt K/V rows in perm order into the pools (each cluster one contiguous run).
@@ -1143,14 +1295,17 @@ int run_cluster(const void* keys, int dtype, int64_t S, int N, int C, int n_iter
   for (int it = 0; it < n_iters; ++it) {
     if (iter_events) LKV_CHECK_HIP(hipEventRecord(reinterpret_cast<hipEvent_t>(iter_events[2 * it]), s));
     // from the second iteration on (bf16), the assignment flags the clusters
-    // that keys entered or left and the update recomputes only those
-    const bool track = dtype == LOUISKV_BF16;
+    // that keys entered or left, keeps the counts up to date, and the update
+    // recomputes only those clusters
+    const bool track = dtype == LOUISKV_BF16 && it > 0;
+    const bool list = track && scatter_in_lds(C);
+    const bool last = it + 1 == n_iters;
     if ((st = launch_assign(keys, dtype, S, N, C, w, assign, true, it > 0, it == 0 ? 1 : 2, s, track)))
       return st;
     if (iter_events) LKV_CHECK_HIP(hipEventRecord(reinterpret_cast<hipEvent_t>(iter_events[2 * it + 1]), s));
-    if ((st = launch_scan_scatter(assign, S, N, C, w, s))) return st;
-    if ((st = launch_sum(keys, dtype, S, N, C, w, reps, reps, units_cap, it + 1 < n_iters, s,
-                         track ? (it == 0 ? 1 : 2) : 0)))
+    if ((st = launch_scan_scatter(assign, S, N, C, w, list, last, s))) return st;
+    if ((st = launch_sum(keys, dtype, S, N, C, w, reps, reps, units_cap, !last, !last && dtype != LOUISKV_BF16, list,
+                         s)))
       return st;
   }
   {
@@ -1408,7 +1563,10 @@ extern "C" int louiskv_kmeans_update(const void* keys, int32_t dtype, int64_t n_
   {
     // a fill kernel rather than a memset node, so the call stays safe to capture
     const int64_t n = n_slices * n_clusters;
-    fill_i32_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(w.counts, 0, n);
+    const unsigned grid = (unsigned)((n + 255) / 256);
+    fill_i32_kernel<<<grid, 256, 0, s>>>(w.counts, 0, n);
+    LKV_CHECK_LAUNCH();
+    fill_i32_kernel<<<grid, 256, 0, s>>>(w.cursor, 0, n);
     LKV_CHECK_LAUNCH();
   }
   const int bps = ceil_div(n_tokens, kCountKeys);
@@ -1416,9 +1574,9 @@ extern "C" int louiskv_kmeans_update(const void* keys, int32_t dtype, int64_t n_
   count_kernel<<<(unsigned)(n_slices * bps), 256, lds_ok ? (size_t)n_clusters * 4 : 0, s>>>(
       assign, w.counts, n_tokens, n_clusters, bps, lds_ok ? 1 : 0);
   LKV_CHECK_LAUNCH();
-  if ((st = launch_scan_scatter(assign, n_slices, n_tokens, n_clusters, w, s))) return st;
+  if ((st = launch_scan_scatter(assign, n_slices, n_tokens, n_clusters, w, false, true, s))) return st;
   if ((st = launch_sum(keys, dtype, n_slices, n_tokens, n_clusters, w, centroids_in, centroids_out,
-                       centroid_stride, false, s)))
+                       centroid_stride, false, false, false, s)))
     return st;
   if (counts)
     LKV_CHECK_HIP(hipMemcpyAsync(counts, w.counts, sizeof(int32_t) * n_slices * n_clusters,
