@@ -153,7 +153,7 @@ size_t louiskv_cluster_prefill_workspace_size(int64_t n_slices, int32_t n_tokens
  *             are written in perm order (keys from `keys`, values from
  *             `values`; v_pool requires values).  pool_on_host: see Pointers.
  * iter_events NULL or an array of 2*n_iters hipEvent_t recorded on `stream`
- *             just before and after each iteration's assignment kernel, for
+ *             just before and after each iteration's assignment, for
  *             callers that time it.
  * Requires 1 <= n_clusters <= n_tokens, n_clusters <= units_cap, n_iters >= 1,
  * pool_rows >= n_tokens when a pool is given.

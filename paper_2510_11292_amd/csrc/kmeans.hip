@@ -5,20 +5,23 @@
 // Per Lloyd iteration:
 //   prep     centroid operand for the matrix cores: -2 * op(c) laid out as MFMA
 //            A-fragments (op = bf16 RNE rounding for bf16 keys, identity for fp32),
-//            plus ||op(c)||^2 (float64 sum, rounded to fp32); zero the counts.
+//            plus ||op(c)||^2 (float64 sum, rounded to fp32).
 //   assign   D = ||op(c)||^2 - 2 op(c).k on MFMA (the norm enters as the
-//            accumulator input), running argmin per key kept in registers,
-//            block histogram of the chosen clusters into counts.
-//   scan     exclusive scan of counts -> CSR offsets and scatter cursors.
-//   scatter  key ids into their cluster's member range (order unspecified).
+//            accumulator input), running argmin per key kept in registers;
+//            the counts follow (a block histogram, later each moved key).
+//   scatter  scan of the counts -> CSR offsets, and key ids into their cluster's
+//            member range (order unspecified).
 //   sum      centroid = float64 sum of members / count, rounded once to fp32;
 //            empty clusters keep their centroid.  Sums of bf16 or fp32 inputs
 //            are exact in float64 at these sizes, so the order is irrelevant.
-//            The same kernel writes the next iteration's operand and clears
-//            the counts (prep runs once, before the first iteration).
-// From the second iteration on, the assignment starts each key's running
+//            The same kernel writes the next iteration's operand (prep runs
+//            once, before the first iteration).
+// From the second iteration on (bf16) the assignment starts each key's running
 // minimum at a bound from its previous centroid, so the index search runs
-// only for tiles that hold a closer centroid.
+// only for tiles that hold a closer centroid, and only the clusters that a key
+// entered or left are scattered and recomputed.  In large calls, from the
+// fourth iteration on, only those clusters' centroids are swept, and the few
+// keys for which that is not enough take a launch of their own.
 // After the last iteration, finalize sorts each member range ascending (the
 // perm output), writes the unit table, and pack copies K/V rows into the pool.
 #include "common.h"
@@ -258,14 +261,39 @@ __device__ __forceinline__ int tile_find(const floatx16& x, float m) {
 #undef LKV_CMP
 #undef LKV_CND
 
+// The second smallest of the lane's 16 results (equal to the smallest where
+// two are): the medians of the five triples that tile_min takes the minima of,
+// merged pair by pair.  A NaN among the results can only make it smaller.
+__device__ __forceinline__ float tile_second(const floatx16& x) {
+  float m = x[15], t = __builtin_inff();
+#pragma unroll
+  for (int v = 0; v < 15; v += 3) {
+    const float a = __builtin_fminf(__builtin_fminf(x[v], x[v + 1]), x[v + 2]);
+    const float b = __builtin_amdgcn_fmed3f(x[v], x[v + 1], x[v + 2]);
+    t = __builtin_fminf(__builtin_fminf(t, b), __builtin_fmaxf(m, a));
+    m = __builtin_fminf(m, a);
+  }
+  return t;
+}
+
+// The smallest float above x (x not NaN; +inf stays).
+__device__ __forceinline__ float next_up(float x) {
+  const int i = __float_as_int(x);
+  if (x == __builtin_inff()) return x;
+  return __int_as_float(x == 0.f ? 1 : i > 0 ? i + 1 : i - 1);
+}
+
 // One stage of the bf16 sweep.  `cur` holds stage st (its copy was waited
 // for); the copy of stage st + kBf16Ring - 1 goes into `nxt`, the buffer that
 // stage st - 1 used.
-template <int kKT>
+// kSecond: sec collects the minimum over every centroid but the winner (a
+// starting bound, bidx -1, is no centroid's value and stays out of it); it
+// costs one minimum per tile outside the search branch.
+template <int kKT, bool kSecond>
 __device__ __forceinline__ void bf16_stage(const char* cur, char* nxt, const uint4* fslice,
                                            const float* cslice, int st, int n_stages, int wave, int lane, int h,
                                            const bf16x8_t (&b)[kKT][kBf16Steps], float (&best)[kKT],
-                                           int (&bidx)[kKT]) {
+                                           int (&bidx)[kKT], float (&sec)[kKT]) {
   wait_vm_stages(min(kBf16Ring - 2, n_stages - 1 - st));
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   __builtin_amdgcn_s_barrier();   // stage st is in LDS for all waves; stage st-1's buffer is free
@@ -313,9 +341,16 @@ __device__ __forceinline__ void bf16_stage(const char* cur, char* nxt, const uin
       if (__builtin_amdgcn_ballot_w64(better)) {
         int sel = better ? 1 : 0;
         int id = cbase + tile_find(acc[kt], m);
-        asm volatile("" : "+v"(sel), "+v"(id));
+        float m2 = kSecond ? tile_second(acc[kt]) : 0.f;
+        asm volatile("" : "+v"(sel), "+v"(id), "+v"(m2));
+        if constexpr (kSecond) {
+          const float won = __builtin_fminf(__builtin_fminf(sec[kt], m2), bidx[kt] >= 0 ? best[kt] : __builtin_inff());
+          sec[kt] = sel ? won : __builtin_fminf(sec[kt], m);
+        }
         bidx[kt] = sel ? id : bidx[kt];
         best[kt] = sel ? m : best[kt];
+      } else if constexpr (kSecond) {
+        sec[kt] = __builtin_fminf(sec[kt], m);
       }
     }
   }
@@ -327,21 +362,21 @@ __device__ __forceinline__ void bf16_stage(const char* cur, char* nxt, const uin
 // which buffer it touches; it then waits only where the code says so instead
 // of draining all copies in flight before each read.  best/bidx come in
 // holding the starting bound (and -1).
-template <int kKT>
+template <int kKT, bool kSecond>
 __device__ __forceinline__ void bf16_sweep(char* __restrict__ r0, char* __restrict__ r1, char* __restrict__ r2,
                                            char* __restrict__ r3, const uint4* fslice, const float* cslice,
                                            int n_stages, int wave, int lane, int h,
                                            const bf16x8_t (&b)[kKT][kBf16Steps], float (&best)[kKT],
-                                           int (&bidx)[kKT]) {
+                                           int (&bidx)[kKT], float (&sec)[kKT]) {
   // the first kBf16Ring - 1 stages were copied by the caller (bf16_prologue)
   for (int st = 0; st < n_stages; st += kBf16Ring) {
-    bf16_stage<kKT>(r0, r3, fslice, cslice, st, n_stages, wave, lane, h, b, best, bidx);
+    bf16_stage<kKT, kSecond>(r0, r3, fslice, cslice, st, n_stages, wave, lane, h, b, best, bidx, sec);
     if (st + 1 >= n_stages) break;
-    bf16_stage<kKT>(r1, r0, fslice, cslice, st + 1, n_stages, wave, lane, h, b, best, bidx);
+    bf16_stage<kKT, kSecond>(r1, r0, fslice, cslice, st + 1, n_stages, wave, lane, h, b, best, bidx, sec);
     if (st + 2 >= n_stages) break;
-    bf16_stage<kKT>(r2, r1, fslice, cslice, st + 2, n_stages, wave, lane, h, b, best, bidx);
+    bf16_stage<kKT, kSecond>(r2, r1, fslice, cslice, st + 2, n_stages, wave, lane, h, b, best, bidx, sec);
     if (st + 3 >= n_stages) break;
-    bf16_stage<kKT>(r3, r2, fslice, cslice, st + 3, n_stages, wave, lane, h, b, best, bidx);
+    bf16_stage<kKT, kSecond>(r3, r2, fslice, cslice, st + 3, n_stages, wave, lane, h, b, best, bidx, sec);
   }
 }
 
@@ -355,44 +390,123 @@ __device__ __forceinline__ void bf16_prologue(char* __restrict__ r0, char* __res
   if (n_stages > 2) stage_async(fslice, cslice, 2, r2, wave, lane);
 }
 
+// What the assignment of a bf16 clustering reads and writes.
+struct AssignArgs {
+  const uint16_t* keys;
+  const uint4* frag;
+  const float* cnorm;
+  int32_t *assign, *counts;
+  int n_tokens, n_clusters, n_ctiles, blocks_per_slice, hist_in_lds;
+  uint4* kswz;
+  int kswz_mode;
+  // from the second iteration of a clustering on (kTrack)
+  int32_t* dirty;          // out: clusters that a key entered or left
+  float *best, *sec;       // per key: D to its cluster, and a lower bound on D to every other
+  const int32_t *ndirty, *dmap, *dlist;   // the clusters recomputed since the last assignment
+  int32_t* recorded;       // per slice, two entries used in turn: the last assignment left `best` and `sec`
+  int turn;
+  const uint4* cfrag;      // their operands, compacted in ascending order
+  const float* ccnorm;
+  int32_t *fail, *nfail;   // out: keys left to assign_rest_kernel
+};
+
+// A key's move from cluster `from` to `to`: both are recomputed, and counted
+// anew (row: the slice's first cluster).
+__device__ __forceinline__ void move_key(const AssignArgs& a, size_t row, int from, int to) {
+  a.dirty[row + to] = 1;
+  atomicAdd(&a.counts[row + to], 1);
+  if (from >= 0 && from < a.n_clusters) {
+    a.dirty[row + from] = 1;
+    atomicSub(&a.counts[row + from], 1);
+  }
+}
+
+// Sweep over the recomputed clusters alone up to this share of all of them
+// (percent); above, the full sweep costs no more and leaves no key over.
+// Above the second share the next one will most likely be full too, and a full
+// sweep that records takes 5-12% longer, so it records nothing.
+constexpr int kPartPercent = 80;
+constexpr int kRecordPercent = 95;
+
+// Modes of the bf16 assignment: on its own or first of a clustering; later
+// iterations, which start from the last assignment (kTrack in the kernel); and
+// those that also record `best` and `sec` and may sweep the recomputed
+// clusters alone.
+constexpr int kAssignPlain = 0, kAssignMoves = 1, kAssignRecord = 2;
+
 // bf16 keys: each wave holds kBf16KeyTiles tiles of 32 keys as MFMA B operands
 // for the whole sweep; centroid tiles stream through a ring of kBf16Ring LDS
 // stage buffers, copied kBf16Ring - 1 stages ahead.  Lane l owns key column
 // l % 32 and rows 8*(v/4) + 4*(l/32) + (v%4) of each 32x32 result, so the
 // argmin over a tile is in-lane; the two lane halves merge at the end.
+//
+// kAssignRecord (third iteration on).  D(k, c) depends on the key and on c's
+// operand alone, so it changes only for the clusters the last update
+// recomputed.  Every such assignment records, per key, D to its cluster
+// (best) and a lower bound on D to all others (sec); the next one then has to
+// evaluate the recomputed clusters only:
+//  - the key's own cluster was not recomputed: `best` still holds, the
+//    clusters not recomputed are no nearer than before, and the argmin is the
+//    lower of `best` and the recomputed clusters' minimum (ties to the lower
+//    id: the sweep starts just above `best`, so an equal value is found);
+//  - it was: the recomputed clusters' minimum is the argmin if it is below
+//    `sec`, which bounds every other cluster; if not, the key goes to the
+//    fail list and assign_rest_kernel sweeps all centroids for it.
+// Both compare the same matrix-core values as the full sweep, so assignments,
+// and with them all outputs, are the same bit for bit.  On the benchmark's
+// keys (32768 around 1024 centres) 93, 74, 51, 40, 27, 19, 15 and 10% of the
+// clusters are recomputed before iterations 3 to 10, and 1.4% of the keys or
+// fewer are left over.
+template <int kMode>
 __global__ __launch_bounds__(kBf16Threads, 8 / kBf16Waves)
-void assign_bf16_kernel(const uint16_t* __restrict__ keys, const uint4* __restrict__ frag,
-                        const float* __restrict__ cnorm, int32_t* __restrict__ assign,
-                        int32_t* __restrict__ counts, int n_tokens, int n_clusters, int n_ctiles,
-                        int blocks_per_slice, int hist_in_lds, int use_bound, uint4* __restrict__ kswz,
-                        int kswz_mode, int32_t* __restrict__ dirty) {
+void assign_bf16_kernel(const AssignArgs a) {
+  constexpr bool kTrack = kMode >= kAssignMoves, kRecord = kMode == kAssignRecord;
   __shared__ __align__(16) char s_ring0[kBf16StageBytes];
   __shared__ __align__(16) char s_ring1[kBf16StageBytes];
   __shared__ __align__(16) char s_ring2[kBf16StageBytes];
   __shared__ __align__(16) char s_ring3[kBf16StageBytes];
   static_assert(kBf16Ring == 4, "the stage loop below is unrolled for four buffers");
 
+  const int n_tokens = a.n_tokens, n_clusters = a.n_clusters;
   const int lb = xcd_local_block(blockIdx.x, gridDim.x);
-  const int slice = lb / blocks_per_slice;
-  const int kb = lb - slice * blocks_per_slice;
+  const int slice = lb / a.blocks_per_slice;
+  const int kb = lb - slice * a.blocks_per_slice;
   // the wave index lives in an SGPR (it addresses the copies every stage)
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, h = lane >> 5,
             j = lane & 31;
   const int key_base = kb * kBf16KeysPerBlock + wave * (32 * kBf16KeyTiles);
-  const uint16_t* kslice = keys + (size_t)slice * n_tokens * kHeadDim;
-  const uint4* fslice = frag + (size_t)slice * n_ctiles * kBf16TileU4;
-  const float* cslice = cnorm + (size_t)slice * n_ctiles * kTileC;
-  const int n_stages = n_ctiles / kBf16StageTiles;   // n_ctiles is padded to whole stages
+  const uint16_t* kslice = a.keys + (size_t)slice * n_tokens * kHeadDim;
+  const uint4* fslice = a.frag + (size_t)slice * a.n_ctiles * kBf16TileU4;
+  const float* cslice = a.cnorm + (size_t)slice * a.n_ctiles * kTileC;
+  int32_t* assign = a.assign + (size_t)slice * n_tokens;
+  // the operands swept: all of the slice's, or the recomputed ones
+  bool some = false, record = false;
+  const uint4* fsweep = fslice;
+  const float* csweep = cslice;
+  int n_stages = a.n_ctiles / kBf16StageTiles;   // n_ctiles is padded to whole stages
+  if constexpr (kRecord) {
+    const int nd = __builtin_amdgcn_readfirstlane(a.ndirty[slice]);
+    const int had = __builtin_amdgcn_readfirstlane(a.recorded[2 * slice + (a.turn ^ 1)]);
+    some = had && nd * 100 <= n_clusters * kPartPercent;
+    record = some || nd * 100 <= n_clusters * kRecordPercent;
+    if (kb == 0 && tid == 0) a.recorded[2 * slice + a.turn] = record ? 1 : 0;
+    if (some) {
+      if (nd == 0) return;                        // no centroid changed, so no key does
+      fsweep = a.cfrag + (size_t)slice * a.n_ctiles * kBf16TileU4;
+      csweep = a.ccnorm + (size_t)slice * a.n_ctiles * kTileC;
+      n_stages = (nd + kBf16StageTiles * kTileC - 1) / (kBf16StageTiles * kTileC);
+    }
+  }
 
   // Start-up latency is the block's fixed cost, so the loads that do not
   // depend on each other are issued together: the ring's first copies, the
   // previous assignment (for the bound), then the keys.
-  bf16_prologue(s_ring0, s_ring1, s_ring2, fslice, cslice, n_stages, wave, lane);
+  bf16_prologue(s_ring0, s_ring1, s_ring2, fsweep, csweep, n_stages, wave, lane);
   int zp[kBf16KeyTiles];
 #pragma unroll
   for (int kt = 0; kt < kBf16KeyTiles; ++kt) {
     const int key = key_base + kt * 32 + j;
-    zp[kt] = (use_bound && key < n_tokens) ? assign[(size_t)slice * n_tokens + key] : -1;
+    zp[kt] = (kTrack && key < n_tokens) ? assign[key] : -1;
   }
   // Key operands.  In B-operand order a load instruction touches 64 rows
   // (16 bytes of each), which makes the block's start slow; so the first
@@ -400,8 +514,9 @@ void assign_bf16_kernel(const uint16_t* __restrict__ keys, const uint4* __restri
   // 1, one contiguous KiB per instruction, padding keys zero), and the later
   // iterations read them back contiguously (kswz_mode 2).
   bf16x8_t b[kBf16KeyTiles][kBf16Steps];
-  uint4* zs = kswz + (((size_t)slice * blocks_per_slice + kb) * kBf16Waves + wave) * (kBf16KeyTiles * kBf16Steps * 64);
-  if (kswz_mode == 2) {
+  uint4* zs =
+      a.kswz + (((size_t)slice * a.blocks_per_slice + kb) * kBf16Waves + wave) * (kBf16KeyTiles * kBf16Steps * 64);
+  if (a.kswz_mode == 2) {
 #pragma unroll
     for (int kt = 0; kt < kBf16KeyTiles; ++kt)
 #pragma unroll
@@ -417,7 +532,7 @@ void assign_bf16_kernel(const uint16_t* __restrict__ keys, const uint4* __restri
         b[kt][s] = __builtin_bit_cast(bf16x8_t, v);
       }
     }
-    if (kswz_mode == 1) {
+    if (a.kswz_mode == 1) {
 #pragma unroll
       for (int kt = 0; kt < kBf16KeyTiles; ++kt)
 #pragma unroll
@@ -432,14 +547,22 @@ void assign_bf16_kernel(const uint16_t* __restrict__ keys, const uint4* __restri
   // <= 7.2e-6 (||c||^2 + ||k||^2), and the margin is 3e-5 of that.  Tiles whose
   // minimum does not beat the bound skip the index search; the nearest
   // centroid's value is strictly below it, so the result is unchanged.
-  float best[kBf16KeyTiles];
+  // In a sweep over the recomputed clusters the bound is the recorded `best`
+  // (own cluster not recomputed) or `sec`.
+  float best[kBf16KeyTiles], sec[kBf16KeyTiles];
   int bidx[kBf16KeyTiles];
 #pragma unroll
   for (int kt = 0; kt < kBf16KeyTiles; ++kt) {
     bidx[kt] = -1;
     best[kt] = __builtin_inff();
-    const bool have = zp[kt] >= 0 && zp[kt] < n_clusters;
-    if (__builtin_amdgcn_ballot_w64(have)) {
+    sec[kt] = __builtin_inff();
+    const bool have = kTrack && zp[kt] >= 0 && zp[kt] < n_clusters;
+    if (some) {
+      const int key = key_base + kt * 32 + j;
+      if (have)
+        best[kt] = a.dmap[(size_t)slice * n_clusters + zp[kt]] < 0 ? next_up(a.best[(size_t)slice * n_tokens + key])
+                                                                   : a.sec[(size_t)slice * n_tokens + key];
+    } else if (kTrack && __builtin_amdgcn_ballot_w64(have)) {
       typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
       const int zc = have ? zp[kt] : 0;
       // the lane's 64 dimensions of -2 op(c): A-fragment row zc % 32, half h
@@ -474,8 +597,12 @@ void assign_bf16_kernel(const uint16_t* __restrict__ keys, const uint4* __restri
   for (int kt = 0; kt < kBf16KeyTiles; ++kt)
 #pragma unroll
     for (int s = 0; s < kBf16Steps; ++s) asm volatile("" ::"v"(b[kt][s]));
-  bf16_sweep<kBf16KeyTiles>(s_ring0, s_ring1, s_ring2, s_ring3, fslice, cslice, n_stages, wave, lane, h, b, best,
-                            bidx);
+  if (kRecord && record)
+    bf16_sweep<kBf16KeyTiles, true>(s_ring0, s_ring1, s_ring2, s_ring3, fsweep, csweep, n_stages, wave, lane, h, b,
+                                    best, bidx, sec);
+  else
+    bf16_sweep<kBf16KeyTiles, false>(s_ring0, s_ring1, s_ring2, s_ring3, fsweep, csweep, n_stages, wave, lane, h, b,
+                                     best, bidx, sec);
 
   int zi[kBf16KeyTiles];
   bool zv[kBf16KeyTiles];
@@ -483,32 +610,191 @@ void assign_bf16_kernel(const uint16_t* __restrict__ keys, const uint4* __restri
   for (int kt = 0; kt < kBf16KeyTiles; ++kt) {
     const float ob = __shfl_xor(best[kt], 32, kWave);
     const int oi = __shfl_xor(bidx[kt], 32, kWave);
+    const float os = kRecord ? __shfl_xor(sec[kt], 32, kWave) : 0.f;
     // a half with no value below its starting bound holds index -1
-    if (bidx[kt] < 0 || (oi >= 0 && (ob < best[kt] || (ob == best[kt] && oi < bidx[kt])))) {
+    const bool other = bidx[kt] < 0 || (oi >= 0 && (ob < best[kt] || (ob == best[kt] && oi < bidx[kt])));
+    if constexpr (kRecord) {
+      const float lost = other ? (bidx[kt] >= 0 ? best[kt] : __builtin_inff()) : (oi >= 0 ? ob : __builtin_inff());
+      sec[kt] = __builtin_fminf(__builtin_fminf(sec[kt], os), lost);
+    }
+    if (other) {
       best[kt] = ob;
       bidx[kt] = oi;
     }
-    if (bidx[kt] < 0) bidx[kt] = 0;   // only reachable with non-finite inputs
     const int key = key_base + kt * 32 + j;
-    zi[kt] = bidx[kt];
     zv[kt] = (h == 0) && key < n_tokens;
-    if (zv[kt]) assign[(size_t)slice * n_tokens + key] = bidx[kt];
-    // a key that changed cluster marks both clusters for the update and moves
-    // from one's count to the other's
-    if (dirty && zv[kt] && bidx[kt] != zp[kt]) {
-      const size_t base = (size_t)slice * n_clusters;
-      dirty[base + bidx[kt]] = 1;
-      atomicAdd(&counts[base + bidx[kt]], 1);
-      if (zp[kt] >= 0 && zp[kt] < n_clusters) {
-        dirty[base + zp[kt]] = 1;
-        atomicSub(&counts[base + zp[kt]], 1);
+    if constexpr (kTrack) {
+      const size_t kr = (size_t)slice * n_tokens + key, cr = (size_t)slice * n_clusters;
+      int id = bidx[kt];
+      float bv = best[kt], sv = sec[kt];
+      bool left = false;
+      if (some) {
+        if (zv[kt]) {
+          if (id >= 0) id = a.dlist[cr + id];
+          const float bo = a.best[kr], so = a.sec[kr];
+          if (a.dmap[cr + zp[kt]] < 0) {
+            if (id >= 0 && (bv < bo || (bv == bo && id < zp[kt]))) {
+              sv = __builtin_fminf(__builtin_fminf(so, bo), sv);
+            } else {
+              sv = __builtin_fminf(__builtin_fminf(so, id >= 0 ? bv : __builtin_inff()), sv);
+              bv = bo;
+              id = zp[kt];
+            }
+          } else {
+            left = id < 0;
+            sv = __builtin_fminf(so, sv);
+          }
+        }
+        const uint64_t m = __builtin_amdgcn_ballot_w64(left);
+        if (m) {
+          int at = 0;
+          if (lane == (int)__builtin_ctzll(m)) at = atomicAdd(&a.nfail[slice], __popcll(m));
+          at = __shfl(at, (int)__builtin_ctzll(m), kWave);
+          if (left)
+            a.fail[(size_t)slice * n_tokens + at +
+                   __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0))] = key;
+        }
+      } else if (id < 0) {
+        id = 0;   // only reachable with non-finite inputs
+        bv = __builtin_inff();
       }
+      if (zv[kt] && !left) {
+        assign[key] = id;
+        if (kRecord && record) {
+          a.best[kr] = bv;
+          a.sec[kr] = sv;
+        }
+        // a key that changed cluster marks both clusters for the update and
+        // moves from one's count to the other's
+        if (id != zp[kt]) move_key(a, cr, zp[kt], id);
+      }
+    } else {
+      if (bidx[kt] < 0) bidx[kt] = 0;   // only reachable with non-finite inputs
+      zi[kt] = bidx[kt];
+      if (zv[kt]) assign[key] = bidx[kt];
     }
   }
-  if (counts && !dirty) {
+  if (!kTrack && a.counts) {
     __syncthreads();
-    block_histogram(reinterpret_cast<int*>(s_ring0), hist_in_lds, n_clusters,
-                    counts + (size_t)slice * n_clusters, zi, zv, kBf16KeyTiles);
+    block_histogram(reinterpret_cast<int*>(s_ring0), a.hist_in_lds, n_clusters,
+                    a.counts + (size_t)slice * n_clusters, zi, zv, kBf16KeyTiles);
+  }
+}
+
+// The keys that a sweep over the recomputed clusters left over: 32 kKT of a
+// slice's list per block, each of its NW waves sweeps every NW-th centroid
+// tile for all of them straight from L2, and the waves' results merge in LDS.
+// The keys are few and scattered: a block per 512 of them, as above, would
+// leave most of the chip idle and its one long sweep would be the iteration's
+// time.  A wave's first two tiles are loaded before anything about the keys is
+// known.  Few slices: 32 keys a block for the shortest chain; many slices: 64
+// keys a block, so that a tile is read from L2 half as often.
+template <int kKT, int NW>
+__global__ __launch_bounds__(64 * NW)
+void assign_rest_kernel(const AssignArgs a, int parts) {
+  constexpr int kKeys = 32 * kKT;
+  __shared__ float s_best[NW][kKeys], s_sec[NW][kKeys];
+  __shared__ int s_idx[NW][kKeys];
+  const int slice = blockIdx.x / parts;
+  const int part = blockIdx.x - slice * parts;
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, h = lane >> 5,
+            j = lane & 31;
+  const int32_t* list = a.fail + (size_t)slice * a.n_tokens;
+  const uint16_t* kslice = a.keys + (size_t)slice * a.n_tokens * kHeadDim;
+  const uint4* fslice = a.frag + (size_t)slice * a.n_ctiles * kBf16TileU4;
+  const float* cslice = a.cnorm + (size_t)slice * a.n_ctiles * kTileC;
+  auto load_tile = [&](int t, bf16x8_t (&x)[kBf16Steps]) {
+    const uint4* f = fslice + (size_t)min(t, a.n_ctiles - 1) * kBf16TileU4 + lane;
+#pragma unroll
+    for (int s = 0; s < kBf16Steps; ++s) x[s] = __builtin_bit_cast(bf16x8_t, f[s * 64]);
+  };
+  bf16x8_t x0[kBf16Steps], x1[kBf16Steps];
+  load_tile(w, x0);
+  const int nf = min(a.nfail[slice], a.n_tokens);
+  for (int k0 = part * kKeys; k0 < nf; k0 += parts * kKeys) {
+    bf16x8_t b[kKT][kBf16Steps];
+    float best[kKT], sec[kKT];
+    int bidx[kKT];
+#pragma unroll
+    for (int kt = 0; kt < kKT; ++kt) {
+      const int key = list[min(k0 + kt * 32 + j, nf - 1)];
+      const uint4* src = reinterpret_cast<const uint4*>(kslice + (size_t)key * kHeadDim + 64 * h);
+#pragma unroll
+      for (int s = 0; s < kBf16Steps; ++s) b[kt][s] = __builtin_bit_cast(bf16x8_t, src[s]);
+      best[kt] = sec[kt] = __builtin_inff();
+      bidx[kt] = -1;
+    }
+    if (k0 != part * kKeys) load_tile(w, x0);
+    auto tile = [&](int t, const bf16x8_t (&x)[kBf16Steps]) {
+      floatx16 cn;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const float4 v = *reinterpret_cast<const float4*>(cslice + t * kTileC + 8 * g + 4 * h);
+        cn[4 * g + 0] = v.x; cn[4 * g + 1] = v.y; cn[4 * g + 2] = v.z; cn[4 * g + 3] = v.w;
+      }
+      floatx16 acc[kKT];
+#pragma unroll
+      for (int kt = 0; kt < kKT; ++kt) acc[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], b[kt][0], cn, 0, 0, 0);
+#pragma unroll
+      for (int s = 1; s < kBf16Steps; ++s)
+#pragma unroll
+        for (int kt = 0; kt < kKT; ++kt)
+          acc[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[s], b[kt][s], acc[kt], 0, 0, 0);
+#pragma unroll
+      for (int kt = 0; kt < kKT; ++kt) {
+        const float m = tile_min(acc[kt]);
+        float m2 = tile_second(acc[kt]);
+        int id = t * kTileC + 4 * h + tile_find(acc[kt], m);
+        int sel = m < best[kt] ? 1 : 0;
+        asm volatile("" : "+v"(sel), "+v"(id), "+v"(m2));
+        const float won = __builtin_fminf(__builtin_fminf(sec[kt], m2), best[kt]);   // best is +inf until one is found
+        sec[kt] = sel ? won : __builtin_fminf(sec[kt], m);
+        bidx[kt] = sel ? id : bidx[kt];
+        best[kt] = sel ? m : best[kt];
+      }
+    };
+    for (int t = w; t < a.n_ctiles; t += 2 * NW) {
+      load_tile(t + NW, x1);
+      tile(t, x0);
+      if (t + 2 * NW < a.n_ctiles) load_tile(t + 2 * NW, x0);
+      if (t + NW < a.n_ctiles) tile(t + NW, x1);
+    }
+    __syncthreads();   // the last round's results have been read
+#pragma unroll
+    for (int kt = 0; kt < kKT; ++kt) {
+      const float ob = __shfl_xor(best[kt], 32, kWave), os = __shfl_xor(sec[kt], 32, kWave);
+      const int oi = __shfl_xor(bidx[kt], 32, kWave);
+      const bool other = bidx[kt] < 0 || (oi >= 0 && (ob < best[kt] || (ob == best[kt] && oi < bidx[kt])));
+      if (h == 0) {
+        s_best[w][kt * 32 + j] = other ? ob : best[kt];
+        s_idx[w][kt * 32 + j] = other ? oi : bidx[kt];
+        s_sec[w][kt * 32 + j] = __builtin_fminf(__builtin_fminf(sec[kt], os), other ? best[kt] : ob);
+      }
+    }
+    __syncthreads();
+    if (tid < kKeys && k0 + tid < nf) {
+      const int key = list[k0 + tid];
+      const size_t kr = (size_t)slice * a.n_tokens + key;
+      const int old = a.assign[kr];
+      float bv = __builtin_inff(), sv = __builtin_inff();
+      int id = -1;
+#pragma unroll
+      for (int q = 0; q < NW; ++q) {
+        const float ob = s_best[q][tid];
+        const int oi = s_idx[q][tid];
+        const bool other = oi >= 0 && (id < 0 || ob < bv || (ob == bv && oi < id));
+        sv = __builtin_fminf(__builtin_fminf(sv, s_sec[q][tid]), other ? bv : ob);
+        if (other) {
+          bv = ob;
+          id = oi;
+        }
+      }
+      if (id < 0) id = 0;   // only reachable with non-finite inputs
+      a.assign[kr] = id;
+      a.best[kr] = bv;
+      a.sec[kr] = sv;
+      if (id != old) move_key(a, (size_t)slice * a.n_clusters, old, id);
+    }
   }
 }
 
@@ -697,13 +983,16 @@ __device__ __forceinline__ int block256_scan(int v, int* s_w, int& excl) {
 // the update).  Block 0 of a slice writes the offsets.
 // With `dirty` only the keys of flagged clusters are placed, the ones the
 // update reads, and block 0 writes the list of those clusters in ascending
-// order and its length.
+// order, each one's place in it (dmap, -1 for the others) and its length, and
+// empties the list of left-over keys for the next assignment.
 template <int kPer>
 __global__ __launch_bounds__(256)
 void scatter_kernel(const int32_t* __restrict__ assign, const int32_t* __restrict__ counts,
                     int32_t* __restrict__ cursor, int32_t* __restrict__ offsets, int32_t* __restrict__ members,
                     int n_tokens, int n_clusters, int blocks_per_slice, const int32_t* __restrict__ dirty,
-                    int32_t* __restrict__ dlist, int32_t* __restrict__ ndirty, int place_all) {
+                    int32_t* __restrict__ dlist, int32_t* __restrict__ dmap, int32_t* __restrict__ ndirty,
+                    int32_t* __restrict__ nfail, uint4* __restrict__ cfrag, float* __restrict__ ccnorm, int n_ctiles,
+                    int place_all, int32_t* __restrict__ clear_recorded) {
   extern __shared__ __align__(16) char smem[];
   __shared__ int s_w[4];
   int* hist = reinterpret_cast<int*>(smem);
@@ -721,46 +1010,66 @@ void scatter_kernel(const int32_t* __restrict__ assign, const int32_t* __restric
     z[q] = i < n_tokens ? assign[(size_t)slice * n_tokens + i] : -1;
     if (z[q] >= n_clusters) z[q] = -1;   // same keys as the count
   }
-  for (int i = tid; i < n_clusters; i += 256) hist[i] = counts[crow + i];
+  // counts, the top bit set for the clusters not to be placed
+  constexpr int kSkip = 1 << 31;
+  for (int i = tid; i < n_clusters; i += 256) hist[i] = counts[crow + i] | (dr && !dr[i] ? kSkip : 0);
   __syncthreads();
   // a thread's run of consecutive clusters
   const int per = (n_clusters + 255) / 256;
   const int c0 = min(tid * per, n_clusters), c1 = min(c0 + per, n_clusters);
   int sum = 0;
-  for (int c = c0; c < c1; ++c) sum += hist[c];
+  int nd = 0;
+  for (int c = c0; c < c1; ++c) {
+    sum += hist[c] & ~kSkip;
+    nd += hist[c] >= 0;
+  }
   int at;
   const int total = block256_scan(sum, s_w, at);
   for (int c = c0; c < c1; ++c) {
     const int n = hist[c];
-    base[c] = at;
+    base[c] = at | (n & kSkip);
     hist[c] = 0;
-    at += n;
+    at += n & ~kSkip;
   }
   __syncthreads();
   if (kb == 0) {
     int32_t* off = offsets + (size_t)slice * (n_clusters + 1);
-    for (int i = tid; i < n_clusters; i += 256) off[i] = base[i];
+    for (int i = tid; i < n_clusters; i += 256) off[i] = base[i] & ~kSkip;
     if (tid == 0) off[n_clusters] = total;
     if (dr) {
-      int nd = 0;
-      for (int c = c0; c < c1; ++c) nd += dr[c] != 0;
       int k;
       const int all = block256_scan(nd, s_w, k);
-      for (int c = c0; c < c1; ++c)
-        if (dr[c]) dlist[crow + k++] = c;
-      if (tid == 0) ndirty[slice] = all;
+      for (int c = c0; c < c1; ++c) {
+        const bool d = base[c] >= 0;
+        dmap[crow + c] = d ? k : -1;
+        if (d) dlist[crow + k++] = c;
+      }
+      // the compacted operand's last stage is padded with rows that never win
+      constexpr int kStageC = kBf16StageTiles * kTileC;
+      const int pad = (all + kStageC - 1) / kStageC * kStageC - all;
+      for (int i = tid; i < pad * 16; i += 256) {
+        const int r = all + i / 16, q = i % 16;   // 16-byte piece q of row r
+        cfrag[((size_t)slice * n_ctiles + r / kTileC) * kBf16TileU4 + (q & 7) * 64 + (q >> 3) * 32 + r % kTileC] =
+            make_uint4(0, 0, 0, 0);
+        if (q == 0) ccnorm[(size_t)slice * n_ctiles * kTileC + r] = __builtin_inff();
+      }
+      if (tid == 0) {
+        ndirty[slice] = all;
+        nfail[slice] = 0;
+        if (clear_recorded) clear_recorded[2 * slice] = clear_recorded[2 * slice + 1] = 0;
+      }
     }
   }
   if (dr && !place_all) {
 #pragma unroll
     for (int q = 0; q < kPer; ++q)
-      if (z[q] >= 0 && !dr[z[q]]) z[q] = -1;
+      if (z[q] >= 0 && base[z[q]] < 0) z[q] = -1;
   }
 #pragma unroll
   for (int q = 0; q < kPer; ++q) pos[q] = z[q] >= 0 ? atomicAdd(&hist[z[q]], 1) : 0;
   __syncthreads();
   for (int i = tid; i < n_clusters; i += 256)
-    if (hist[i]) base[i] += atomicAdd(&cursor[crow + i], hist[i]);
+    if (hist[i]) base[i] = (base[i] & ~kSkip) + atomicAdd(&cursor[crow + i], hist[i]);
   __syncthreads();
 #pragma unroll
   for (int q = 0; q < kPer; ++q)
@@ -798,7 +1107,9 @@ struct UpdateArgs {
   uint4* frag;
   float* cnorm;
   int n_ctiles, zero_counts;
-  int32_t *dirty, *dlist, *ndirty;
+  int32_t *dirty, *dlist, *dmap, *ndirty;
+  uint4* cfrag;       // the recomputed clusters' operands in list order, with frag and dirty
+  float* ccnorm;
 };
 
 template <class T, int kSplit>
@@ -822,7 +1133,8 @@ void centroid_update_kernel(const UpdateArgs<T> a) {
     const int c = a.dlist ? a.dlist[crow + e] : e;
     const int n = a.counts[crow + c];
     const int off = a.offsets[(size_t)s * (a.n_clusters + 1) + c];
-    const bool clean = track && !a.dlist && a.dirty[crow + c] == 0;
+    const int slot = !track ? 0 : a.dlist ? e : a.dmap[crow + c];   // place in the slice's list
+    const bool clean = slot < 0;
     float* dst = a.cout + ((size_t)s * a.stride + c) * kHeadDim;
     if constexpr (kSplit > 1) __syncthreads();   // every wave has read the count and the flag before one clears them
     if (clean) continue;
@@ -837,6 +1149,14 @@ void centroid_update_kernel(const UpdateArgs<T> a) {
         const float* src = a.cin + ((size_t)s * a.stride + c) * kHeadDim;
         dst[2 * lane] = src[2 * lane];
         dst[2 * lane + 1] = src[2 * lane + 1];
+      }
+      // in the list all the same: its operand goes to its place there
+      if (track && a.frag && part == 0 && lane < 16) {
+        const int at = (lane & 7) * 64 + (lane >> 3) * 32;
+        a.cfrag[((size_t)s * a.n_ctiles + slot / kTileC) * kBf16TileU4 + at + slot % kTileC] =
+            a.frag[((size_t)s * a.n_ctiles + c / kTileC) * kBf16TileU4 + at + c % kTileC];
+        if (lane == 0)
+          a.ccnorm[(size_t)s * a.n_ctiles * kTileC + slot] = a.cnorm[(size_t)s * a.n_ctiles * kTileC + c];
       }
       continue;
     }
@@ -907,7 +1227,10 @@ void centroid_update_kernel(const UpdateArgs<T> a) {
         wd[d / 2] = (uint32_t)f32_to_bf16(-2.f * o0) | ((uint32_t)f32_to_bf16(-2.f * o1) << 16);
       }
       const int step = (d0 & 63) >> 3;
-      a.frag[((size_t)s * a.n_ctiles + t) * kBf16TileU4 + step * 64 + flane] = make_uint4(wd[0], wd[1], wd[2], wd[3]);
+      const uint4 op = make_uint4(wd[0], wd[1], wd[2], wd[3]);
+      a.frag[((size_t)s * a.n_ctiles + t) * kBf16TileU4 + step * 64 + flane] = op;
+      if (track)
+        a.cfrag[((size_t)s * a.n_ctiles + slot / kTileC) * kBf16TileU4 + step * 64 + hh * 32 + slot % kTileC] = op;
     } else {
 #pragma unroll
       for (int d = 0; d < kDims; ++d) nrm += (double)mean[d] * mean[d];
@@ -918,7 +1241,10 @@ void centroid_update_kernel(const UpdateArgs<T> a) {
     }
 #pragma unroll
     for (int o = 1; o < kLpr; o <<= 1) nrm += __shfl_xor(nrm, o, kWave);
-    if (sub == 0) a.cnorm[(size_t)s * a.n_ctiles * kTileC + c] = (float)nrm;
+    if (sub == 0) {
+      a.cnorm[(size_t)s * a.n_ctiles * kTileC + c] = (float)nrm;
+      if (track) a.ccnorm[(size_t)s * a.n_ctiles * kTileC + slot] = (float)nrm;
+    }
   }
 }
 
@@ -1079,6 +1405,12 @@ struct Ws {
   int32_t* dirty;    // per cluster: a key entered or left it in the last assignment
   int32_t* dlist;    // the flagged clusters of a slice, ascending
   int32_t* ndirty;   // their number
+  int32_t* dmap;     // per cluster: its place in dlist, or -1
+  uint4* cfrag;      // bf16: the listed clusters' operands and norms, compacted
+  float* ccnorm;
+  float *best, *sec;     // bf16, per key: D to its cluster, a lower bound on D to every other
+  int32_t *fail, *nfail; // bf16: keys left over by a sweep over the listed clusters, their number
+  int32_t* recorded;     // per slice, by the iteration's parity: it recorded best and sec
   uint4* kswz;   // bf16 key operands in B-operand order (kswz_mode of the assignment)
   size_t bytes;
 };
@@ -1104,6 +1436,15 @@ Ws carve(void* base, int64_t n_slices, int n_tokens, int n_clusters, int dtype) 
   w.dirty = cv.take<int32_t>((size_t)n_slices * n_clusters);
   w.dlist = cv.take<int32_t>((size_t)n_slices * n_clusters);
   w.ndirty = cv.take<int32_t>((size_t)n_slices);
+  w.dmap = cv.take<int32_t>((size_t)n_slices * n_clusters);
+  w.nfail = cv.take<int32_t>((size_t)n_slices);
+  w.recorded = cv.take<int32_t>((size_t)n_slices * 2);
+  const size_t bf = dtype == LOUISKV_BF16 ? 1 : 0;
+  w.cfrag = cv.take<uint4>(bf * n_slices * n_ctiles * tile_u4);
+  w.ccnorm = cv.take<float>(bf * n_slices * n_ctiles * kTileC);
+  w.best = cv.take<float>(bf * n_slices * n_tokens);
+  w.sec = cv.take<float>(bf * n_slices * n_tokens);
+  w.fail = cv.take<int32_t>(bf * n_slices * n_tokens);
   w.kswz = dtype == LOUISKV_BF16
                ? cv.take<uint4>((size_t)n_slices * ceil_div(n_tokens, kBf16KeysPerBlock) * kBf16KeysPerBlock * 16)
                : nullptr;
@@ -1127,6 +1468,19 @@ constexpr int kSplit16Members = 64;
 constexpr int64_t kShareClusters = 65536;
 // Scatter blocks of 4096 keys instead of 1024 once that leaves the chip full.
 constexpr int64_t kWideScatterBlocks = 4096;
+// Assignments record (and sweep the recomputed clusters alone) from this
+// iteration on, where nearly every cluster moves before; a call of fewer
+// (key, centroid) pairs does not: its sweep is short, and the launch for the
+// left-over keys (8-10 us) takes back what the shorter sweeps give (8 slices of
+// 20011 keys, 625 clusters, 1.0e8 pairs: 707 us without, 735 with; 8 of 32768
+// keys, 1024 clusters, 2.7e8 pairs: 946 without, 824 with).
+constexpr int kFirstRecord = 2;
+constexpr double kRecordPairs = 1.5e8;
+// A block of assign_rest_kernel for this many of a slice's keys (32 at a
+// time; about 1% of the keys come to it, more only make the blocks loop), or
+// two blocks a slice from kRestManySlices on, where the slices fill the chip.
+constexpr int kRestKeysPerBlock = 2048;
+constexpr int64_t kRestManySlices = 64;
 
 // clear: the counts, scatter cursors and flags of a new clustering start at zero.
 int launch_prep(const float* reps, int stride, int64_t S, int C, int dtype, const Ws& w, bool clear,
@@ -1144,20 +1498,57 @@ int launch_prep(const float* reps, int stride, int64_t S, int C, int dtype, cons
   return LOUISKV_OK;
 }
 
-// use_bound: assign holds a valid previous assignment; kswz_mode: 0 keys only,
-// 1 keys and store the operand copy, 2 read the copy (bf16 path only).
-// mark_dirty: flag the clusters a key enters or leaves (bf16 path; needs the
-// previous assignment, i.e. use_bound).
+// kswz_mode: 0 keys only, 1 keys and store the operand copy, 2 read the copy
+// (bf16 path only).  mode (bf16): from kAssignMoves on, assign holds the
+// previous iteration's result, whose counts are kept up to date and whose
+// clusters that a key enters or leaves are flagged; with kAssignRecord the
+// update has listed the clusters it recomputed, and where the assignment
+// before recorded the sweep leaves out the others.  it: the iteration.
 int launch_assign(const void* keys, int dtype, int64_t S, int N, int C, const Ws& w, int32_t* assign,
-                  bool with_counts, bool use_bound, int kswz_mode, hipStream_t st, bool mark_dirty = false) {
+                  bool with_counts, int kswz_mode, hipStream_t st, int mode = kAssignPlain, int it = 0) {
   const int n_ctiles = n_ctiles_for(C, dtype);
   if (dtype == LOUISKV_BF16) {
-    const int bps = ceil_div(N, kBf16KeysPerBlock);
-    const bool hist_lds = (size_t)C * 4 <= (size_t)kBf16StageBytes;
-    assign_bf16_kernel<<<(unsigned)(S * bps), kBf16Threads, 0, st>>>(
-        static_cast<const uint16_t*>(keys), w.frag, w.cnorm, assign, with_counts ? w.counts : nullptr, N, C,
-        n_ctiles, bps, hist_lds ? 1 : 0, use_bound ? 1 : 0, w.kswz, kswz_mode,
-        mark_dirty && use_bound ? w.dirty : nullptr);
+    AssignArgs a{};
+    a.keys = static_cast<const uint16_t*>(keys);
+    a.frag = w.frag;
+    a.cnorm = w.cnorm;
+    a.assign = assign;
+    a.counts = with_counts ? w.counts : nullptr;
+    a.n_tokens = N;
+    a.n_clusters = C;
+    a.n_ctiles = n_ctiles;
+    a.blocks_per_slice = ceil_div(N, kBf16KeysPerBlock);
+    a.hist_in_lds = (size_t)C * 4 <= (size_t)kBf16StageBytes ? 1 : 0;
+    a.kswz = w.kswz;
+    a.kswz_mode = kswz_mode;
+    a.dirty = w.dirty;
+    a.best = w.best;
+    a.sec = w.sec;
+    a.ndirty = w.ndirty;
+    a.recorded = w.recorded;
+    a.turn = it & 1;
+    a.dmap = w.dmap;
+    a.dlist = w.dlist;
+    a.cfrag = w.cfrag;
+    a.ccnorm = w.ccnorm;
+    a.fail = w.fail;
+    a.nfail = w.nfail;
+    const unsigned grid = (unsigned)(S * a.blocks_per_slice);
+    if (mode == kAssignRecord)
+      assign_bf16_kernel<kAssignRecord><<<grid, kBf16Threads, 0, st>>>(a);
+    else if (mode == kAssignMoves)
+      assign_bf16_kernel<kAssignMoves><<<grid, kBf16Threads, 0, st>>>(a);
+    else
+      assign_bf16_kernel<kAssignPlain><<<grid, kBf16Threads, 0, st>>>(a);
+    if (mode == kAssignRecord && it > kFirstRecord) {
+      LKV_CHECK_LAUNCH();
+      if (S >= kRestManySlices)
+        assign_rest_kernel<2, 8><<<(unsigned)(2 * S), 512, 0, st>>>(a, 2);
+      else {
+        const int parts = ceil_div(N, kRestKeysPerBlock);
+        assign_rest_kernel<1, 8><<<(unsigned)(S * parts), 512, 0, st>>>(a, parts);
+      }
+    }
   } else {
     const int bps = ceil_div(N, kF32KeysPerBlock);
     size_t lds = (size_t)kF32StageTiles * (kF32TileU4 * 16 + kTileC * 4);
@@ -1176,15 +1567,17 @@ int launch_assign(const void* keys, int dtype, int64_t S, int N, int C, const Ws
 bool scatter_in_lds(int C) { return (size_t)C * 8 <= kMaxHistLds; }
 
 // list: only the flagged clusters' members are placed and the list of those
-// clusters is written (all: every key is placed all the same).
-int launch_scan_scatter(const int32_t* assign, int64_t S, int N, int C, const Ws& w, bool list, bool all,
+// clusters is written (all: every key is placed all the same; first: nothing
+// has been recorded yet).
+int launch_scan_scatter(const int32_t* assign, int64_t S, int N, int C, const Ws& w, bool list, bool all, bool first,
                         hipStream_t st) {
   const int bps = ceil_div(N, kScatterKeys);
   if (scatter_in_lds(C)) {
 #define LKV_SCATTER(PER)                                                                                           \
   scatter_kernel<PER><<<(unsigned)(S * ceil_div(N, 256 * PER)), 256, (size_t)C * 8, st>>>(                          \
       assign, w.counts, w.cursor, w.offsets, w.members, N, C, ceil_div(N, 256 * PER), list ? w.dirty : nullptr,      \
-      w.dlist, w.ndirty, all ? 1 : 0)
+      w.dlist, w.dmap, w.ndirty, w.nfail, w.cfrag, w.ccnorm, n_ctiles_for(C, LOUISKV_BF16), all ? 1 : 0,           \
+      first ? w.recorded : nullptr)
     if (S * bps >= kWideScatterBlocks) {
       LKV_SCATTER(16);
     } else {
@@ -1224,6 +1617,9 @@ int launch_sum_t(const void* keys, int64_t S, int N, int C, int n_ctiles, const 
   a.zero_counts = zero_counts ? 1 : 0;
   a.dirty = list ? w.dirty : nullptr;
   a.ndirty = w.ndirty;
+  a.dmap = w.dmap;
+  a.cfrag = w.cfrag;
+  a.ccnorm = w.ccnorm;
   const int64_t rows = S * C;
   if (rows < kSplit4Clusters) {
     a.blocks_per_slice = a.stride_e = C;
@@ -1300,10 +1696,12 @@ int run_cluster(const void* keys, int dtype, int64_t S, int N, int C, int n_iter
     const bool track = dtype == LOUISKV_BF16 && it > 0;
     const bool list = track && scatter_in_lds(C);
     const bool last = it + 1 == n_iters;
-    if ((st = launch_assign(keys, dtype, S, N, C, w, assign, true, it > 0, it == 0 ? 1 : 2, s, track)))
+    const bool record = list && it >= kFirstRecord && (double)S * N * C >= kRecordPairs;
+    const int mode = !track ? kAssignPlain : record ? kAssignRecord : kAssignMoves;
+    if ((st = launch_assign(keys, dtype, S, N, C, w, assign, true, it == 0 ? 1 : 2, s, mode, it)))
       return st;
     if (iter_events) LKV_CHECK_HIP(hipEventRecord(reinterpret_cast<hipEvent_t>(iter_events[2 * it + 1]), s));
-    if ((st = launch_scan_scatter(assign, S, N, C, w, list, last, s))) return st;
+    if ((st = launch_scan_scatter(assign, S, N, C, w, list, last, it < kFirstRecord, s))) return st;
     if ((st = launch_sum(keys, dtype, S, N, C, w, reps, reps, units_cap, !last, !last && dtype != LOUISKV_BF16, list,
                          s)))
       return st;
@@ -1544,7 +1942,7 @@ extern "C" int louiskv_kmeans_assign(const void* keys, int32_t dtype, int64_t n_
   const Ws w = carve(workspace, n_slices, n_tokens, n_clusters, dtype);
   hipStream_t s = as_stream(stream);
   if ((st = launch_prep(centroids, centroid_stride, n_slices, n_clusters, dtype, w, false, s))) return st;
-  return launch_assign(keys, dtype, n_slices, n_tokens, n_clusters, w, assign, false, false, 0, s);
+  return launch_assign(keys, dtype, n_slices, n_tokens, n_clusters, w, assign, false, 0, s);
 }
 
 extern "C" int louiskv_kmeans_update(const void* keys, int32_t dtype, int64_t n_slices, int32_t n_tokens, int32_t d,
@@ -1574,7 +1972,7 @@ extern "C" int louiskv_kmeans_update(const void* keys, int32_t dtype, int64_t n_
   count_kernel<<<(unsigned)(n_slices * bps), 256, lds_ok ? (size_t)n_clusters * 4 : 0, s>>>(
       assign, w.counts, n_tokens, n_clusters, bps, lds_ok ? 1 : 0);
   LKV_CHECK_LAUNCH();
-  if ((st = launch_scan_scatter(assign, n_slices, n_tokens, n_clusters, w, false, true, s))) return st;
+  if ((st = launch_scan_scatter(assign, n_slices, n_tokens, n_clusters, w, false, true, false, s))) return st;
   if ((st = launch_sum(keys, dtype, n_slices, n_tokens, n_clusters, w, centroids_in, centroids_out,
                        centroid_stride, false, false, false, s)))
     return st;

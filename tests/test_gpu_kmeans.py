@@ -180,6 +180,51 @@ def test_cluster_prefill_matches_oracle_end_to_end():
            bound=max(2, S * P * wl.n_iters // 10000), of="assignment near-ties")
 
 
+@pytest.mark.parametrize("S,N,C,kind", [
+    (8, 20011, 1000, "clusters"),        # ragged tokens and clusters; left-over keys 32 a block
+    (8, 20011, 1000, "overlapping"),     # most clusters move on every iteration
+    (64, 2563, 960, "clusters"),         # many slices: left-over keys 64 a block
+    (8, 20000, 1024, "ties"),            # few distinct keys and values: equal distances
+    (8, 20011, 1000, "nonfinite"),       # NaN and infinite keys among the others
+    (2, 16384, 8192, "clusters"),        # the most clusters the scatter scans in LDS
+])
+def test_prefill_equals_full_sweeps(S, N, C, kind):
+    """A clustering large enough to sweep the recomputed clusters alone equals,
+    bit for bit after every iteration count, the chain of full assignments and
+    updates."""
+    L = _L()
+    assert S * N * C >= 1.5e8
+    keys = _keys(S, N, torch.bfloat16, seed=N + C, centres=C)
+    if kind == "overlapping":
+        keys = (keys.float() + torch.randn(keys.shape, generator=torch.Generator(device=DEV).manual_seed(1),
+                                           device=DEV)).to(torch.bfloat16)
+    if kind == "ties":
+        keys = (keys.float().clamp(-1.4, 1.4).round() * (torch.arange(128, device=DEV) < 12)).to(torch.bfloat16)
+    if kind == "nonfinite":
+        keys[:, 5::997, 3] = float("nan")
+        keys[:, 7::1999, 60] = float("inf")
+        keys[:, 11::2999, 61] = -float("inf")
+    init = _init(S, N, C, seed=C)
+    cents = keys.float()[torch.arange(S, device=DEV)[:, None], init.long()].contiguous()
+    z = torch.empty(S, N, dtype=torch.int32, device=DEV)
+    reps = torch.empty(S, C, 128, device=DEV)
+    ustart = torch.empty(S, C, dtype=torch.int32, device=DEV)
+    usize = torch.empty_like(ustart)
+    assign = torch.empty_like(z)
+    perm = torch.empty_like(z)
+    for it in range(1, 11):
+        L.kmeans_assign(keys, C, cents, z)
+        new = torch.empty_like(cents)
+        L.kmeans_update(keys, C, z, cents, new)
+        cents = new
+        if it in (2, 3, 4, 5, 7, 10):
+            L.cluster_prefill(keys, C, it, init, reps, ustart, usize, assign, perm)
+            torch.cuda.synchronize()
+            assert torch.equal(assign, z), f"assignments after {it} iterations"
+            assert torch.equal(reps.view(torch.int32), cents.view(torch.int32)), f"centroids after {it} iterations"
+            assert torch.equal(perm.long(), z.argsort(dim=1, stable=True))
+
+
 @pytest.mark.parametrize("dtype,S,N,C", [
     (torch.bfloat16, 1, 40000, 3),       # clusters past one 16384-id window, sixteen waves a cluster
     (torch.float32, 2, 2048, 32),        # 64 members on average: sixteen waves
