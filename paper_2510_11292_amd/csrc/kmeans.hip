@@ -456,7 +456,9 @@ constexpr int kAssignPlain = 0, kAssignMoves = 1, kAssignRecord = 2;
 // and with them all outputs, are the same bit for bit.  On the benchmark's
 // keys (32768 around 1024 centres) 93, 74, 51, 40, 27, 19, 15 and 10% of the
 // clusters are recomputed before iterations 3 to 10, and 1.4% of the keys or
-// fewer are left over.
+// fewer are left over: the ten assignments of 256 such slices take 2.13, 1.83,
+// 1.9, 1.6, 1.2, .96, .78, .68, .62 and .59 ms where ten full sweeps took 18.3,
+// those of 8 slices 473 us where they took 685 (MI355X).
 template <int kMode>
 __global__ __launch_bounds__(kBf16Threads, 8 / kBf16Waves)
 void assign_bf16_kernel(const AssignArgs a) {
@@ -1046,7 +1048,7 @@ void scatter_kernel(const int32_t* __restrict__ assign, const int32_t* __restric
       }
       // the compacted operand's last stage is padded with rows that never win
       constexpr int kStageC = kBf16StageTiles * kTileC;
-      const int pad = (all + kStageC - 1) / kStageC * kStageC - all;
+      const int pad = cfrag ? (all + kStageC - 1) / kStageC * kStageC - all : 0;
       for (int i = tid; i < pad * 16; i += 256) {
         const int r = all + i / 16, q = i % 16;   // 16-byte piece q of row r
         cfrag[((size_t)slice * n_ctiles + r / kTileC) * kBf16TileU4 + (q & 7) * 64 + (q >> 3) * 32 + r % kTileC] =
@@ -1108,7 +1110,7 @@ struct UpdateArgs {
   float* cnorm;
   int n_ctiles, zero_counts;
   int32_t *dirty, *dlist, *dmap, *ndirty;
-  uint4* cfrag;       // the recomputed clusters' operands in list order, with frag and dirty
+  uint4* cfrag;       // the recomputed clusters' operands in list order, or NULL
   float* ccnorm;
 };
 
@@ -1151,7 +1153,7 @@ void centroid_update_kernel(const UpdateArgs<T> a) {
         dst[2 * lane + 1] = src[2 * lane + 1];
       }
       // in the list all the same: its operand goes to its place there
-      if (track && a.frag && part == 0 && lane < 16) {
+      if (a.cfrag && a.frag && part == 0 && lane < 16) {
         const int at = (lane & 7) * 64 + (lane >> 3) * 32;
         a.cfrag[((size_t)s * a.n_ctiles + slot / kTileC) * kBf16TileU4 + at + slot % kTileC] =
             a.frag[((size_t)s * a.n_ctiles + c / kTileC) * kBf16TileU4 + at + c % kTileC];
@@ -1229,7 +1231,7 @@ void centroid_update_kernel(const UpdateArgs<T> a) {
       const int step = (d0 & 63) >> 3;
       const uint4 op = make_uint4(wd[0], wd[1], wd[2], wd[3]);
       a.frag[((size_t)s * a.n_ctiles + t) * kBf16TileU4 + step * 64 + flane] = op;
-      if (track)
+      if (a.cfrag)
         a.cfrag[((size_t)s * a.n_ctiles + slot / kTileC) * kBf16TileU4 + step * 64 + hh * 32 + slot % kTileC] = op;
     } else {
 #pragma unroll
@@ -1243,7 +1245,7 @@ void centroid_update_kernel(const UpdateArgs<T> a) {
     for (int o = 1; o < kLpr; o <<= 1) nrm += __shfl_xor(nrm, o, kWave);
     if (sub == 0) {
       a.cnorm[(size_t)s * a.n_ctiles * kTileC + c] = (float)nrm;
-      if (track) a.ccnorm[(size_t)s * a.n_ctiles * kTileC + slot] = (float)nrm;
+      if (a.cfrag) a.ccnorm[(size_t)s * a.n_ctiles * kTileC + slot] = (float)nrm;
     }
   }
 }
@@ -1329,20 +1331,272 @@ void finalize_kernel(const int32_t* __restrict__ members, const int32_t* __restr
   }
 }
 
-// pool[s][r] = src[s][perm[s][r]] for r < n_tokens; 16 lanes per row.
+// ---------------------------------------------------------------------------
+// Clustering of a short prompt in one launch: a block per slice runs the
+// initial centroids, every Lloyd iteration and the CSR, perm and unit outputs,
+// its keys in registers as matrix B operands (wave w holds the 32-key tiles
+// w, w + 16, ..) and the centroid operands, the assignment, counts and member
+// lists in LDS.  The launches above take 3-8 us each whatever their size, four
+// an iteration; here an iteration is a chain of barriers and one gather of
+// the member rows of the clusters that keys entered or left, from L2.  Same
+// matrix-core values, order of ties and means as those launches, so the same
+// outputs.  8 slices of 500 keys in 16 clusters: 175 -> 67 us, 256 of 1024 keys
+// in 32: 445 -> 181 us (sixteen waves; eight took 74 and 202).  It serves what
+// fits one block's registers (1024 keys) and a few operand tiles; a block per
+// slice is also fastest where slices are few, as the launches it replaces are
+// latency alone there.
+struct SmallArgs {
+  const uint16_t* keys;
+  const int32_t* init_idx;
+  float* reps;
+  int32_t *unit_start, *unit_size, *assign, *perm;
+  int n_tokens, n_clusters, units_cap, n_iters;
+};
+
+constexpr int kSmallWaves = 16;
+constexpr int kSmallKeys = 32 * 2 * kSmallWaves;   // 1024: two key tiles a wave
+constexpr int kSmallTiles = 4;                     // centroid tiles (32 KiB of operands)
+constexpr int kSmallClusters = kSmallTiles * kTileC;
+
+// Lane l < 16 holds dims 8 l .. 8 l + 7 of a centroid: its operand -2 op(c)
+// into row `c` of the A-fragment tiles and ||op(c)||^2 (every lane of the 16).
+__device__ __forceinline__ void small_operand(const float (&v)[8], int c, int l, uint4* s_frag, float* s_cn) {
+  uint32_t wd[4];
+  double nrm = 0.0;
+#pragma unroll
+  for (int d = 0; d < 8; d += 2) {
+    const float o0 = bf16_to_f32(f32_to_bf16(v[d])), o1 = bf16_to_f32(f32_to_bf16(v[d + 1]));
+    nrm += (double)o0 * o0 + (double)o1 * o1;
+    wd[d / 2] = (uint32_t)f32_to_bf16(-2.f * o0) | ((uint32_t)f32_to_bf16(-2.f * o1) << 16);
+  }
+  s_frag[(c / kTileC) * kBf16TileU4 + (l & 7) * 64 + (l >> 3) * 32 + c % kTileC] = make_uint4(wd[0], wd[1], wd[2], wd[3]);
+#pragma unroll
+  for (int o = 1; o < 16; o <<= 1) nrm += __shfl_xor(nrm, o, kWave);
+  if (l == 0) s_cn[c] = (float)nrm;
+}
+
+template <int kKT>
+__global__ __launch_bounds__(64 * kSmallWaves)
+void lloyd_small_kernel(const SmallArgs a) {
+  __shared__ uint4 s_frag[kSmallTiles * kBf16TileU4];
+  __shared__ float s_cn[kSmallClusters];
+  __shared__ int s_assign[kSmallKeys], s_mem[kSmallKeys];
+  __shared__ int s_cnt[kSmallClusters], s_off[kSmallClusters], s_cur[kSmallClusters], s_dirty[kSmallClusters];
+  __shared__ uint32_t s_bits[kSmallWaves][kSmallKeys / 32];
+  constexpr int kRows = kKT == 1 ? 8 : 4;   // row loads in flight a lane
+  const int64_t s = blockIdx.x;
+  const int N = a.n_tokens, C = a.n_clusters;
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, h = lane >> 5,
+            j = lane & 31, sub = lane & 15, grp = lane >> 4;
+  const int n_tiles = (C + kTileC - 1) / kTileC;
+  const uint16_t* kslice = a.keys + (size_t)s * N * kHeadDim;
+  float* reps = a.reps + (size_t)s * a.units_cap * kHeadDim;
+
+  // the keys, and the initial centroids (four a wave at a time)
+  bf16x8_t b[kKT][kBf16Steps];
+#pragma unroll
+  for (int kt = 0; kt < kKT; ++kt) {
+    const int key = 32 * (w + kt * kSmallWaves) + j;
+    const uint4* src = reinterpret_cast<const uint4*>(kslice + (size_t)key * kHeadDim + 64 * h);
+#pragma unroll
+    for (int t = 0; t < kBf16Steps; ++t)
+      b[kt][t] = __builtin_bit_cast(bf16x8_t, key < N ? src[t] : make_uint4(0, 0, 0, 0));
+  }
+  for (int c0 = 4 * w; c0 < n_tiles * kTileC; c0 += 4 * kSmallWaves) {
+    const int c = c0 + grp;
+    float v[8] = {};
+    if (c < C) {
+      const int t = min(max(a.init_idx[s * C + c], 0), N - 1);
+      const uint4 x = reinterpret_cast<const uint4*>(kslice + (size_t)t * kHeadDim)[sub];
+      const uint16_t* e = reinterpret_cast<const uint16_t*>(&x);
+#pragma unroll
+      for (int d = 0; d < 8; ++d) v[d] = bf16_to_f32(e[d]);
+      float4* dst = reinterpret_cast<float4*>(reps + (size_t)c * kHeadDim + 8 * sub);
+      dst[0] = make_float4(v[0], v[1], v[2], v[3]);
+      dst[1] = make_float4(v[4], v[5], v[6], v[7]);
+    }
+    small_operand(v, c, sub, s_frag, s_cn);
+    if (c >= C && sub == 0) s_cn[c] = __builtin_inff();   // padding rows never win
+  }
+  for (int i = tid; i < kSmallKeys; i += 64 * kSmallWaves) s_assign[i] = -1;
+  if (tid < kSmallClusters) {
+    s_cnt[tid] = 0;
+    s_dirty[tid] = 1;
+  }
+  __syncthreads();
+
+  for (int it = 0; it < a.n_iters; ++it) {
+    const bool last = it + 1 == a.n_iters;
+    float best[kKT];
+    int bidx[kKT];
+#pragma unroll
+    for (int kt = 0; kt < kKT; ++kt) {
+      best[kt] = __builtin_inff();
+      bidx[kt] = -1;
+    }
+    for (int t = 0; t < n_tiles; ++t) {
+      floatx16 cn;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const float4 x = *reinterpret_cast<const float4*>(&s_cn[t * kTileC + 8 * g + 4 * h]);
+        cn[4 * g + 0] = x.x; cn[4 * g + 1] = x.y; cn[4 * g + 2] = x.z; cn[4 * g + 3] = x.w;
+      }
+      floatx16 acc[kKT];
+#pragma unroll
+      for (int q = 0; q < kBf16Steps; ++q) {
+        const bf16x8_t x = __builtin_bit_cast(bf16x8_t, s_frag[t * kBf16TileU4 + q * 64 + lane]);
+#pragma unroll
+        for (int kt = 0; kt < kKT; ++kt)
+          acc[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, b[kt][q], q == 0 ? cn : acc[kt], 0, 0, 0);
+      }
+#pragma unroll
+      for (int kt = 0; kt < kKT; ++kt) {
+        const float m = tile_min(acc[kt]);
+        int id = t * kTileC + 4 * h + tile_find(acc[kt], m);
+        int sel = m < best[kt] ? 1 : 0;
+        asm volatile("" : "+v"(sel), "+v"(id));
+        bidx[kt] = sel ? id : bidx[kt];
+        best[kt] = sel ? m : best[kt];
+      }
+    }
+#pragma unroll
+    for (int kt = 0; kt < kKT; ++kt) {
+      const float ob = __shfl_xor(best[kt], 32, kWave);
+      const int oi = __shfl_xor(bidx[kt], 32, kWave);
+      if (bidx[kt] < 0 || (oi >= 0 && (ob < best[kt] || (ob == best[kt] && oi < bidx[kt])))) bidx[kt] = oi;
+      if (bidx[kt] < 0) bidx[kt] = 0;   // only reachable with non-finite inputs
+      const int key = 32 * (w + kt * kSmallWaves) + j;
+      if (h == 0 && key < N) {
+        const int old = s_assign[key], id = bidx[kt];
+        if (id != old) {
+          s_assign[key] = id;
+          s_dirty[id] = 1;
+          atomicAdd(&s_cnt[id], 1);
+          if (old >= 0) {
+            s_dirty[old] = 1;
+            atomicSub(&s_cnt[old], 1);
+          }
+        }
+      }
+    }
+    __syncthreads();
+    if (w == 0) {   // offsets: lane l scans clusters 2l, 2l + 1
+      const int c0 = 2 * lane;
+      const int n0 = c0 < C ? s_cnt[c0] : 0, n1 = c0 + 1 < C ? s_cnt[c0 + 1] : 0;
+      int x = n0 + n1;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(x, o, kWave);
+        if (lane >= o) x += y;
+      }
+      s_off[c0] = s_cur[c0] = x - n0 - n1;
+      s_off[c0 + 1] = s_cur[c0 + 1] = x - n1;
+    }
+    __syncthreads();
+    for (int i = tid; i < N; i += 64 * kSmallWaves) {
+      const int z = s_assign[i];
+      if (last || s_dirty[z]) s_mem[atomicAdd(&s_cur[z], 1)] = i;
+    }
+    __syncthreads();
+    // means of the flagged clusters, one wave each, 4 kRows rows in flight
+    for (int c = w; c < C; c += kSmallWaves) {
+      const int n = s_cnt[c];
+      const bool flagged = s_dirty[c] != 0;
+      if (!flagged || n == 0) {
+        if (lane == 0) s_dirty[c] = 0;
+        continue;
+      }
+      const int off = s_off[c];
+      double acc[8];
+#pragma unroll
+      for (int d = 0; d < 8; ++d) acc[d] = 0.0;
+      for (int m0 = 0; m0 < n; m0 += 4 * kRows) {
+        uint4 x[kRows];
+#pragma unroll
+        for (int u = 0; u < kRows; ++u) {
+          const int r = m0 + 4 * u + grp;
+          x[u] = r < n ? reinterpret_cast<const uint4*>(kslice + (size_t)s_mem[off + r] * kHeadDim)[sub]
+                       : make_uint4(0, 0, 0, 0);
+        }
+#pragma unroll
+        for (int u = 0; u < kRows; ++u) {
+          const uint16_t* e = reinterpret_cast<const uint16_t*>(&x[u]);
+#pragma unroll
+          for (int d = 0; d < 8; ++d) acc[d] += (double)bf16_to_f32(e[d]);
+        }
+      }
+#pragma unroll
+      for (int o = 16; o < kWave; o <<= 1)
+#pragma unroll
+        for (int d = 0; d < 8; ++d) acc[d] += __shfl_xor(acc[d], o, kWave);
+      float mean[8];
+#pragma unroll
+      for (int d = 0; d < 8; ++d) mean[d] = (float)(acc[d] / (double)n);
+      if (grp == 0) {
+        float4* dst = reinterpret_cast<float4*>(reps + (size_t)c * kHeadDim + 8 * sub);
+        dst[0] = make_float4(mean[0], mean[1], mean[2], mean[3]);
+        dst[1] = make_float4(mean[4], mean[5], mean[6], mean[7]);
+        small_operand(mean, c, sub, s_frag, s_cn);
+      }
+      if (lane == 0) s_dirty[c] = 0;
+    }
+    __syncthreads();
+  }
+
+  // outputs: members of each cluster in ascending order through a bitmap
+  for (int i = tid; i < N; i += 64 * kSmallWaves) a.assign[(size_t)s * N + i] = s_assign[i];
+  uint32_t* bits = s_bits[w];
+  for (int c = w; c < C; c += kSmallWaves) {
+    const int n = s_cnt[c], off = s_off[c];
+    if (lane == 0) {
+      a.unit_start[s * a.units_cap + c] = off;
+      a.unit_size[s * a.units_cap + c] = n;
+    }
+    if (lane < kSmallKeys / 32) bits[lane] = 0u;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    for (int i = lane; i < n; i += kWave) {
+      const int id = s_mem[off + i];
+      atomicOr(&bits[id >> 5], 1u << (id & 31));
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    uint32_t x = lane < kSmallKeys / 32 ? bits[lane] : 0u;
+    int incl = __popc(x);
+    const int mine = incl;
+#pragma unroll
+    for (int o = 1; o < 32; o <<= 1) {
+      const int y = __shfl_up(incl, o, kWave);
+      if (lane >= o) incl += y;
+    }
+    int at = off + incl - mine;
+    while (x) {
+      a.perm[(size_t)s * N + at++] = 32 * lane + __builtin_ctz(x);
+      x &= x - 1;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  }
+}
+
+// pool[s][r] = src[s][perm[s][r]] for r < n_tokens; 16 lanes per row.  The
+// first `blocks` blocks write the pool of src, the others (values given) that
+// of src2: one launch for keys and values.
 template <class T>
-__global__ void pack_pool_kernel(const T* __restrict__ src, const int32_t* __restrict__ perm,
-                                 T* __restrict__ pool, int64_t pool_rows, int n_tokens, int64_t n_rows) {
+__global__ void pack_pool_kernel(const T* __restrict__ src, const T* __restrict__ src2,
+                                 const int32_t* __restrict__ perm, T* __restrict__ pool, T* __restrict__ pool2,
+                                 int64_t pool_rows, int n_tokens, int64_t n_rows, int blocks) {
   // 16 rows per block of 256 per round; a grid smaller than n_rows / 16
   // blocks strides over the rest (a pack that shares the chip with clustering)
   const int sub = threadIdx.x & 15;
-  for (int64_t g = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4); g < n_rows; g += (int64_t)gridDim.x * 16) {
+  const bool second = (int)blockIdx.x >= blocks;
+  const int blk = second ? blockIdx.x - blocks : blockIdx.x;
+  const T* from = second ? src2 : src;
+  T* to = second ? pool2 : pool;
+  for (int64_t g = (int64_t)blk * 16 + (threadIdx.x >> 4); g < n_rows; g += (int64_t)blocks * 16) {
     const int64_t s = g / n_tokens;
     const int r = (int)(g - s * n_tokens);
     const int tok = min(max(perm[s * n_tokens + r], 0), n_tokens - 1);   // perm may come from the caller
     constexpr int kU4 = kHeadDim * sizeof(T) / 16;
-    const uint4* a = reinterpret_cast<const uint4*>(src + ((size_t)s * n_tokens + tok) * kHeadDim);
-    uint4* b = reinterpret_cast<uint4*>(pool + ((size_t)s * pool_rows + r) * kHeadDim);
+    const uint4* a = reinterpret_cast<const uint4*>(from + ((size_t)s * n_tokens + tok) * kHeadDim);
+    uint4* b = reinterpret_cast<uint4*>(to + ((size_t)s * pool_rows + r) * kHeadDim);
 #pragma unroll
     for (int q = sub; q < kU4; q += 16) b[q] = a[q];
   }
@@ -1406,10 +1660,11 @@ struct Ws {
   int32_t* dlist;    // the flagged clusters of a slice, ascending
   int32_t* ndirty;   // their number
   int32_t* dmap;     // per cluster: its place in dlist, or -1
-  uint4* cfrag;      // bf16: the listed clusters' operands and norms, compacted
+  // calls that record (see records()):
+  uint4* cfrag;      // the listed clusters' operands and norms, compacted
   float* ccnorm;
-  float *best, *sec;     // bf16, per key: D to its cluster, a lower bound on D to every other
-  int32_t *fail, *nfail; // bf16: keys left over by a sweep over the listed clusters, their number
+  float *best, *sec;     // per key: D to its cluster, a lower bound on D to every other
+  int32_t *fail, *nfail; // keys left over by a sweep over the listed clusters, their number
   int32_t* recorded;     // per slice, by the iteration's parity: it recorded best and sec
   uint4* kswz;   // bf16 key operands in B-operand order (kswz_mode of the assignment)
   size_t bytes;
@@ -1420,6 +1675,24 @@ struct Ws {
 int n_ctiles_for(int n_clusters, int dtype) {
   const int t = ceil_div(n_clusters, kTileC);
   return dtype == LOUISKV_BF16 ? ceil_div(t, kBf16StageTiles) * kBf16StageTiles : t;
+}
+
+constexpr size_t kMaxHistLds = 64 * 1024;
+
+// Whether the scatter scans the counts in LDS (two ints a cluster); above,
+// the scan is a launch of its own and every cluster is updated every time.
+bool scatter_in_lds(int C) { return (size_t)C * 8 <= kMaxHistLds; }
+
+// Assignments record (and sweep the recomputed clusters alone) from this
+// iteration on, where nearly every cluster moves before; a call of fewer
+// (key, centroid) pairs does not: its sweep is short, and the launch for the
+// left-over keys (8-10 us) takes back what the shorter sweeps give (8 slices of
+// 20011 keys, 625 clusters, 1.0e8 pairs: 707 us without, 735 with; 8 of 32768
+// keys, 1024 clusters, 2.7e8 pairs: 946 without, 824 with).
+constexpr int kFirstRecord = 2;
+constexpr double kRecordPairs = 1.5e8;
+bool records(int64_t S, int N, int C, int dtype) {
+  return dtype == LOUISKV_BF16 && scatter_in_lds(C) && (double)S * N * C >= kRecordPairs;
 }
 
 Ws carve(void* base, int64_t n_slices, int n_tokens, int n_clusters, int dtype) {
@@ -1439,7 +1712,7 @@ Ws carve(void* base, int64_t n_slices, int n_tokens, int n_clusters, int dtype) 
   w.dmap = cv.take<int32_t>((size_t)n_slices * n_clusters);
   w.nfail = cv.take<int32_t>((size_t)n_slices);
   w.recorded = cv.take<int32_t>((size_t)n_slices * 2);
-  const size_t bf = dtype == LOUISKV_BF16 ? 1 : 0;
+  const size_t bf = records(n_slices, n_tokens, n_clusters, dtype) ? 1 : 0;
   w.cfrag = cv.take<uint4>(bf * n_slices * n_ctiles * tile_u4);
   w.ccnorm = cv.take<float>(bf * n_slices * n_ctiles * kTileC);
   w.best = cv.take<float>(bf * n_slices * n_tokens);
@@ -1452,7 +1725,6 @@ Ws carve(void* base, int64_t n_slices, int n_tokens, int n_clusters, int dtype) 
   return w;
 }
 
-constexpr size_t kMaxHistLds = 64 * 1024;
 // Waves per cluster of the update, by the clusters of the whole call: one
 // each fills the chip from kSplit4Clusters on; below that the four waves of a
 // block share a cluster's members.  Below kSplit16Clusters sixteen do where a
@@ -1468,14 +1740,6 @@ constexpr int kSplit16Members = 64;
 constexpr int64_t kShareClusters = 65536;
 // Scatter blocks of 4096 keys instead of 1024 once that leaves the chip full.
 constexpr int64_t kWideScatterBlocks = 4096;
-// Assignments record (and sweep the recomputed clusters alone) from this
-// iteration on, where nearly every cluster moves before; a call of fewer
-// (key, centroid) pairs does not: its sweep is short, and the launch for the
-// left-over keys (8-10 us) takes back what the shorter sweeps give (8 slices of
-// 20011 keys, 625 clusters, 1.0e8 pairs: 707 us without, 735 with; 8 of 32768
-// keys, 1024 clusters, 2.7e8 pairs: 946 without, 824 with).
-constexpr int kFirstRecord = 2;
-constexpr double kRecordPairs = 1.5e8;
 // A block of assign_rest_kernel for this many of a slice's keys (32 at a
 // time; about 1% of the keys come to it, more only make the blocks loop), or
 // two blocks a slice from kRestManySlices on, where the slices fill the chip.
@@ -1562,21 +1826,18 @@ int launch_assign(const void* keys, int dtype, int64_t S, int N, int C, const Ws
   return LOUISKV_OK;
 }
 
-// Whether the scatter scans the counts in LDS (two ints a cluster); above,
-// the scan is a launch of its own and every cluster is updated every time.
-bool scatter_in_lds(int C) { return (size_t)C * 8 <= kMaxHistLds; }
-
 // list: only the flagged clusters' members are placed and the list of those
 // clusters is written (all: every key is placed all the same; first: nothing
 // has been recorded yet).
 int launch_scan_scatter(const int32_t* assign, int64_t S, int N, int C, const Ws& w, bool list, bool all, bool first,
                         hipStream_t st) {
   const int bps = ceil_div(N, kScatterKeys);
+  const bool rec = list && records(S, N, C, LOUISKV_BF16);
   if (scatter_in_lds(C)) {
 #define LKV_SCATTER(PER)                                                                                           \
   scatter_kernel<PER><<<(unsigned)(S * ceil_div(N, 256 * PER)), 256, (size_t)C * 8, st>>>(                          \
       assign, w.counts, w.cursor, w.offsets, w.members, N, C, ceil_div(N, 256 * PER), list ? w.dirty : nullptr,      \
-      w.dlist, w.dmap, w.ndirty, w.nfail, w.cfrag, w.ccnorm, n_ctiles_for(C, LOUISKV_BF16), all ? 1 : 0,           \
+      w.dlist, w.dmap, w.ndirty, w.nfail, rec ? w.cfrag : nullptr, w.ccnorm, n_ctiles_for(C, LOUISKV_BF16), all ? 1 : 0,           \
       first ? w.recorded : nullptr)
     if (S * bps >= kWideScatterBlocks) {
       LKV_SCATTER(16);
@@ -1618,7 +1879,7 @@ int launch_sum_t(const void* keys, int64_t S, int N, int C, int n_ctiles, const 
   a.dirty = list ? w.dirty : nullptr;
   a.ndirty = w.ndirty;
   a.dmap = w.dmap;
-  a.cfrag = w.cfrag;
+  a.cfrag = list && records(S, N, C, LOUISKV_BF16) ? w.cfrag : nullptr;
   a.ccnorm = w.ccnorm;
   const int64_t rows = S * C;
   if (rows < kSplit4Clusters) {
@@ -1646,24 +1907,31 @@ int launch_sum(const void* keys, int dtype, int64_t S, int N, int C, const Ws& w
              : launch_sum_t<float>(keys, S, N, C, n_ctiles, w, cin, cout, stride, prep_next, zero_counts, list, st);
 }
 
+constexpr int64_t kMaxPackGrid = 1 << 20;   // blocks a pool; they stride over more rows
+
 // Prompt K/V rows in perm order into the pools (each cluster one contiguous run).
 int launch_pack(const void* keys, const void* values, int dtype, int64_t S, int N, const int32_t* perm, void* k_pool,
                 void* v_pool, int64_t pool_rows, hipStream_t s, int max_grid = 0) {
   const int64_t prow = S * N;
-  int pgrid = (int)((prow + 15) / 16);
+  int pgrid = (int)std::min<int64_t>((prow + 15) / 16, kMaxPackGrid);
   if (max_grid > 0) pgrid = std::min(pgrid, max_grid);
-  for (int which = 0; which < 2; ++which) {
-    void* pool = which == 0 ? k_pool : v_pool;
-    const void* src = which == 0 ? keys : values;
-    if (!pool) continue;
-    if (dtype == LOUISKV_BF16)
-      pack_pool_kernel<uint16_t><<<pgrid, 256, 0, s>>>(static_cast<const uint16_t*>(src), perm,
-                                                        static_cast<uint16_t*>(pool), pool_rows, N, prow);
-    else
-      pack_pool_kernel<float><<<pgrid, 256, 0, s>>>(static_cast<const float*>(src), perm, static_cast<float*>(pool),
-                                                     pool_rows, N, prow);
-    LKV_CHECK_LAUNCH();
+  if (!k_pool) {   // values alone
+    keys = values;
+    k_pool = v_pool;
+    v_pool = nullptr;
   }
+  if (!k_pool) return LOUISKV_OK;
+  const unsigned grid = (unsigned)pgrid * (v_pool ? 2u : 1u);
+  if (dtype == LOUISKV_BF16)
+    pack_pool_kernel<uint16_t><<<grid, 256, 0, s>>>(static_cast<const uint16_t*>(keys),
+                                                    static_cast<const uint16_t*>(values), perm,
+                                                    static_cast<uint16_t*>(k_pool), static_cast<uint16_t*>(v_pool),
+                                                    pool_rows, N, prow, pgrid);
+  else
+    pack_pool_kernel<float><<<grid, 256, 0, s>>>(static_cast<const float*>(keys), static_cast<const float*>(values),
+                                                 perm, static_cast<float*>(k_pool), static_cast<float*>(v_pool),
+                                                 pool_rows, N, prow, pgrid);
+  LKV_CHECK_LAUNCH();
   return LOUISKV_OK;
 }
 
@@ -1674,6 +1942,16 @@ int run_cluster(const void* keys, int dtype, int64_t S, int N, int C, int n_iter
                 float* reps, int units_cap, int32_t* unit_start, int32_t* unit_size, int32_t* assign, int32_t* perm,
                 void* const* iter_events, const Ws& w, hipStream_t s) {
   int st;
+  if (dtype == LOUISKV_BF16 && N <= kSmallKeys && C <= kSmallClusters && !iter_events) {
+    SmallArgs a{static_cast<const uint16_t*>(keys), init_idx, reps, unit_start, unit_size, assign, perm, N, C,
+                units_cap, n_iters};
+    if (N <= kSmallKeys / 2)
+      lloyd_small_kernel<1><<<(unsigned)S, 64 * kSmallWaves, 0, s>>>(a);
+    else
+      lloyd_small_kernel<2><<<(unsigned)S, 64 * kSmallWaves, 0, s>>>(a);
+    LKV_CHECK_LAUNCH();
+    return LOUISKV_OK;
+  }
   {
     const int64_t rows = S * C;
     const int grid = (int)((rows + 3) / 4);
@@ -1696,7 +1974,7 @@ int run_cluster(const void* keys, int dtype, int64_t S, int N, int C, int n_iter
     const bool track = dtype == LOUISKV_BF16 && it > 0;
     const bool list = track && scatter_in_lds(C);
     const bool last = it + 1 == n_iters;
-    const bool record = list && it >= kFirstRecord && (double)S * N * C >= kRecordPairs;
+    const bool record = it >= kFirstRecord && records(S, N, C, dtype);
     const int mode = !track ? kAssignPlain : record ? kAssignRecord : kAssignMoves;
     if ((st = launch_assign(keys, dtype, S, N, C, w, assign, true, it == 0 ? 1 : 2, s, mode, it)))
       return st;

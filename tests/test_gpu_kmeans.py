@@ -187,13 +187,20 @@ def test_cluster_prefill_matches_oracle_end_to_end():
     (8, 20000, 1024, "ties"),            # few distinct keys and values: equal distances
     (8, 20011, 1000, "nonfinite"),       # NaN and infinite keys among the others
     (2, 16384, 8192, "clusters"),        # the most clusters the scatter scans in LDS
+    (3, 1024, 128, "clusters"),          # the largest clustering that one block a slice runs
+    (2, 1025, 128, "clusters"),          # one key, one cluster more: a launch per stage
+    (2, 1024, 129, "clusters"),
+    (5, 513, 31, "overlapping"),         # one block a slice: two key tiles a wave, ragged
+    (4, 512, 32, "ties"),
+    (3, 1000, 64, "nonfinite"),
+    (2, 33, 33, "clusters"),
+    (2, 1, 1, "clusters"),
 ])
 def test_prefill_equals_full_sweeps(S, N, C, kind):
-    """A clustering large enough to sweep the recomputed clusters alone equals,
-    bit for bit after every iteration count, the chain of full assignments and
-    updates."""
+    """A clustering large enough to sweep the recomputed clusters alone, or
+    small enough to run in one launch, equals, bit for bit after every
+    iteration count, the chain of full assignments and updates."""
     L = _L()
-    assert S * N * C >= 1.5e8
     keys = _keys(S, N, torch.bfloat16, seed=N + C, centres=C)
     if kind == "overlapping":
         keys = (keys.float() + torch.randn(keys.shape, generator=torch.Generator(device=DEV).manual_seed(1),
@@ -217,7 +224,7 @@ def test_prefill_equals_full_sweeps(S, N, C, kind):
         new = torch.empty_like(cents)
         L.kmeans_update(keys, C, z, cents, new)
         cents = new
-        if it in (2, 3, 4, 5, 7, 10):
+        if it in (1, 2, 3, 4, 5, 7, 10):
             L.cluster_prefill(keys, C, it, init, reps, ustart, usize, assign, perm)
             torch.cuda.synchronize()
             assert torch.equal(assign, z), f"assignments after {it} iterations"
