@@ -1,8 +1,8 @@
-"""ctypes binding of libLouisKV.
+"""Python binding of libLouisKV.
 
-Each function marshals torch tensors into the C ABI of include/louiskv.h
-(pointers, sizes, the current HIP stream) and raises LouisKVError on a
-non-zero status.  All arithmetic happens in the library's HIP kernels; if the
+Each function passes torch tensors to the C ABI of include/louiskv.h (pointers,
+sizes, the current HIP stream; marshalled natively, csrc/binding.cpp) and
+raises LouisKVError on a non-zero status.  All arithmetic happens in the library's HIP kernels; if the
 library is not built this module fails loudly instead of computing anything.
 """
 from __future__ import annotations
@@ -162,18 +162,28 @@ def load_library(path: Optional[str] = None) -> ctypes.CDLL:
     return lib
 
 
+_binding = None
+
+
+def _native():
+    """The native marshalling of the ABI calls (csrc/binding.cpp)."""
+    global _binding
+    if _binding is None:
+        if not os.path.exists(LIB_PATH):
+            load_library()   # raises
+        try:
+            from . import _binding as m
+        except ImportError as e:
+            raise RuntimeError(f"the binding of libLouisKV is not built ({e}); "
+                               f"run `python -m paper_2510_11292_amd.build`") from e
+        _binding = m
+    return _binding
+
+
 def _check(status: int) -> None:
     if status != 0:
         lib = load_library()
         raise LouisKVError(status, lib.louiskv_last_error().decode())
-
-
-def _ptr(t: Optional[torch.Tensor]):
-    if t is None:
-        return None
-    if not t.is_contiguous():
-        raise ValueError("libLouisKV needs contiguous tensors")
-    return ctypes.c_void_p(t.data_ptr())
 
 
 def _dtype_code(t: torch.Tensor) -> int:
@@ -184,15 +194,12 @@ def _dtype_code(t: torch.Tensor) -> int:
     raise TypeError(f"unsupported dtype {t.dtype}")
 
 
-def _stream(stream=None):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
-
-
-def _ws(nbytes: int, device, workspace: Optional[torch.Tensor]):
+def _ws(workspace: Optional[torch.Tensor], device, size, *args):
+    """The workspace and its bytes; one of size(*args) bytes where none is given."""
     if workspace is None:
-        workspace = torch.empty(max(int(nbytes), 1), dtype=torch.uint8, device=device)
-    return workspace, workspace.numel() * workspace.element_size()
+        workspace = torch.empty(max(int(size(*args)), 1), dtype=torch.uint8, device=device)
+        return workspace, workspace.numel()
+    return workspace, workspace.nbytes
 
 
 def abi_version() -> int:
@@ -201,13 +208,14 @@ def abi_version() -> int:
 
 def window_info(step: int, window: int, seg_len: int):
     """(evicted_segment or -1, n_evicted, n_local, local_start) after storing token `step`."""
-    out = [ctypes.c_int32() for _ in range(4)]
-    _check(load_library().louiskv_window_info(step, window, seg_len, *[ctypes.byref(o) for o in out]))
-    return tuple(o.value for o in out)
+    out = _native().window_info(step, window, seg_len)
+    if type(out) is int:
+        _check(out)
+    return out
 
 
 def cluster_prefill_workspace_size(n_slices, n_tokens, n_clusters, dtype_code, d=128) -> int:
-    return load_library().louiskv_cluster_prefill_workspace_size(n_slices, n_tokens, d, n_clusters, dtype_code)
+    return _native().cluster_prefill_workspace_size(n_slices, n_tokens, d, n_clusters, dtype_code)
 
 
 def cluster_prefill(keys, n_clusters: int, n_iters: int, init_idx, reps, unit_start, unit_size, assign, perm,
@@ -215,22 +223,22 @@ def cluster_prefill(keys, n_clusters: int, n_iters: int, init_idx, reps, unit_st
                     iter_events: Optional[Sequence] = None, workspace=None, stream=None):
     s, n, d = keys.shape
     dt = _dtype_code(keys)
-    ws, wsb = _ws(cluster_prefill_workspace_size(s, n, n_clusters, dt, d), keys.device, workspace)
+    ws, wsb = _ws(workspace, keys.device, cluster_prefill_workspace_size, s, n, n_clusters, dt, d)
     pool_rows = k_pool.shape[1] if k_pool is not None else (v_pool.shape[1] if v_pool is not None else 0)
     ev = None
     if iter_events is not None:
         arr = (ctypes.c_void_p * len(iter_events))(*[e.cuda_event for e in iter_events])
-        ev = ctypes.cast(arr, ctypes.c_void_p)
-    _check(load_library().louiskv_cluster_prefill(
-        _ptr(keys), dt, s, n, d, n_clusters, n_iters, _ptr(init_idx),
-        _ptr(reps), reps.shape[1], _ptr(unit_start), _ptr(unit_size), _ptr(assign), _ptr(perm),
-        _ptr(values), _ptr(k_pool), _ptr(v_pool), pool_rows, int(pool_on_host), ev,
-        _ptr(ws), wsb, _stream(stream)))
+        ev = ctypes.addressof(arr)
+    _check(_native().cluster_prefill(
+        keys, dt, s, n, d, n_clusters, n_iters, init_idx,
+        reps, reps.shape[1], unit_start, unit_size, assign, perm,
+        values, k_pool, v_pool, pool_rows, int(pool_on_host), ev,
+        ws, wsb, stream))
 
 
 def cluster_prefill_pipelined_workspace_size(slices_per_chunk, n_tokens, n_clusters, dtype_code, pool_on_host,
                                              copy_engine, d=128) -> int:
-    return load_library().louiskv_cluster_prefill_pipelined_workspace_size(
+    return _native().cluster_prefill_pipelined_workspace_size(
         slices_per_chunk, n_tokens, d, n_clusters, dtype_code, int(pool_on_host), int(copy_engine))
 
 
@@ -242,34 +250,34 @@ def cluster_prefill_pipelined(keys, n_clusters: int, n_iters: int, init_idx, rep
     torch.cuda.Event objects (recorded once already, so that they exist)."""
     s, n, d = keys.shape
     dt = _dtype_code(keys)
-    ws, wsb = _ws(cluster_prefill_pipelined_workspace_size(min(slices_per_chunk, s), n, n_clusters, dt,
-                                                           pool_on_host, copy_engine, d), keys.device, workspace)
+    ws, wsb = _ws(workspace, keys.device, cluster_prefill_pipelined_workspace_size, min(slices_per_chunk, s), n,
+                  n_clusters, dt, pool_on_host, copy_engine, d)
     arr = (ctypes.c_void_p * len(chunk_events))(*[e.cuda_event for e in chunk_events])
-    _check(load_library().louiskv_cluster_prefill_pipelined(
-        _ptr(keys), dt, s, n, d, n_clusters, n_iters, _ptr(init_idx),
-        _ptr(reps), reps.shape[1], _ptr(unit_start), _ptr(unit_size), _ptr(assign), _ptr(perm),
-        _ptr(values), _ptr(k_pool), _ptr(v_pool), k_pool.shape[1], int(pool_on_host), slices_per_chunk,
-        int(copy_engine), ctypes.cast(arr, ctypes.c_void_p), len(chunk_events), _ptr(ws), wsb, _stream(stream),
-        _stream(copy_stream)))
+    _check(_native().cluster_prefill_pipelined(
+        keys, dt, s, n, d, n_clusters, n_iters, init_idx,
+        reps, reps.shape[1], unit_start, unit_size, assign, perm,
+        values, k_pool, v_pool, k_pool.shape[1], int(pool_on_host), slices_per_chunk,
+        int(copy_engine), ctypes.addressof(arr), len(chunk_events), ws, wsb, stream,
+        copy_stream))
 
 
 def kmeans_assign(keys, n_clusters: int, centroids, assign, workspace=None, stream=None):
     s, n, d = keys.shape
     dt = _dtype_code(keys)
-    ws, wsb = _ws(cluster_prefill_workspace_size(s, n, n_clusters, dt, d), keys.device, workspace)
-    _check(load_library().louiskv_kmeans_assign(
-        _ptr(keys), dt, s, n, d, n_clusters, _ptr(centroids), centroids.shape[1], _ptr(assign),
-        _ptr(ws), wsb, _stream(stream)))
+    ws, wsb = _ws(workspace, keys.device, cluster_prefill_workspace_size, s, n, n_clusters, dt, d)
+    _check(_native().kmeans_assign(
+        keys, dt, s, n, d, n_clusters, centroids, centroids.shape[1], assign,
+        ws, wsb, stream))
 
 
 def kmeans_update(keys, n_clusters: int, assign, centroids_in, centroids_out, counts=None, workspace=None,
                   stream=None):
     s, n, d = keys.shape
     dt = _dtype_code(keys)
-    ws, wsb = _ws(cluster_prefill_workspace_size(s, n, n_clusters, dt, d), keys.device, workspace)
-    _check(load_library().louiskv_kmeans_update(
-        _ptr(keys), dt, s, n, d, n_clusters, _ptr(assign), _ptr(centroids_in), _ptr(centroids_out),
-        centroids_out.shape[1], _ptr(counts), _ptr(ws), wsb, _stream(stream)))
+    ws, wsb = _ws(workspace, keys.device, cluster_prefill_workspace_size, s, n, n_clusters, dt, d)
+    _check(_native().kmeans_update(
+        keys, dt, s, n, d, n_clusters, assign, centroids_in, centroids_out,
+        centroids_out.shape[1], counts, ws, wsb, stream))
 
 
 def segment_output(k_new, v_new, k_local, v_local, step: int, seg_len: int, reps, unit_start, unit_size,
@@ -277,21 +285,21 @@ def segment_output(k_new, v_new, k_local, v_local, step: int, seg_len: int, reps
                    stream=None):
     s, d = k_new.shape
     pool_rows = k_pool.shape[1] if k_pool is not None else 0
-    _check(load_library().louiskv_segment_output(
-        _ptr(k_new), _ptr(v_new), _dtype_code(k_new), s, d, _ptr(k_local), _ptr(v_local), k_local.shape[1],
-        step, seg_len, _ptr(reps), _ptr(unit_start), _ptr(unit_size), reps.shape[1], n_clusters,
-        _ptr(k_pool), _ptr(v_pool), pool_rows, prompt_len, int(pool_on_host), _stream(stream)))
+    _check(_native().segment_output(
+        k_new, v_new, _dtype_code(k_new), s, d, k_local, v_local, k_local.shape[1],
+        step, seg_len, reps, unit_start, unit_size, reps.shape[1], n_clusters,
+        k_pool, v_pool, pool_rows, prompt_len, int(pool_on_host), stream))
 
 
 def boundary_check(q, q_ref, tau: float, mode: int, first_step: bool, fire_out, r_out=None, stream=None):
     g, h, d = q.shape
-    _check(load_library().louiskv_boundary_check(
-        _ptr(q), _ptr(q_ref), _dtype_code(q), g, h, d, float(tau), int(mode), int(first_step),
-        _ptr(r_out), _ptr(fire_out), _stream(stream)))
+    _check(_native().boundary_check(
+        q, q_ref, _dtype_code(q), g, h, d, float(tau), int(mode), int(first_step),
+        r_out, fire_out, stream))
 
 
 def retrieve_workspace_size(n_slices, units_cap, budget) -> int:
-    return load_library().louiskv_retrieve_workspace_size(n_slices, units_cap, budget)
+    return _native().retrieve_workspace_size(n_slices, units_cap, budget)
 
 
 def retrieve(q, n_kv_heads: int, reps, unit_start, unit_size, n_units: int, k_pool, v_pool, budget: int,
@@ -300,18 +308,18 @@ def retrieve(q, n_kv_heads: int, reps, unit_start, unit_size, n_units: int, k_po
     g, hq, d = q.shape
     s = reps.shape[0]
     cap = reps.shape[1]
-    ws, wsb = _ws(retrieve_workspace_size(s, cap, budget), q.device, workspace)
+    ws, wsb = _ws(workspace, q.device, retrieve_workspace_size, s, cap, budget)
     sc = (1.0 / d ** 0.5) if scale is None else scale
-    _check(load_library().louiskv_retrieve(
-        _ptr(q), _dtype_code(q), s, n_kv_heads, hq // n_kv_heads, d, float(sc),
-        _ptr(reps), _ptr(unit_start), _ptr(unit_size), cap, n_units,
-        _ptr(k_pool), _ptr(v_pool), k_pool.shape[1], int(pool_on_host), budget, _ptr(fire),
-        _ptr(sel_units), _ptr(n_sel_units), _ptr(n_sel), _ptr(k_buf), _ptr(v_buf), _ptr(scores_out),
-        _ptr(ws), wsb, _stream(stream)))
+    _check(_native().retrieve(
+        q, _dtype_code(q), s, n_kv_heads, hq // n_kv_heads, d, float(sc),
+        reps, unit_start, unit_size, cap, n_units,
+        k_pool, v_pool, k_pool.shape[1], int(pool_on_host), budget, fire,
+        sel_units, n_sel_units, n_sel, k_buf, v_buf, scores_out,
+        ws, wsb, stream))
 
 
 def sparse_decode_attn_workspace_size(n_slices, group_size, buf_rows, window, d=128) -> int:
-    return load_library().louiskv_sparse_decode_attn_workspace_size(n_slices, group_size, d, buf_rows, window)
+    return _native().sparse_decode_attn_workspace_size(n_slices, group_size, d, buf_rows, window)
 
 
 def sparse_decode_attn(q, n_kv_heads: int, k_buf, v_buf, n_sel, k_local, v_local, local_start: int, n_local: int,
@@ -321,16 +329,16 @@ def sparse_decode_attn(q, n_kv_heads: int, k_buf, v_buf, n_sel, k_local, v_local
     gs = hq // n_kv_heads
     buf_rows = k_buf.shape[1] if k_buf is not None else 0
     window = k_local.shape[1] if k_local is not None else 0
-    ws, wsb = _ws(sparse_decode_attn_workspace_size(s, gs, buf_rows, window, d), q.device, workspace)
+    ws, wsb = _ws(workspace, q.device, sparse_decode_attn_workspace_size, s, gs, buf_rows, window, d)
     sc = (1.0 / d ** 0.5) if scale is None else scale
-    _check(load_library().louiskv_sparse_decode_attn(
-        _ptr(q), _dtype_code(q), s, n_kv_heads, gs, d, float(sc), _ptr(k_buf), _ptr(v_buf), _ptr(n_sel), buf_rows,
-        _ptr(k_local), _ptr(v_local), window, local_start, n_local, _ptr(out), _dtype_code(out), _ptr(lse_out),
-        _ptr(ws), wsb, _stream(stream)))
+    _check(_native().sparse_decode_attn(
+        q, _dtype_code(q), s, n_kv_heads, gs, d, float(sc), k_buf, v_buf, n_sel, buf_rows,
+        k_local, v_local, window, local_start, n_local, out, _dtype_code(out), lse_out,
+        ws, wsb, stream))
 
 
 def retrieve_rows_workspace_size(n_slices, units_cap) -> int:
-    return load_library().louiskv_retrieve_rows_workspace_size(n_slices, units_cap)
+    return _native().retrieve_rows_workspace_size(n_slices, units_cap)
 
 
 def retrieve_rows(q, n_kv_heads: int, reps, unit_start, unit_size, n_units: int, budget: int, sel_units,
@@ -340,17 +348,17 @@ def retrieve_rows(q, n_kv_heads: int, reps, unit_start, unit_size, n_units: int,
     g, hq, d = q.shape
     s = reps.shape[0]
     cap = reps.shape[1]
-    ws, wsb = _ws(retrieve_rows_workspace_size(s, cap), q.device, workspace)
+    ws, wsb = _ws(workspace, q.device, retrieve_rows_workspace_size, s, cap)
     sc = (1.0 / d ** 0.5) if scale is None else scale
-    _check(load_library().louiskv_retrieve_rows(
-        _ptr(q), _dtype_code(q), s, n_kv_heads, hq // n_kv_heads, d, float(sc),
-        _ptr(reps), _ptr(unit_start), _ptr(unit_size), cap, n_units, budget, _ptr(fire),
-        _ptr(sel_units), _ptr(n_sel_units), _ptr(n_sel), _ptr(sel_rows), _ptr(scores_out),
-        _ptr(ws), wsb, _stream(stream)))
+    _check(_native().retrieve_rows(
+        q, _dtype_code(q), s, n_kv_heads, hq // n_kv_heads, d, float(sc),
+        reps, unit_start, unit_size, cap, n_units, budget, fire,
+        sel_units, n_sel_units, n_sel, sel_rows, scores_out,
+        ws, wsb, stream))
 
 
 def sparse_decode_attn_rows_workspace_size(n_slices, group_size, budget, window, d=128) -> int:
-    return load_library().louiskv_sparse_decode_attn_rows_workspace_size(n_slices, group_size, d, budget, window)
+    return _native().sparse_decode_attn_rows_workspace_size(n_slices, group_size, d, budget, window)
 
 
 def sparse_decode_attn_rows(q, n_kv_heads: int, k_pool, v_pool, sel_rows, n_sel, k_local, v_local,
@@ -362,17 +370,17 @@ def sparse_decode_attn_rows(q, n_kv_heads: int, k_pool, v_pool, sel_rows, n_sel,
     gs = hq // n_kv_heads
     budget = sel_rows.shape[1]
     window = k_local.shape[1] if k_local is not None else 0
-    ws, wsb = _ws(sparse_decode_attn_rows_workspace_size(s, gs, budget, window, d), q.device, workspace)
+    ws, wsb = _ws(workspace, q.device, sparse_decode_attn_rows_workspace_size, s, gs, budget, window, d)
     sc = (1.0 / d ** 0.5) if scale is None else scale
-    _check(load_library().louiskv_sparse_decode_attn_rows(
-        _ptr(q), _dtype_code(q), s, n_kv_heads, gs, d, float(sc), _ptr(k_pool), _ptr(v_pool), k_pool.shape[1],
-        _ptr(sel_rows), _ptr(n_sel), budget, _ptr(k_local), _ptr(v_local), window, local_start, n_local,
-        _ptr(out), _dtype_code(out), _ptr(lse_out), _ptr(ws), wsb, _stream(stream)))
+    _check(_native().sparse_decode_attn_rows(
+        q, _dtype_code(q), s, n_kv_heads, gs, d, float(sc), k_pool, v_pool, k_pool.shape[1],
+        sel_rows, n_sel, budget, k_local, v_local, window, local_start, n_local,
+        out, _dtype_code(out), lse_out, ws, wsb, stream))
 
 
 def decode_step_workspace_size(n_slices: int, dtype_code: int, group_size: int, units_cap: int, budget: int,
                                window: int) -> int:
-    return int(load_library().louiskv_decode_step_workspace_size(n_slices, dtype_code, group_size, units_cap,
+    return int(_native().decode_step_workspace_size(n_slices, dtype_code, group_size, units_cap,
                                                                  budget, window))
 
 
@@ -391,17 +399,17 @@ def decode_step(q, q_ref, tau: float, mode: int, step: int, fire, r_out, k_new, 
     if workspace is None:
         workspace = torch.zeros(decode_step_workspace_size(s, dt, hq // h, reps.shape[1], budget, window),
                                 dtype=torch.uint8, device=q.device)
-    _check(load_library().louiskv_decode_step(
-        _ptr(q), _ptr(q_ref), dt, g, hq, h, d, float(tau), mode, step, _ptr(r_out), _ptr(fire),
-        _ptr(k_new), _ptr(v_new), _ptr(k_local), _ptr(v_local), window, seg_len, _ptr(reps), _ptr(unit_start),
-        _ptr(unit_size), reps.shape[1], n_clusters, _ptr(k_pool), _ptr(v_pool), k_pool.shape[1], prompt_len,
-        budget, _ptr(sel_units), _ptr(n_sel_units), _ptr(n_sel), _ptr(sel_rows), _ptr(scores_out), _ptr(out),
-        _dtype_code(out), _ptr(lse_out), _ptr(workspace), workspace.numel(), _stream(stream)))
+    _check(_native().decode_step(
+        q, q_ref, dt, g, hq, h, d, float(tau), mode, step, r_out, fire,
+        k_new, v_new, k_local, v_local, window, seg_len, reps, unit_start,
+        unit_size, reps.shape[1], n_clusters, k_pool, v_pool, k_pool.shape[1], prompt_len,
+        budget, sel_units, n_sel_units, n_sel, sel_rows, scores_out, out,
+        _dtype_code(out), lse_out, workspace, workspace.numel(), stream))
 
 
 def decode_step_cached_workspace_size(n_slices: int, dtype_code: int, group_size: int, units_cap: int, budget: int,
                                       window: int) -> int:
-    return int(load_library().louiskv_decode_step_cached_workspace_size(n_slices, dtype_code, group_size, units_cap,
+    return int(_native().decode_step_cached_workspace_size(n_slices, dtype_code, group_size, units_cap,
                                                                         budget, window))
 
 
@@ -420,14 +428,14 @@ def decode_step_cached(q, q_ref, tau: float, mode: int, step: int, fire, r_out, 
     if workspace is None:
         workspace = torch.zeros(decode_step_cached_workspace_size(s, dt, hq // h, reps.shape[1], budget, window),
                                 dtype=torch.uint8, device=q.device)
-    _check(load_library().louiskv_decode_step_cached(
-        _ptr(q), _ptr(q_ref), dt, g, hq, h, d, float(tau), mode, step, _ptr(r_out), _ptr(fire),
-        _ptr(k_new), _ptr(v_new), _ptr(k_local), _ptr(v_local), window, seg_len, _ptr(reps), _ptr(unit_start),
-        _ptr(unit_size), reps.shape[1], n_clusters, _ptr(k_pool), _ptr(v_pool), k_pool.shape[1], int(pool_on_host),
-        prompt_len, budget, k_buf.shape[1], _ptr(k_buf), _ptr(v_buf), _ptr(buf_row), _ptr(slot_step),
-        _ptr(slot_list), _ptr(n_fetched), _ptr(sel_units), _ptr(n_sel_units), _ptr(n_sel), _ptr(sel_rows),
-        _ptr(scores_out), _ptr(out), _dtype_code(out), _ptr(lse_out), _ptr(workspace), workspace.numel(),
-        _stream(stream)))
+    _check(_native().decode_step_cached(
+        q, q_ref, dt, g, hq, h, d, float(tau), mode, step, r_out, fire,
+        k_new, v_new, k_local, v_local, window, seg_len, reps, unit_start,
+        unit_size, reps.shape[1], n_clusters, k_pool, v_pool, k_pool.shape[1], int(pool_on_host),
+        prompt_len, budget, k_buf.shape[1], k_buf, v_buf, buf_row, slot_step,
+        slot_list, n_fetched, sel_units, n_sel_units, n_sel, sel_rows,
+        scores_out, out, _dtype_code(out), lse_out, workspace, workspace.numel(),
+        stream))
 
 
 NOALLOC_SCRATCH_BYTES = 8 << 20   # LOUISKV_NOALLOC_SCRATCH_BYTES
@@ -444,10 +452,10 @@ def sparse_decode_attn_rows_noalloc(q, n_kv_heads: int, k_pool, v_pool, sel_rows
     budget = sel_rows.shape[1]
     window = k_local.shape[1] if k_local is not None else 0
     sc = (1.0 / d ** 0.5) if scale is None else scale
-    _check(load_library().louiskv_sparse_decode_attn_rows_noalloc(
-        _ptr(q), _dtype_code(q), s, n_kv_heads, gs, d, float(sc), _ptr(k_pool), _ptr(v_pool), k_pool.shape[1],
-        _ptr(sel_rows), _ptr(n_sel), budget, _ptr(k_local), _ptr(v_local), window, local_start, n_local,
-        _ptr(out), _dtype_code(out), _ptr(lse_out), _stream(stream)))
+    _check(_native().sparse_decode_attn_rows_noalloc(
+        q, _dtype_code(q), s, n_kv_heads, gs, d, float(sc), k_pool, v_pool, k_pool.shape[1],
+        sel_rows, n_sel, budget, k_local, v_local, window, local_start, n_local,
+        out, _dtype_code(out), lse_out, stream))
 
 
 def decode_prologue(q, q_ref, tau: float, mode: int, first_step: bool, fire, r_out, k_new, v_new, k_local, v_local,
@@ -458,18 +466,18 @@ def decode_prologue(q, q_ref, tau: float, mode: int, first_step: bool, fire, r_o
     s = k_new.shape[0]
     window = k_local.shape[1]
     pool_rows = k_pool.shape[1] if k_pool is not None else 0
-    _check(load_library().louiskv_decode_prologue(
-        _ptr(q), _ptr(q_ref), _dtype_code(q), g, hq, d, float(tau), mode, int(first_step), _ptr(r_out), _ptr(fire),
-        _ptr(k_new), _ptr(v_new), s, _ptr(k_local), _ptr(v_local), window, step, seg_len, _ptr(reps),
-        _ptr(unit_start), _ptr(unit_size), reps.shape[1], n_clusters, _ptr(k_pool), _ptr(v_pool), pool_rows,
-        prompt_len, int(pool_on_host), _stream(stream)))
+    _check(_native().decode_prologue(
+        q, q_ref, _dtype_code(q), g, hq, d, float(tau), mode, int(first_step), r_out, fire,
+        k_new, v_new, s, k_local, v_local, window, step, seg_len, reps,
+        unit_start, unit_size, reps.shape[1], n_clusters, k_pool, v_pool, pool_rows,
+        prompt_len, int(pool_on_host), stream))
 
 
 # ------------------------------------------------------ ablation baselines
 
 def fire_every(fire, step: int, stride: int, stream=None):
     """Fixed-stride trigger: fire[g] = (step % stride == 0) for every group."""
-    _check(load_library().louiskv_fire_every(_ptr(fire), fire.shape[0], step, stride, _stream(stream)))
+    _check(_native().fire_every(fire, fire.shape[0], step, stride, stream))
 
 
 def page_prefill(keys, page_len: int, reps, unit_start, unit_size, values=None, k_pool=None, v_pool=None,
@@ -477,10 +485,10 @@ def page_prefill(keys, page_len: int, reps, unit_start, unit_size, values=None, 
     """Page-level index of the prompt (mean key per page), pool in token order."""
     s, n, d = keys.shape
     pool_rows = k_pool.shape[1] if k_pool is not None else 0
-    _check(load_library().louiskv_page_prefill(
-        _ptr(keys), _ptr(values), _dtype_code(keys), s, n, d, page_len, _ptr(reps), reps.shape[1],
-        _ptr(unit_start), _ptr(unit_size), _ptr(k_pool), _ptr(v_pool), pool_rows, int(pool_on_host),
-        _stream(stream)))
+    _check(_native().page_prefill(
+        keys, values, _dtype_code(keys), s, n, d, page_len, reps, reps.shape[1],
+        unit_start, unit_size, k_pool, v_pool, pool_rows, int(pool_on_host),
+        stream))
 
 
 def retrieve_rows_per_head(q, n_kv_heads: int, reps, unit_start, unit_size, n_units: int, budget: int, sel_units,
@@ -491,13 +499,13 @@ def retrieve_rows_per_head(q, n_kv_heads: int, reps, unit_start, unit_size, n_un
     s = reps.shape[0]
     cap = reps.shape[1]
     gs = hq // n_kv_heads
-    ws, wsb = _ws(retrieve_rows_workspace_size(s * gs, cap), q.device, workspace)
+    ws, wsb = _ws(workspace, q.device, retrieve_rows_workspace_size, s * gs, cap)
     sc = (1.0 / d ** 0.5) if scale is None else scale
-    _check(load_library().louiskv_retrieve_rows_per_head(
-        _ptr(q), _dtype_code(q), s, n_kv_heads, gs, d, float(sc),
-        _ptr(reps), _ptr(unit_start), _ptr(unit_size), cap, n_units, budget, _ptr(fire),
-        _ptr(sel_units), _ptr(n_sel_units), _ptr(n_sel), _ptr(sel_rows), _ptr(scores_out),
-        _ptr(ws), wsb, _stream(stream)))
+    _check(_native().retrieve_rows_per_head(
+        q, _dtype_code(q), s, n_kv_heads, gs, d, float(sc),
+        reps, unit_start, unit_size, cap, n_units, budget, fire,
+        sel_units, n_sel_units, n_sel, sel_rows, scores_out,
+        ws, wsb, stream))
 
 
 def sparse_decode_attn_rows_per_head(q, n_kv_heads: int, k_pool, v_pool, sel_rows, n_sel, k_local, v_local,
@@ -510,25 +518,25 @@ def sparse_decode_attn_rows_per_head(q, n_kv_heads: int, k_pool, v_pool, sel_row
     gs = hq // n_kv_heads
     budget = sel_rows.shape[1]
     window = k_local.shape[1] if k_local is not None else 0
-    ws, wsb = _ws(sparse_decode_attn_rows_workspace_size(s * gs, 1, budget, window, d), q.device, workspace)
+    ws, wsb = _ws(workspace, q.device, sparse_decode_attn_rows_workspace_size, s * gs, 1, budget, window, d)
     sc = (1.0 / d ** 0.5) if scale is None else scale
-    _check(load_library().louiskv_sparse_decode_attn_rows_per_head(
-        _ptr(q), _dtype_code(q), s, n_kv_heads, gs, d, float(sc), _ptr(k_pool), _ptr(v_pool), k_pool.shape[1],
-        _ptr(sel_rows), _ptr(n_sel), budget, _ptr(k_local), _ptr(v_local), window, local_start, n_local,
-        _ptr(out), _dtype_code(out), _ptr(lse_out), _ptr(ws), wsb, _stream(stream)))
+    _check(_native().sparse_decode_attn_rows_per_head(
+        q, _dtype_code(q), s, n_kv_heads, gs, d, float(sc), k_pool, v_pool, k_pool.shape[1],
+        sel_rows, n_sel, budget, k_local, v_local, window, local_start, n_local,
+        out, _dtype_code(out), lse_out, ws, wsb, stream))
 
 
 # ------------------------------------------------ boundary-delimited segments
 
 def segment_state_ints(window: int) -> int:
     """int32 entries per slice of the segment state (louiskv_segment_state_ints)."""
-    return load_library().louiskv_segment_state_ints(window)
+    return _native().segment_state_ints(window)
 
 
 def segment_state_init(seg_state, window: int, n_clusters: int, stream=None):
     """Segment state before decode step 0 (clusters only, empty window)."""
-    _check(load_library().louiskv_segment_state_init(_ptr(seg_state), seg_state.shape[0], window, n_clusters,
-                                                     _stream(stream)))
+    _check(_native().segment_state_init(seg_state, seg_state.shape[0], window, n_clusters,
+                                                     stream))
 
 
 def segment_output_boundary(k_new, v_new, k_local, v_local, step: int, seg_max: int, fire, seg_state, reps,
@@ -536,11 +544,11 @@ def segment_output_boundary(k_new, v_new, k_local, v_local, step: int, seg_max: 
                             prompt_len: int = 0, pool_on_host: bool = False, stream=None):
     s, d = k_new.shape
     pool_rows = k_pool.shape[1] if k_pool is not None else 0
-    _check(load_library().louiskv_segment_output_boundary(
-        _ptr(k_new), _ptr(v_new), _dtype_code(k_new), s, n_kv_heads, d, _ptr(k_local), _ptr(v_local),
-        k_local.shape[1], step, seg_max, _ptr(fire), _ptr(seg_state), _ptr(reps), _ptr(unit_start),
-        _ptr(unit_size), reps.shape[1], n_clusters, _ptr(k_pool), _ptr(v_pool), pool_rows, prompt_len,
-        int(pool_on_host), _stream(stream)))
+    _check(_native().segment_output_boundary(
+        k_new, v_new, _dtype_code(k_new), s, n_kv_heads, d, k_local, v_local,
+        k_local.shape[1], step, seg_max, fire, seg_state, reps, unit_start,
+        unit_size, reps.shape[1], n_clusters, k_pool, v_pool, pool_rows, prompt_len,
+        int(pool_on_host), stream))
 
 
 def retrieve_seg(q, n_kv_heads: int, reps, unit_start, unit_size, max_units: int, seg_state, window: int, k_pool,
@@ -550,14 +558,14 @@ def retrieve_seg(q, n_kv_heads: int, reps, unit_start, unit_size, max_units: int
     g, hq, d = q.shape
     s = reps.shape[0]
     cap = reps.shape[1]
-    ws, wsb = _ws(retrieve_workspace_size(s, cap, budget), q.device, workspace)
+    ws, wsb = _ws(workspace, q.device, retrieve_workspace_size, s, cap, budget)
     sc = (1.0 / d ** 0.5) if scale is None else scale
-    _check(load_library().louiskv_retrieve_seg(
-        _ptr(q), _dtype_code(q), s, n_kv_heads, hq // n_kv_heads, d, float(sc),
-        _ptr(reps), _ptr(unit_start), _ptr(unit_size), cap, max_units, _ptr(seg_state), window,
-        _ptr(k_pool), _ptr(v_pool), k_pool.shape[1], int(pool_on_host), budget, _ptr(fire),
-        _ptr(sel_units), _ptr(n_sel_units), _ptr(n_sel), _ptr(k_buf), _ptr(v_buf), _ptr(scores_out),
-        _ptr(ws), wsb, _stream(stream)))
+    _check(_native().retrieve_seg(
+        q, _dtype_code(q), s, n_kv_heads, hq // n_kv_heads, d, float(sc),
+        reps, unit_start, unit_size, cap, max_units, seg_state, window,
+        k_pool, v_pool, k_pool.shape[1], int(pool_on_host), budget, fire,
+        sel_units, n_sel_units, n_sel, k_buf, v_buf, scores_out,
+        ws, wsb, stream))
 
 
 def retrieve_rows_seg(q, n_kv_heads: int, reps, unit_start, unit_size, max_units: int, seg_state, window: int,
@@ -566,13 +574,13 @@ def retrieve_rows_seg(q, n_kv_heads: int, reps, unit_start, unit_size, max_units
     g, hq, d = q.shape
     s = reps.shape[0]
     cap = reps.shape[1]
-    ws, wsb = _ws(retrieve_rows_workspace_size(s, cap), q.device, workspace)
+    ws, wsb = _ws(workspace, q.device, retrieve_rows_workspace_size, s, cap)
     sc = (1.0 / d ** 0.5) if scale is None else scale
-    _check(load_library().louiskv_retrieve_rows_seg(
-        _ptr(q), _dtype_code(q), s, n_kv_heads, hq // n_kv_heads, d, float(sc),
-        _ptr(reps), _ptr(unit_start), _ptr(unit_size), cap, max_units, _ptr(seg_state), window, budget,
-        _ptr(fire), _ptr(sel_units), _ptr(n_sel_units), _ptr(n_sel), _ptr(sel_rows), _ptr(scores_out),
-        _ptr(ws), wsb, _stream(stream)))
+    _check(_native().retrieve_rows_seg(
+        q, _dtype_code(q), s, n_kv_heads, hq // n_kv_heads, d, float(sc),
+        reps, unit_start, unit_size, cap, max_units, seg_state, window, budget,
+        fire, sel_units, n_sel_units, n_sel, sel_rows, scores_out,
+        ws, wsb, stream))
 
 
 def sparse_decode_attn_seg(q, n_kv_heads: int, k_buf, v_buf, n_sel, k_local, v_local, seg_state, n_tokens: int,
@@ -582,12 +590,12 @@ def sparse_decode_attn_seg(q, n_kv_heads: int, k_buf, v_buf, n_sel, k_local, v_l
     gs = hq // n_kv_heads
     buf_rows = k_buf.shape[1] if k_buf is not None else 0
     window = k_local.shape[1]
-    ws, wsb = _ws(sparse_decode_attn_workspace_size(s, gs, buf_rows, window, d), q.device, workspace)
+    ws, wsb = _ws(workspace, q.device, sparse_decode_attn_workspace_size, s, gs, buf_rows, window, d)
     sc = (1.0 / d ** 0.5) if scale is None else scale
-    _check(load_library().louiskv_sparse_decode_attn_seg(
-        _ptr(q), _dtype_code(q), s, n_kv_heads, gs, d, float(sc), _ptr(k_buf), _ptr(v_buf), _ptr(n_sel), buf_rows,
-        _ptr(k_local), _ptr(v_local), window, _ptr(seg_state), n_tokens, _ptr(out), _dtype_code(out),
-        _ptr(lse_out), _ptr(ws), wsb, _stream(stream)))
+    _check(_native().sparse_decode_attn_seg(
+        q, _dtype_code(q), s, n_kv_heads, gs, d, float(sc), k_buf, v_buf, n_sel, buf_rows,
+        k_local, v_local, window, seg_state, n_tokens, out, _dtype_code(out),
+        lse_out, ws, wsb, stream))
 
 
 def sparse_decode_attn_rows_seg(q, n_kv_heads: int, k_pool, v_pool, sel_rows, n_sel, k_local, v_local, seg_state,
@@ -598,16 +606,16 @@ def sparse_decode_attn_rows_seg(q, n_kv_heads: int, k_pool, v_pool, sel_rows, n_
     gs = hq // n_kv_heads
     budget = sel_rows.shape[1]
     window = k_local.shape[1]
-    ws, wsb = _ws(sparse_decode_attn_rows_workspace_size(s, gs, budget, window, d), q.device, workspace)
+    ws, wsb = _ws(workspace, q.device, sparse_decode_attn_rows_workspace_size, s, gs, budget, window, d)
     sc = (1.0 / d ** 0.5) if scale is None else scale
-    _check(load_library().louiskv_sparse_decode_attn_rows_seg(
-        _ptr(q), _dtype_code(q), s, n_kv_heads, gs, d, float(sc), _ptr(k_pool), _ptr(v_pool), k_pool.shape[1],
-        _ptr(sel_rows), _ptr(n_sel), budget, _ptr(k_local), _ptr(v_local), window, _ptr(seg_state), n_tokens,
-        _ptr(out), _dtype_code(out), _ptr(lse_out), _ptr(ws), wsb, _stream(stream)))
+    _check(_native().sparse_decode_attn_rows_seg(
+        q, _dtype_code(q), s, n_kv_heads, gs, d, float(sc), k_pool, v_pool, k_pool.shape[1],
+        sel_rows, n_sel, budget, k_local, v_local, window, seg_state, n_tokens,
+        out, _dtype_code(out), lse_out, ws, wsb, stream))
 
 
 def retrieve_delta_workspace_size(n_slices, units_cap, budget) -> int:
-    return load_library().louiskv_retrieve_delta_workspace_size(n_slices, units_cap, budget)
+    return _native().retrieve_delta_workspace_size(n_slices, units_cap, budget)
 
 
 def retrieve_delta(q, n_kv_heads: int, reps, unit_start, unit_size, n_units: int, k_pool, v_pool, budget: int,
@@ -618,14 +626,14 @@ def retrieve_delta(q, n_kv_heads: int, reps, unit_start, unit_size, n_units: int
     g, hq, d = q.shape
     s = reps.shape[0]
     cap = reps.shape[1]
-    ws, wsb = _ws(retrieve_delta_workspace_size(s, cap, budget), q.device, workspace)
+    ws, wsb = _ws(workspace, q.device, retrieve_delta_workspace_size, s, cap, budget)
     sc = (1.0 / d ** 0.5) if scale is None else scale
-    _check(load_library().louiskv_retrieve_delta(
-        _ptr(q), _dtype_code(q), s, n_kv_heads, hq // n_kv_heads, d, float(sc),
-        _ptr(reps), _ptr(unit_start), _ptr(unit_size), cap, n_units, _ptr(seg_state), window,
-        _ptr(k_pool), _ptr(v_pool), k_pool.shape[1], int(pool_on_host), budget, _ptr(fire),
-        _ptr(sel_units), _ptr(n_sel_units), _ptr(n_sel), _ptr(k_buf), _ptr(v_buf), _ptr(buf_row),
-        _ptr(slot_list), _ptr(n_fetched), _ptr(scores_out), _ptr(ws), wsb, _stream(stream)))
+    _check(_native().retrieve_delta(
+        q, _dtype_code(q), s, n_kv_heads, hq // n_kv_heads, d, float(sc),
+        reps, unit_start, unit_size, cap, n_units, seg_state, window,
+        k_pool, v_pool, k_pool.shape[1], int(pool_on_host), budget, fire,
+        sel_units, n_sel_units, n_sel, k_buf, v_buf, buf_row,
+        slot_list, n_fetched, scores_out, ws, wsb, stream))
 
 
 CACHE_MAX_ROWS = 65536   # louiskv_retrieve_cached: slots per slice at most
@@ -639,19 +647,19 @@ def retrieve_cached(q, n_kv_heads: int, reps, unit_start, unit_size, n_units: in
     g, hq, d = q.shape
     s = reps.shape[0]
     cap = reps.shape[1]
-    ws, wsb = _ws(retrieve_delta_workspace_size(s, cap, budget), q.device, workspace)
+    ws, wsb = _ws(workspace, q.device, retrieve_delta_workspace_size, s, cap, budget)
     sc = (1.0 / d ** 0.5) if scale is None else scale
-    _check(load_library().louiskv_retrieve_cached(
-        _ptr(q), _dtype_code(q), s, n_kv_heads, hq // n_kv_heads, d, float(sc),
-        _ptr(reps), _ptr(unit_start), _ptr(unit_size), cap, n_units, _ptr(seg_state), window,
-        _ptr(k_pool), _ptr(v_pool), k_pool.shape[1], int(pool_on_host), budget, k_buf.shape[1], step, _ptr(fire),
-        _ptr(sel_units), _ptr(n_sel_units), _ptr(n_sel), _ptr(k_buf), _ptr(v_buf), _ptr(buf_row), _ptr(slot_step),
-        _ptr(slot_list), _ptr(n_fetched), _ptr(scores_out), _ptr(ws), wsb, _stream(stream)))
+    _check(_native().retrieve_cached(
+        q, _dtype_code(q), s, n_kv_heads, hq // n_kv_heads, d, float(sc),
+        reps, unit_start, unit_size, cap, n_units, seg_state, window,
+        k_pool, v_pool, k_pool.shape[1], int(pool_on_host), budget, k_buf.shape[1], step, fire,
+        sel_units, n_sel_units, n_sel, k_buf, v_buf, buf_row, slot_step,
+        slot_list, n_fetched, scores_out, ws, wsb, stream))
 
 
 def pack_pool(keys, values, perm, k_pool, v_pool=None, pool_on_host: bool = False, stream=None):
     """Prompt K/V rows into the pools in perm order (each cluster contiguous)."""
     s, n, d = keys.shape
-    _check(load_library().louiskv_pack_pool(
-        _ptr(keys), _ptr(values), _dtype_code(keys), s, n, d, _ptr(perm), _ptr(k_pool), _ptr(v_pool),
-        k_pool.shape[1], int(pool_on_host), _stream(stream)))
+    _check(_native().pack_pool(
+        keys, values, _dtype_code(keys), s, n, d, perm, k_pool, v_pool,
+        k_pool.shape[1], int(pool_on_host), stream))

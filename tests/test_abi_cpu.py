@@ -232,3 +232,25 @@ def test_bench_refuses_more_than_one_gpu():
     r = subprocess.run([sys.executable, os.path.join(root, "bench.py"), "--gpus", "2"], capture_output=True,
                        text=True, timeout=120)
     assert r.returncode == 2 and "one GPU" in r.stderr and r.stdout == ""
+
+
+def test_native_binding_marshals_like_the_abi(lib):
+    """The native binding has every ABI call with sizes, status or a stream,
+    refuses what the ABI cannot take, and passes sizes and pointers through."""
+    import torch
+    from paper_2510_11292_amd import louiskv as L
+    N = L._native()
+    for name in declared_functions():
+        if name not in ("louiskv_abi_version", "louiskv_status_str", "louiskv_last_error"):
+            assert hasattr(N, name[len("louiskv_"):]), name
+    assert (N.decode_step_workspace_size(8, L.BF16, 4, 1024, 2048, 128)
+            == lib.louiskv_decode_step_workspace_size(8, L.BF16, 4, 1024, 2048, 128))
+    with pytest.raises(TypeError):
+        N.decode_step_workspace_size(8, L.BF16)
+    with pytest.raises(TypeError):
+        N.decode_step_workspace_size(8.5, L.BF16, 4, 1024, 2048, 128)
+    x = torch.zeros(4, 128)
+    with pytest.raises(ValueError, match="contiguous"):
+        L.pack_pool(x.view(1, 4, 128), None, torch.zeros(1, 4, dtype=torch.int32), torch.zeros(1, 128, 4).mT, stream=0)
+    with pytest.raises(L.LouisKVError, match="pool_rows"):    # status and text of a refused call
+        L.pack_pool(x.view(1, 4, 128), None, torch.zeros(1, 4, dtype=torch.int32), torch.zeros(1, 3, 128), stream=0)
