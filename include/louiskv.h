@@ -437,12 +437,11 @@ int louiskv_sparse_decode_attn_rows(const void* q, int32_t dtype, int64_t n_slic
  * selected pool rows) and the attention over [KV_critical : KV_local]
  * (Section 3.1), current token included.  Meant for few groups per call (one
  * layer of a model at a time): every kernel spreads a slice over many
- * blocks, and the blocks of a slice hand over through the workspace (the
- * last one to finish a phase completes it) instead of through extra
- * launches.  In the one-launch form each block of a slice scores a part of
- * the units and attends a chunk of the rows; when the group fires, blocks
- * wait (bounded) for the slice's last scoring block to publish the
- * selection.
+ * blocks, and the blocks of a slice hand over through the workspace instead
+ * of through extra launches.  In the one-launch form each block of a slice
+ * scores a part of the units, attends a chunk of the rows and merges a share
+ * of the outputs; when the group fires, blocks wait (bounded) for the slice's
+ * last block to make the selection.
  *
  * Results equal, bit for bit, louiskv_decode_prologue + louiskv_retrieve_rows
  * + louiskv_sparse_decode_attn_rows (the selected units, rows, scores, r,
@@ -463,8 +462,10 @@ int louiskv_sparse_decode_attn_rows(const void* q, int32_t dtype, int64_t n_slic
  *
  * workspace  louiskv_decode_step_workspace_size() bytes.  It must be zero
  *            before its first use (for example allocated zeroed); every call
- *            leaves its arrival counters and flags at zero again, so it is
- *            reused without clearing.  Calls that share it must not overlap.
+ *            leaves its arrival counters and the words its blocks handed each
+ *            other at zero again, so it is reused without clearing, also by
+ *            calls of the other dtype or louiskv_decode_step_cached with the
+ *            same sizes.  Calls that share it must not overlap.
  *            Its first (4 * n_slices + 1) * 64 int32 words are those
  *            counters and flags; the last of them is a status word that a
  *            block sets to 1 if its wait for a selection ever gave up (after

@@ -53,44 +53,62 @@ __device__ __forceinline__ void load_row8(const float* p, float* x) {
 
 constexpr int kBndHeadsPerPass = 32;   // 16 lane groups x 2 heads, all loads issued together
 
+// The 8 dims of two heads of q and q_ref that a thread takes in one pass, as
+// loaded; kept apart from the arithmetic so that a caller can issue other
+// loads in between.
+template <class T>
+struct BoundaryRows {
+  uint4 a[2][sizeof(T) / 2], b[2][sizeof(T) / 2];
+};
+
+template <class T>
+__device__ __forceinline__ void boundary_load(const T* __restrict__ q, const T* __restrict__ q_ref, int n_heads,
+                                              int64_t g, int p, BoundaryRows<T>& x) {
+  const int tid = threadIdx.x, sub = tid & 15, hg = tid >> 4;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int h = p + hg + 16 * i;
+    const size_t o = ((size_t)g * n_heads + (h < n_heads ? h : 0)) * kHeadDim + 8 * sub;
+#pragma unroll
+    for (int c = 0; c < (int)sizeof(T) / 2; ++c) {
+      x.a[i][c] = reinterpret_cast<const uint4*>(q + o)[c];
+      x.b[i][c] = reinterpret_cast<const uint4*>(q_ref + o)[c];
+    }
+  }
+}
+
 // r of group g (Section 4.1): the mean over the group's n_heads query heads
-// of cos(q_ref, q), in float64; NaN at the first step.  Threads 0..255 load:
+// of cos(q_ref, q), in float64; NaN at the first step.  Threads 0..255 load
+// (x: the first pass, boundary_load with p = 0):
 // 16 lanes per head (lane sub holds dims 8*sub..+7), each 16-lane group takes
 // two heads per pass, the dot product and norms of a head are DPP row sums.
 // Every thread of the block must call it (one barrier); every thread gets r,
 // summed in the same order, so blocks that test the same group agree bit
 // for bit.
 template <class T>
-__device__ __forceinline__ double boundary_r(const T* __restrict__ q, const T* __restrict__ q_ref, int n_heads,
-                                             int first, int64_t g, double* s_part /* [16] in LDS */) {
+__device__ __forceinline__ double boundary_r(BoundaryRows<T>& x, const T* __restrict__ q, const T* __restrict__ q_ref,
+                                             int n_heads, int first, int64_t g, double* s_part /* [16] in LDS */) {
   const int tid = threadIdx.x, sub = tid & 15, hg = tid >> 4;
-  const size_t base = (size_t)g * n_heads * kHeadDim;
   double acc = 0.0;
   if (!first && tid < 256) {
     for (int p = 0; p < n_heads; p += kBndHeadsPerPass) {
-      float a[2][8], b[2][8];
-      bool ok[2];
+      if (p > 0) boundary_load(q, q_ref, n_heads, g, p, x);
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        const int h = p + hg + 16 * i;
-        ok[i] = h < n_heads;
-        const size_t o = base + (size_t)(ok[i] ? h : 0) * kHeadDim + 8 * sub;
-        load_row8(q + o, a[i]);
-        load_row8(q_ref + o, b[i]);
-      }
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
+        float a[8], b[8];
+        load_row8(reinterpret_cast<const T*>(x.a[i]), a);
+        load_row8(reinterpret_cast<const T*>(x.b[i]), b);
         double dot = 0.0, na = 0.0, nb = 0.0;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          dot = fma((double)a[i][e], (double)b[i][e], dot);
-          na = fma((double)a[i][e], (double)a[i][e], na);
-          nb = fma((double)b[i][e], (double)b[i][e], nb);
+          dot = fma((double)a[e], (double)b[e], dot);
+          na = fma((double)a[e], (double)a[e], na);
+          nb = fma((double)b[e], (double)b[e], nb);
         }
         dot = row16_sum_f64(dot);
         na = row16_sum_f64(na);
         nb = row16_sum_f64(nb);
-        if (ok[i]) acc += dot / fmax(sqrt(na) * sqrt(nb), 1e-30);
+        if (p + hg + 16 * i < n_heads) acc += dot / fmax(sqrt(na) * sqrt(nb), 1e-30);
       }
     }
   }
@@ -100,6 +118,14 @@ __device__ __forceinline__ double boundary_r(const T* __restrict__ q, const T* _
   double r = 0.0;
   for (int i = 0; i < 16; ++i) r += s_part[i];
   return r / (double)n_heads;
+}
+
+template <class T>
+__device__ __forceinline__ double boundary_r(const T* __restrict__ q, const T* __restrict__ q_ref, int n_heads,
+                                             int first, int64_t g, double* s_part) {
+  BoundaryRows<T> x;
+  if (!first && threadIdx.x < 256) boundary_load(q, q_ref, n_heads, g, 0, x);
+  return boundary_r(x, q, q_ref, n_heads, first, g, s_part);
 }
 
 // One block of 4 waves per group: r, the decision (first step, or r < tau),
@@ -341,9 +367,20 @@ __device__ __forceinline__ uint64_t unit_key(double a, int id) {
 }
 __device__ __forceinline__ int key_unit(uint64_t k) { return kMaxUnits - 1 - (int)(k & (kMaxUnits - 1)); }
 
+// x of lane (lane ^ 16) and (lane ^ 32): the lane-row swaps of gfx950 and a
+// select, on the vector ALU.  (ds_bpermute shares the compute unit's one LDS
+// pipe: with eight waves exchanging at once it is what they wait for.)
+__device__ __forceinline__ uint32_t xor16_u32(uint32_t x, int lane) {
+  const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);   // rows 0 0 2 2 and 1 1 3 3
+  return lane & 16 ? r[0] : r[1];
+}
+__device__ __forceinline__ uint32_t xor32_u32(uint32_t x, int lane) {
+  const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);   // the lower half twice, the upper half twice
+  return lane & 32 ? r[0] : r[1];
+}
+
 // The key of lane (lane ^ JJ), JJ < 64.  Distances 1 and 2 are quad
-// permutations and 4 and 8 row shifts (DPP, no LDS crossbar); 16 and 32 go
-// through ds_bpermute.
+// permutations and 4 and 8 row shifts (DPP); 16 and 32 lane-row swaps.
 template <int JJ>
 __device__ __forceinline__ uint64_t xor_partner_u64(uint64_t v, int lane) {
   const int lo = (int)(uint32_t)v, hi = (int)(uint32_t)(v >> 32);
@@ -362,11 +399,41 @@ __device__ __forceinline__ uint64_t xor_partner_u64(uint64_t v, int lane) {
     const bool up = (lane & JJ) != 0;
     plo = up ? blo : alo;
     phi = up ? bhi : ahi;
+  } else if constexpr (JJ == 16) {
+    plo = (int)xor16_u32((uint32_t)lo, lane);
+    phi = (int)xor16_u32((uint32_t)hi, lane);
   } else {
-    plo = __shfl_xor(lo, JJ, kWave);
-    phi = __shfl_xor(hi, JJ, kWave);
+    static_assert(JJ == 32, "a power of two below the wave's width");
+    plo = (int)xor32_u32((uint32_t)lo, lane);
+    phi = (int)xor32_u32((uint32_t)hi, lane);
   }
   return ((uint64_t)(uint32_t)phi << 32) | (uint32_t)plo;
+}
+
+// Sum and maximum over a wave, every lane (the sum pairs lanes 32, 16, .., 1
+// apart in that order, as wave_sum does).
+__device__ __forceinline__ double xor_partner_f64(double x, int lane, int o) {
+  const uint64_t v = (uint64_t)__double_as_longlong(x);
+  uint64_t r;
+  switch (o) {   // o is a constant wherever this is called
+    case 32: r = xor_partner_u64<32>(v, lane); break;
+    case 16: r = xor_partner_u64<16>(v, lane); break;
+    case 8: r = xor_partner_u64<8>(v, lane); break;
+    case 4: r = xor_partner_u64<4>(v, lane); break;
+    case 2: r = xor_partner_u64<2>(v, lane); break;
+    default: r = xor_partner_u64<1>(v, lane); break;
+  }
+  return __longlong_as_double((long long)r);
+}
+__device__ __forceinline__ double lane_sum_f64(double x, int lane) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) x += xor_partner_f64(x, lane, o);
+  return x;
+}
+__device__ __forceinline__ double lane_max_f64(double x, int lane) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) x = fmax(x, xor_partner_f64(x, lane, o));
+  return x;
 }
 
 // One compare-exchange step at distance JJ of bitonic stage k (element index i).
@@ -408,15 +475,20 @@ __device__ __forceinline__ void sort128_desc(uint64_t& v0, uint64_t& v1, int lan
   bitonic_in_wave2(v0, v1, i0, i1, 2 * kWave, kWave / 2);
 }
 
+// v of lane 63 - lane.
+__device__ __forceinline__ uint64_t reverse_lanes_u64(uint64_t v, int lane) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, 0x140, 0xF, 0xF, false);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), 0x140, 0xF, 0xF, false);
+  return xor_partner_u64<32>(xor_partner_u64<16>((uint64_t)hi << 32 | lo, lane), lane);
+}
+
 // The 128 largest of two descending 128-key lists (t, v; same layout), in
 // descending order into t: the elementwise maxima of t and v reversed are
 // those keys as a bitonic sequence, which the last stage of the network sorts.
 __device__ __forceinline__ void merge_top128(uint64_t& t0, uint64_t& t1, uint64_t v0, uint64_t v1, int lane) {
-  const int src = kWave - 1 - lane;   // element 127 - i of v sits in lane 63 - i%64, the other register
-  const uint64_t r1 = ((uint64_t)(uint32_t)__shfl((int)(uint32_t)(v1 >> 32), src, kWave) << 32) |
-                      (uint32_t)__shfl((int)(uint32_t)v1, src, kWave);
-  const uint64_t r0 = ((uint64_t)(uint32_t)__shfl((int)(uint32_t)(v0 >> 32), src, kWave) << 32) |
-                      (uint32_t)__shfl((int)(uint32_t)v0, src, kWave);
+  // element 127 - i of v sits in lane 63 - i%64 of the other register: rows
+  // mirrored, then exchanged end to end
+  const uint64_t r0 = reverse_lanes_u64(v0, lane), r1 = reverse_lanes_u64(v1, lane);
   t0 = t0 > r1 ? t0 : r1;
   t1 = t1 > r0 ? t1 : r0;
   if (t0 < t1) {
@@ -487,9 +559,28 @@ __device__ __forceinline__ double lane_group_sum_f64(double x) {
   return x;
 }
 
+// Words handed from block to block inside one launch of the decode step.  The
+// receiver takes a word that is all zero bits as not written yet, and writes
+// it back to zero once it has read it, so that the words are zero again
+// between calls; the sender stores +0.0 as -0.0.  No flag or count goes with
+// the data: a flag has to wait until the stores before it are done (1-2 us
+// across the chip), a receiver's poll costs nothing beyond the load itself.
+__device__ __forceinline__ void hand_f64(double* p, double v) {
+  if (__double_as_longlong(v) == 0) v = -0.0;
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint32_t hand_bits(float v) {
+  const uint32_t b = __float_as_uint(v);
+  return b ? b : 0x80000000u;
+}
+__device__ __forceinline__ void hand_f32x2(float* p, float a, float b) {
+  __hip_atomic_store(reinterpret_cast<uint64_t*>(p), (uint64_t)hand_bits(b) << 32 | hand_bits(a), __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ bool handed_f32x2(uint64_t v) { return (uint32_t)v != 0 && (uint32_t)(v >> 32) != 0; }
+
 // The logits of units u0 .. u0 + 31 (those below u_end): maxima per head into
-// mx, each logit stored once (kShared: with device-scope stores, for another
-// block of the same launch to read).
+// mx, each logit stored once (kShared: handed to another block of the launch).
 template <int G, bool kShared>
 __device__ __forceinline__ void wave_unit_logits(const double (&qd)[G][LogitLayout<G>::kDims],
                                                  const float* __restrict__ rs, int u0, int u_end, double scale,
@@ -522,7 +613,7 @@ __device__ __forceinline__ void wave_unit_logits(const double (&qd)[G][LogitLayo
         mx[j] = fmax(mx[j], a);
         if (sub == j) {
           if constexpr (kShared)
-            __hip_atomic_store(lg + (size_t)u * G + j, a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            hand_f64(lg + (size_t)u * G + j, a);
           else
             lg[(size_t)u * G + j] = a;
         }
@@ -594,16 +685,25 @@ __device__ __forceinline__ double load_logit(const double* p) {
 //  pool-row list.  kShared: the logits come from other blocks of the launch;
 //  they are read coherently and the exponentials are recomputed in pass 3
 //  instead of written back (the results are the same, bit for bit).
-//  kPublish: the row list and its length are read by other blocks of the
-//  launch, so they are written with device-scope stores.
-template <int G, bool kShared, bool kPublish = false, int NT = kSelThreads>
-__device__ __forceinline__ void select_after_max(double* __restrict__ lg, const double* s_m, int n_units, int n_pad,
+//  kHanded (the one-launch decode step): the logits are still on their way
+//  from the other blocks of the slice, so the block polls for them and takes
+//  their maxima itself; the rows and their number go to the slice's blocks
+//  through `hand` as well as to the outputs.
+struct SelectHand {
+  int32_t* rows;      // [budget]: row + 1
+  int32_t* n_sel;     // one word per block of the slice: n_sel + 1
+  int n_blk, spin_limit;
+  int32_t* status;
+};
+
+template <int G, bool kShared, bool kHanded = false, int NT = kSelThreads>
+__device__ __forceinline__ void select_after_max(double* __restrict__ lg, double* s_m, int n_units, int n_pad,
                                                  int64_t s, int64_t ps, int units_cap, int budget,
                                                  const int32_t* __restrict__ unit_start,
                                                  int32_t* __restrict__ sel_units, int32_t* __restrict__ n_sel_units,
                                                  int32_t* __restrict__ n_sel, int32_t* __restrict__ row_ws,
                                                  double* __restrict__ scores_out, uint64_t* s_key, int* s_size,
-                                                 int* s_incl) {
+                                                 int* s_incl, const SelectHand hand = {}) {
   constexpr int NW = NT / 64;
   static_assert(kSumThreads % NT == 0 && NT >= 128, "block size");
   __shared__ double s_rz[G][kSumThreads / 64];
@@ -638,12 +738,90 @@ __device__ __forceinline__ void select_after_max(double* __restrict__ lg, const 
   for (int k = 0; k < NV; ++k)
 #pragma unroll
     for (int j = 0; j < G; ++j) zs[k][j] = 0.0;
+  if constexpr (kHanded) {
+    // every logit of the slice, as soon as it is there, and the maxima
+    __shared__ double s_rm[G][NW];
+    double mx[G];
+#pragma unroll
+    for (int j = 0; j < G; ++j) mx[j] = -__builtin_inf();
+    int polls = 0;
+    if (in_regs) {
+      // the last head's words first: a poll is then one load a unit
+      for (bool all = false; !all;) {
+        bool got = true;
+#pragma unroll
+        for (int r = 0; r < kRegUnits; ++r) {
+          const int u = tid + (r / RV) * NT + (r % RV) * kSumThreads;
+          if (u < n_units) got = got && __double_as_longlong(load_logit<true>(lg + (size_t)u * G + G - 1)) != 0;
+        }
+        all = __builtin_amdgcn_ballot_w64(!got) == 0 || ++polls >= hand.spin_limit;
+      }
+      for (bool all = false; !all;) {
+        bool got = true;
+#pragma unroll
+        for (int r = 0; r < kRegUnits; ++r) {
+          const int u = tid + (r / RV) * NT + (r % RV) * kSumThreads;
+#pragma unroll
+          for (int j = 0; j < G; ++j) ev[r][j] = u < n_units ? load_logit<true>(lg + (size_t)u * G + j) : 1.0;
+        }
+#pragma unroll
+        for (int r = 0; r < kRegUnits; ++r)
+#pragma unroll
+          for (int j = 0; j < G; ++j) got = got && __double_as_longlong(ev[r][j]) != 0;
+        all = __builtin_amdgcn_ballot_w64(!got) == 0 || ++polls >= hand.spin_limit;
+      }
+#pragma unroll
+      for (int r = 0; r < kRegUnits; ++r) {
+        const int u = tid + (r / RV) * NT + (r % RV) * kSumThreads;
+        if (u < n_units) {
+#pragma unroll
+          for (int j = 0; j < G; ++j) {
+            mx[j] = fmax(mx[j], ev[r][j]);
+            __hip_atomic_store(lg + (size_t)u * G + j, 0.0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          }
+        }
+      }
+    } else {
+      for (int u0 = 0; u0 < n_units; u0 += NT) {   // uniform trips: the polls are wave-uniform
+        const int u = u0 + tid;
+        double x[G];
+        for (bool all = false; !all;) {
+          bool got = true;
+#pragma unroll
+          for (int j = 0; j < G; ++j) x[j] = u < n_units ? load_logit<true>(lg + (size_t)u * G + j) : 1.0;
+#pragma unroll
+          for (int j = 0; j < G; ++j) got = got && __double_as_longlong(x[j]) != 0;
+          all = __builtin_amdgcn_ballot_w64(!got) == 0 || ++polls >= hand.spin_limit;
+        }
+        if (u < n_units) {
+#pragma unroll
+          for (int j = 0; j < G; ++j) mx[j] = fmax(mx[j], x[j]);
+        }
+      }
+    }
+    if (polls >= hand.spin_limit && lane == 0)
+      __hip_atomic_store(hand.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+    for (int j = 0; j < G; ++j) {
+      const double m = lane_max_f64(mx[j], lane);
+      if (lane == 0) s_rm[j][w] = m;
+    }
+    __syncthreads();
+    if (tid < G) {
+      double m = s_rm[tid][0];
+      for (int q2 = 1; q2 < NW; ++q2) m = fmax(m, s_rm[tid][q2]);
+      s_m[tid] = m;
+    }
+    __syncthreads();
+  }
   if (in_regs) {
+    if constexpr (!kHanded) {
 #pragma unroll
-    for (int r = 0; r < kRegUnits; ++r) {
-      const int u = tid + (r / RV) * NT + (r % RV) * kSumThreads;
+      for (int r = 0; r < kRegUnits; ++r) {
+        const int u = tid + (r / RV) * NT + (r % RV) * kSumThreads;
 #pragma unroll
-      for (int j = 0; j < G; ++j) ev[r][j] = u < n_units ? load_logit<kShared>(lg + (size_t)u * G + j) : 0.0;
+        for (int j = 0; j < G; ++j) ev[r][j] = u < n_units ? load_logit<kShared>(lg + (size_t)u * G + j) : 0.0;
+      }
     }
 #pragma unroll
     for (int r = 0; r < kRegUnits; ++r) {
@@ -675,7 +853,7 @@ __device__ __forceinline__ void select_after_max(double* __restrict__ lg, const 
   for (int k = 0; k < NV; ++k)
 #pragma unroll
     for (int j = 0; j < G; ++j) {
-      const double z = wave_sum(zs[k][j]);
+      const double z = lane_sum_f64(zs[k][j], lane);
       if (lane == 0) s_rz[j][w + k * NW] = z;
     }
 #pragma unroll
@@ -720,6 +898,11 @@ __device__ __forceinline__ void select_after_max(double* __restrict__ lg, const 
 #pragma unroll
         for (int j = 0; j < G; ++j)
           a += (kShared ? exp(load_logit<kShared>(lg + (size_t)u * G + j) - s_m[j]) : lg[(size_t)u * G + j]) / s_z[j];
+        if constexpr (kHanded) {
+#pragma unroll
+          for (int j = 0; j < G; ++j)
+            __hip_atomic_store(lg + (size_t)u * G + j, 0.0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
         a /= (double)G;
         key = unit_key(a, u);
         if (scores_out) scores_out[(size_t)s * units_cap + u] = a;
@@ -732,8 +915,8 @@ __device__ __forceinline__ void select_after_max(double* __restrict__ lg, const 
   // The prefix stop (Section 3.1 budget; units taken in rank order until the
   // next one does not fit), first over the 128 highest keys: each wave sorts
   // its 128-key chunks of s_key in registers and keeps the 128 largest keys
-  // it has seen (merge_top128), wave 0 merges the waves' lists, takes their
-  // inclusive size sums and finds where the budget stops the prefix.  If it
+  // it has seen (merge_top128), the waves' lists merge in pairs, wave 0 takes
+  // their inclusive size sums and finds where the budget stops the prefix.  If it
   // stops inside those 128, or every unit fits, that is the selection (the
   // same units in the same order as the full search below); otherwise the
   // search below runs.  Tried when the budget holds fewer than kTopTry units
@@ -764,10 +947,21 @@ __device__ __forceinline__ void select_after_max(double* __restrict__ lg, const 
       s_top[w][lane] = t0;
       s_top[w][kWave + lane] = t1;
     }
+    // the waves' lists merge in pairs (one wave merging all eight in turn took
+    // longer than the sorts)
     __syncthreads();
+#pragma unroll
+    for (int o = 1; o < NW; o *= 2) {
+      if (w % (2 * o) == 0 && (w + o) * 2 * kWave < n_pad) {
+        uint64_t t0 = s_top[w][lane], t1 = s_top[w][kWave + lane];
+        merge_top128(t0, t1, s_top[w + o][lane], s_top[w + o][kWave + lane], lane);
+        s_top[w][lane] = t0;
+        s_top[w][kWave + lane] = t1;
+      }
+      __syncthreads();
+    }
     if (w == 0) {
-      uint64_t t0 = s_top[0][lane], t1 = s_top[0][kWave + lane];
-      for (int q2 = 1; q2 < NW; ++q2) merge_top128(t0, t1, s_top[q2][lane], s_top[q2][kWave + lane], lane);
+      const uint64_t t0 = s_top[0][lane], t1 = s_top[0][kWave + lane];
       const int n_real = min(2 * kWave, n_units);   // the list's real keys (the rest are padding zeros)
       const int i0 = lane, i1 = kWave + lane;
       const int z0 = i0 < n_real ? s_size[key_unit(t0)] : 0;
@@ -793,16 +987,19 @@ __device__ __forceinline__ void select_after_max(double* __restrict__ lg, const 
       const uint64_t kb = ntake < kWave ? k0 : k1;
       const bool fast = ntake < n_real ? kb != 0 : n_real == n_units;
       if (fast) {
+        // the starts, read before the sums take their place (one wave's LDS
+        // operations are in order)
+        const int u0 = i0 < ntake ? key_unit(t0) : 0, u1 = i1 < ntake ? key_unit(t1) : 0;
+        const uint32_t st0 = (uint32_t)s_incl[u0], st1 = (uint32_t)s_incl[u1];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         if (i0 < ntake) {
-          const int u = key_unit(t0);
-          sel_units[(size_t)s * units_cap + i0] = u;
-          s_key[i0] = ((uint64_t)(uint32_t)ustart[u] << 32) | (uint32_t)z0;
+          sel_units[(size_t)s * units_cap + i0] = u0;
+          s_key[i0] = ((uint64_t)st0 << 32) | (uint32_t)z0;
           s_incl[i0] = inc0 > 0x3fffffff ? 0x3fffffff : (int)inc0;
         }
         if (i1 < ntake) {
-          const int u = key_unit(t1);
-          sel_units[(size_t)s * units_cap + i1] = u;
-          s_key[i1] = ((uint64_t)(uint32_t)ustart[u] << 32) | (uint32_t)z1;
+          sel_units[(size_t)s * units_cap + i1] = u1;
+          s_key[i1] = ((uint64_t)st1 << 32) | (uint32_t)z1;
           s_incl[i1] = inc1 > 0x3fffffff ? 0x3fffffff : (int)inc1;
         }
       }
@@ -1041,6 +1238,10 @@ __device__ __forceinline__ void select_after_max(double* __restrict__ lg, const 
   __syncthreads();
   const int ntake = s_ntake;
   const int nsel = ntake > 0 ? s_incl[ntake - 1] : 0;
+  if constexpr (kHanded) {
+    if (tid < hand.n_blk)
+      __hip_atomic_store(hand.n_sel + tid, nsel + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
   // one wave per selected unit: its rows in order
   for (int p = w; p < ntake; p += NW) {
     const uint64_t e = s_key[p];
@@ -1048,18 +1249,14 @@ __device__ __forceinline__ void select_after_max(double* __restrict__ lg, const 
     const int st0 = (int)(uint32_t)(e >> 32);
     const int ex = s_incl[p] - sz;
     for (int i = lane; i < sz; i += kWave) {
-      if constexpr (kPublish)
-        __hip_atomic_store(rows + ex + i, st0 + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      else
-        rows[ex + i] = st0 + i;
+      if constexpr (kHanded)
+        __hip_atomic_store(hand.rows + ex + i, max(st0 + i, 0) + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      rows[ex + i] = st0 + i;
     }
   }
   if (tid == 0) {
     n_sel_units[s] = ntake;
-    if constexpr (kPublish)
-      __hip_atomic_store(n_sel + s, nsel, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    else
-      n_sel[s] = nsel;
+    n_sel[s] = nsel;
   }
 }
 
@@ -1109,7 +1306,11 @@ void score_select_kernel(const T* __restrict__ q, int n_kv_heads, double scale, 
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int32_t* us = unit_size + (size_t)ps * units_cap;
-  for (int u = tid; u < n_units; u += NT) s_size[u] = max(us[u], 0);
+  const int32_t* ust = unit_start + (size_t)ps * units_cap;
+  for (int u = tid; u < n_units; u += NT) {
+    s_size[u] = max(us[u], 0);
+    s_incl[u] = ust[u];
+  }
 
   // pass 1: maxima of the logits, computed here (own_logits: many slices,
   // one block each) or read back from unit_logits_kernel (few slices)
@@ -1154,9 +1355,9 @@ void score_select_kernel(const T* __restrict__ q, int n_kv_heads, double scale, 
 // counter (`counter`), and the last part to arrive resets it, loads every part's maxima
 // and the unit sizes and makes the selection (select_after_max, the same
 // code as the per-stage kernel, so scores and selections are equal bit for
-// bit).  Returns true in the block that made the selection.
-template <class T, int G, bool kPublish>
-__device__ __forceinline__ bool select_part(const T* __restrict__ q, int n_kv_heads, int64_t s, int part, int n_parts,
+// bit).
+template <class T, int G>
+__device__ __forceinline__ void select_part(const T* __restrict__ q, int n_kv_heads, int64_t s, int part, int n_parts,
                                             double scale, const float* __restrict__ reps, int units_cap, int n_units,
                                             int n_pad, int budget, const int32_t* __restrict__ unit_start,
                                             const int32_t* __restrict__ unit_size, int32_t* __restrict__ sel_units,
@@ -1211,14 +1412,18 @@ __device__ __forceinline__ bool select_part(const T* __restrict__ q, int n_kv_he
     if (s_last) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   __syncthreads();
-  if (!s_last) return false;
+  if (!s_last) return;
   // the parts' maxima (one coherent load per thread, all in flight) and the unit sizes
   __shared__ double s_pmax[kMaxSelectParts * kMaxGroupSize];
   if (tid < n_parts * G)
     s_pmax[tid] = __hip_atomic_load(part_max + (size_t)s * n_parts * G + tid, __ATOMIC_RELAXED,
                                     __HIP_MEMORY_SCOPE_AGENT);
   const int32_t* us = unit_size + (size_t)s * units_cap;
-  for (int u = tid; u < n_units; u += kSelThreads) s_size[u] = max(us[u], 0);
+  const int32_t* ust = unit_start + (size_t)s * units_cap;
+  for (int u = tid; u < n_units; u += kSelThreads) {
+    s_size[u] = max(us[u], 0);
+    s_incl[u] = ust[u];
+  }
   __syncthreads();
   if (tid < G) {
     double m = -__builtin_inf();
@@ -1226,9 +1431,55 @@ __device__ __forceinline__ bool select_part(const T* __restrict__ q, int n_kv_he
     s_m[tid] = m;
   }
   __syncthreads();
-  select_after_max<G, true, kPublish>(lg, s_m, n_units, n_pad, s, s, units_cap, budget, unit_start, sel_units,
-                                      n_sel_units, n_sel, sel_rows, scores_out, s_key, s_size, s_incl);
-  return true;
+  select_after_max<G, true>(lg, s_m, n_units, n_pad, s, s, units_cap, budget, unit_start, sel_units, n_sel_units,
+                            n_sel, sel_rows, scores_out, s_key, s_size, s_incl);
+}
+
+// The same in the one-launch decode step: every block of the slice hands the
+// logits of its part over (hand_f64), the selector makes the selection from
+// them as they arrive and hands the rows over.
+template <class T, int G>
+__device__ __forceinline__ void select_handed(const T* __restrict__ q, int n_kv_heads, int64_t s, int part, int n_parts,
+                                              bool selector, double scale, const float* __restrict__ reps,
+                                              int units_cap, int n_units, int n_pad, int budget,
+                                              const int32_t* __restrict__ unit_start,
+                                              const int32_t* __restrict__ unit_size, int32_t* __restrict__ sel_units,
+                                              int32_t* __restrict__ n_sel_units, int32_t* __restrict__ n_sel,
+                                              int32_t* __restrict__ sel_rows, double* __restrict__ scores_out,
+                                              double* __restrict__ logit_ws, char* smem, const SelectHand& hand) {
+  uint64_t* s_key = reinterpret_cast<uint64_t*>(smem);            // [n_pad]
+  int* s_size = reinterpret_cast<int*>(s_key + n_pad);            // [n_pad] unit sizes by unit id
+  int* s_incl = s_size + n_pad;                                    // [n_pad] inclusive size sums by rank
+  __shared__ double s_m[G];
+  const int64_t grp = s / n_kv_heads;
+  const int kvh = (int)(s - grp * n_kv_heads);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int per = (n_units + n_parts - 1) / n_parts;
+  const int u_begin = part * per, u_end = min(n_units, u_begin + per);
+  double* lg = logit_ws + (size_t)s * units_cap * G;
+  if (selector) {
+    const int32_t* us = unit_size + (size_t)s * units_cap;
+    const int32_t* ust = unit_start + (size_t)s * units_cap;
+    for (int u = tid; u < n_units; u += kSelThreads) {
+      s_size[u] = max(us[u], 0);
+      s_incl[u] = ust[u];
+    }
+  }
+  if (u_begin < u_end) {
+    double mx[G];   // unused: the selector takes the maxima
+#pragma unroll
+    for (int j = 0; j < G; ++j) mx[j] = -__builtin_inf();
+    double qd[G][LogitLayout<G>::kDims];
+    load_q_f64<G>(q, (size_t)grp * n_kv_heads * G + (size_t)kvh * G, lane, qd);
+    const float* rs = reps + (size_t)s * units_cap * kHeadDim;
+    for (int u0 = u_begin + w * kLogitUnitsPerIter; u0 < u_end; u0 += kSelWaves * kLogitUnitsPerIter)
+      wave_unit_logits<G, true>(qd, rs, u0, u_end, scale, lg, mx, lane);
+  }
+  if (!selector) return;
+  __syncthreads();
+  select_after_max<G, true, true>(lg, s_m, n_units, n_pad, s, s, units_cap, budget, unit_start, sel_units,
+                                  n_sel_units, n_sel, sel_rows, scores_out, s_key, s_size, s_incl, hand);
 }
 
 // The first launch of a two-launch decode step (fixed segments): one
@@ -1272,7 +1523,7 @@ void step_select_kernel(const T* __restrict__ q, const T* __restrict__ q_ref, in
     store_slice(k_new, v_new, k_local, v_local, window, step, seg_len, evict_seg, reps, unit_start, unit_size,
                 units_cap, n_clusters, k_pool, v_pool, pool_rows, prompt_len, s, lane);
   if (!fire) return;
-  select_part<T, G, false>(q, n_kv_heads, s, part, n_parts, scale, reps, units_cap, n_units, n_pad, budget,
+  select_part<T, G>(q, n_kv_heads, s, part, n_parts, scale, reps, units_cap, n_units, n_pad, budget,
                            unit_start, unit_size, sel_units, n_sel_units, n_sel, sel_rows, scores_out, logit_ws,
                            part_max, counter + s, smem);
 }
@@ -1888,7 +2139,7 @@ __device__ __forceinline__ void update_q_ref(const StepSync& sync, const T* __re
 // accumulators kMergeBatch chunks at a time, all loads of a batch in flight.
 constexpr int kMergeBatch = 32;
 
-template <int G, bool kOneTrip = false>
+template <int G>
 __device__ __forceinline__ bool attn_last_block_merge(const float* __restrict__ part, int32_t* __restrict__ counter,
                                                       int64_t s, int n_chunks, void* __restrict__ out, int out_bf16,
                                                       float* __restrict__ lse_out, int tid, int n_threads,
@@ -1905,57 +2156,9 @@ __device__ __forceinline__ bool attn_last_block_merge(const float* __restrict__ 
   if (!s_last) return false;
   constexpr size_t pstride = 2 + kHeadDim;
   const float* ps = part + (size_t)s * n_chunks * G * pstride;
-  if (kOneTrip && n_chunks <= kMergeBatch) {
-    // every chunk's (m, l) and accumulators of a thread's head and two dims
-    // loaded at once: one round trip, the same arithmetic as below
-    for (int i = tid; i < G * (kHeadDim / 2); i += n_threads) {
-      const int j = i / (kHeadDim / 2), lane = i % (kHeadDim / 2);
-      const uint64_t* pm = reinterpret_cast<const uint64_t*>(ps + (size_t)j * pstride);
-      const uint64_t* pa = reinterpret_cast<const uint64_t*>(ps + (size_t)j * pstride + 2) + lane;
-      uint64_t mlv[kMergeBatch], v[kMergeBatch];
-#pragma unroll
-      for (int c = 0; c < kMergeBatch; ++c) {
-        mlv[c] = c < n_chunks ? __hip_atomic_load(pm + (size_t)c * G * (pstride / 2), __ATOMIC_RELAXED,
-                                                  __HIP_MEMORY_SCOPE_AGENT)
-                              : 0;
-        v[c] = c < n_chunks ? __hip_atomic_load(pa + (size_t)c * G * (pstride / 2), __ATOMIC_RELAXED,
-                                                __HIP_MEMORY_SCOPE_AGENT)
-                            : 0;
-      }
-      float mm = -__builtin_inff();
-#pragma unroll
-      for (int c = 0; c < kMergeBatch; ++c)
-        if (c < n_chunks) mm = fmaxf(mm, __uint_as_float((uint32_t)mlv[c]));
-      float ll = 0.f, a0 = 0.f, a1 = 0.f;
-      if (mm != -__builtin_inff()) {
-#pragma unroll
-        for (int c = 0; c < kMergeBatch; ++c) {
-          if (c < n_chunks) {
-            const float w = __builtin_amdgcn_exp2f(__uint_as_float((uint32_t)mlv[c]) - mm);
-            ll += __uint_as_float((uint32_t)(mlv[c] >> 32)) * w;
-            a0 += __uint_as_float((uint32_t)v[c]) * w;
-            a1 += __uint_as_float((uint32_t)(v[c] >> 32)) * w;
-          }
-        }
-      }
-      const float inv = ll > 0.f ? 1.f / ll : 0.f;
-      const size_t row = (size_t)s * G + j;
-      if (out_bf16) {
-        uint16_t* o = static_cast<uint16_t*>(out) + row * kHeadDim;
-        store_from_f32(o, 2 * lane, a0 * inv);
-        store_from_f32(o, 2 * lane + 1, a1 * inv);
-      } else {
-        float* o = static_cast<float*>(out) + row * kHeadDim;
-        store_from_f32(o, 2 * lane, a0 * inv);
-        store_from_f32(o, 2 * lane + 1, a1 * inv);
-      }
-      if (lse_out && lane == 0) lse_out[row] = ll > 0.f ? 0.6931471805599453f * (mm + log2f(ll)) : -__builtin_inff();
-    }
-    return true;
-  }
   for (int i = tid; i < n_chunks * G; i += n_threads) {
-    const uint64_t v = __hip_atomic_load(reinterpret_cast<const uint64_t*>(ps + (size_t)i * pstride),
-                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint64_t v = __hip_atomic_load(reinterpret_cast<const uint64_t*>(ps + (size_t)i * pstride), __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
     s_ml[i] = make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32)));
   }
   __syncthreads();
@@ -2007,7 +2210,7 @@ __device__ __forceinline__ bool attn_last_block_merge(const float* __restrict__ 
 // (m, l, acc[128]) per head for attn_combine_kernel, or, with `counter` (the
 // slice's arrival counter), for the in-kernel merge.  True when this block
 // wrote the slice's output (one chunk, or the last block of an in-kernel merge).
-template <int G, int NW, bool kOneTrip = false>
+template <int G, int NW>
 __device__ __forceinline__ bool attn_block_merge(const float (*s_m)[G], const float (*s_l)[G],
                                                  const float (*s_acc)[G][kHeadDim], int tid, int64_t s, int chunk,
                                                  int n_chunks, float* __restrict__ part, void* __restrict__ out,
@@ -2054,8 +2257,164 @@ __device__ __forceinline__ bool attn_block_merge(const float (*s_m)[G], const fl
   }
   if (n_chunks == 1) return true;
   if (counter)
-    return attn_last_block_merge<G, kOneTrip>(part, counter, s, n_chunks, out, out_bf16, lse_out, tid, NW * 64, s_ml);
+    return attn_last_block_merge<G>(part, counter, s, n_chunks, out, out_bf16, lse_out, tid, NW * 64, s_ml);
   return false;
+}
+
+// Output dims 2d, 2d + 1 of head j (pair i = 64 j + d) from the softmax state.
+template <int G>
+__device__ __forceinline__ void store_pair(void* __restrict__ out, int out_bf16, float* __restrict__ lse_out, int64_t s,
+                                           int i, float mm, float ll, float a0, float a1) {
+  const int j = i / (kHeadDim / 2), d = i % (kHeadDim / 2);
+  const float inv = ll > 0.f ? 1.f / ll : 0.f;
+  const size_t row = (size_t)s * G + j;
+  if (out_bf16) {
+    const uint32_t lo = f32_to_bf16(a0 * inv), hi = f32_to_bf16(a1 * inv);
+    reinterpret_cast<uint32_t*>(static_cast<uint16_t*>(out) + row * kHeadDim)[d] = lo | hi << 16;
+  } else {
+    reinterpret_cast<float2*>(static_cast<float*>(out) + row * kHeadDim)[d] = make_float2(a0 * inv, a1 * inv);
+  }
+  if (lse_out && d == 0) lse_out[row] = ll > 0.f ? 0.6931471805599453f * (mm + log2f(ll)) : -__builtin_inff();
+}
+
+// The same at the end of the one-launch decode step, in two parts: every block
+// hands its result per head and pair of dims (two accumulators, m, l) to the
+// block that merges the pair (attn_hand), and merges its own share of the
+// pairs, P of them, chunks in order (attn_merge_share).  A thread waits for
+// one chunk's words of one pair at a time, the block's threads split over the
+// chunks (up to a power of two) and as many pairs as that leaves.  (A step of
+// one layer: 18.2 us with partials counted in and merged by the slice's last
+// block; 20.7 with one block merging the words as they arrive; 15.2 with the
+// shares spread.)
+template <int G, int NW>
+__device__ __forceinline__ void attn_hand(const float (*s_m)[G], const float (*s_l)[G],
+                                          const float (*s_acc)[G][kHeadDim], int tid, int64_t s, int chunk,
+                                          int n_chunks, float* __restrict__ part, void* __restrict__ out, int out_bf16,
+                                          float* __restrict__ lse_out) {
+  constexpr int kPairs = G * (kHeadDim / 2);
+  float* ps = part + (size_t)s * n_chunks * kPairs * 4;   // [chunk][pair][a0, a1, m, l]
+  for (int i = tid; i < kPairs; i += NW * 64) {
+    const int j = i / (kHeadDim / 2), d = i % (kHeadDim / 2);
+    float mm = -__builtin_inff();
+#pragma unroll
+    for (int q2 = 0; q2 < NW; ++q2) mm = fmaxf(mm, s_m[q2][j]);
+    float ll = 0.f, a0 = 0.f, a1 = 0.f;
+    if (mm != -__builtin_inff()) {
+#pragma unroll
+      for (int q2 = 0; q2 < NW; ++q2) {
+        const float c = __builtin_amdgcn_exp2f(s_m[q2][j] - mm);
+        const float2 x = *reinterpret_cast<const float2*>(&s_acc[q2][j][2 * d]);
+        ll += s_l[q2][j] * c;
+        a0 += x.x * c;
+        a1 += x.y * c;
+      }
+    }
+    if (n_chunks == 1) {
+      store_pair<G>(out, out_bf16, lse_out, s, i, mm, ll, a0, a1);
+    } else {
+      float* mine = ps + ((size_t)chunk * kPairs + i) * 4;
+      hand_f32x2(mine, a0, a1);
+      hand_f32x2(mine + 2, mm, ll);
+    }
+  }
+}
+
+// One block's share (that of block `chunk` unless a block leaves it to another)
+// of a slice's pairs.  With `met` (the slice's 64-bit word of arrivals) the
+// blocks of the slice may not all have started, and this one may be what the
+// others wait for to get a compute unit: so after kStepPatience polls it asks
+// the word.  All started: it goes on waiting, for words that are then sure to
+// come.  Otherwise it leaves its bit there for the last block to start, which
+// merges its share, and returns.  s_late: zero, a barrier before this call.
+// Returns the polls, for the caller's bound.
+constexpr int kStepPatience = 64;
+
+template <int G, int NW>
+__device__ __forceinline__ int attn_merge_share(int tid, int64_t s, int chunk, int n_chunks, float* __restrict__ part,
+                                                void* __restrict__ out, int out_bf16, float* __restrict__ lse_out,
+                                                int spin_limit, uint64_t* met, int patience, int* s_late,
+                                                float4* s_hand) {
+  constexpr int kPairs = G * (kHeadDim / 2);
+  float* ps = part + (size_t)s * n_chunks * kPairs * 4;
+  int at_once = NW * 64, P = kPairs;                       // pairs merged at once; the share's pairs
+  for (int n = 1; n < n_chunks; n *= 2) {
+    at_once /= 2;
+    if ((P / 2) * n_chunks >= kPairs) P /= 2;
+  }
+  const int c = tid / at_once, pr = tid % at_once, lane = tid & 63;
+  int polls = 0;
+  for (int r = 0; r < P; r += at_once) {
+    const int i0 = chunk * P + r;                          // pairs i0 .. of this round
+    if (i0 >= kPairs) {                                    // block-uniform
+      if (r == 0) __syncthreads();                         // the caller counts on one
+      break;
+    }
+    const int n_pairs = min(min(at_once, P - r), kPairs - i0);
+    const bool mine = c < n_chunks && pr < n_pairs;
+    uint64_t* w = reinterpret_cast<uint64_t*>(ps + ((size_t)(mine ? c : 0) * kPairs + i0 + (mine ? pr : 0)) * 4);
+    uint64_t x = 0, y = 0;
+    auto collect = [&](int limit) -> bool {                // until the wave's words are there
+      for (int n = 0;;) {
+        if (mine) {
+          x = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          y = __hip_atomic_load(w + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        const bool got = !mine || (handed_f32x2(x) && handed_f32x2(y));
+        if (__builtin_amdgcn_ballot_w64(!got) == 0) return true;
+        polls = max(polls, ++n);
+        if (n >= limit) return false;
+      }
+    };
+    auto stage = [&]() {
+      s_hand[tid] = make_float4(__uint_as_float((uint32_t)x), __uint_as_float((uint32_t)(x >> 32)),
+                                __uint_as_float((uint32_t)y), __uint_as_float((uint32_t)(y >> 32)));
+    };
+    const bool ask = met && r == 0;                        // later rounds: every block has handed words
+    const bool all = collect(ask ? patience : spin_limit);
+    if (ask && !all && lane == 0) *s_late = 1;
+    if (r > 0) __syncthreads();                            // the last round's sums are done
+    stage();
+    __syncthreads();
+    if (ask && *s_late) {                                  // block-uniform
+      __syncthreads();
+      if (tid == (NW - 2) * 64) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this block's own arrival is counted
+        const uint64_t bit = 1ull << chunk;
+        const int n = (int)(__hip_atomic_fetch_or(met, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 32);
+        const bool leave = n > 0 && n < n_chunks;          // zero again: counted to the end and reset
+        if (!leave) __hip_atomic_fetch_and(met, ~bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *s_late = leave ? 2 : 1;
+      }
+      __syncthreads();
+      if (*s_late == 2) return 0;
+      polls = 0;
+      collect(spin_limit);
+      stage();
+      __syncthreads();
+    } else if (ask) {
+      polls = 0;
+    }
+    if (mine) {
+      __hip_atomic_store(w, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(w + 1, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (tid < n_pairs) {
+      float mm = -__builtin_inff();
+      for (int q = 0; q < n_chunks; ++q) mm = fmaxf(mm, s_hand[q * at_once + tid].z);
+      float ll = 0.f, a0 = 0.f, a1 = 0.f;
+      if (mm != -__builtin_inff()) {
+        for (int q = 0; q < n_chunks; ++q) {
+          const float4 h = s_hand[q * at_once + tid];
+          const float e = __builtin_amdgcn_exp2f(h.z - mm);
+          ll += h.w * e;
+          a0 += h.x * e;
+          a1 += h.y * e;
+        }
+      }
+      store_pair<G>(out, out_bf16, lse_out, s, i0 + tid, mm, ll, a0, a1);
+    }
+  }
+  return polls;
 }
 
 // With boundary-delimited segments the window of slice s holds the tokens
@@ -2341,29 +2700,34 @@ __device__ __forceinline__ void attn_mfma_tile(const attn_bf16x8 (&qa)[NM][4], c
 }
 
 // A wave's totals into its LDS slot: l over the 16 row positions, acc over
-// the 4 lane groups (m is wave-uniform).
+// the 4 lane groups (m is wave-uniform).  Four accumulators at a time: two
+// 16-lane swaps and one 32-lane swap, each with an add, leave lane row r with
+// the sum of accumulator r, so a head's eight take six swaps and six adds on
+// the vector ALU where ds_bpermute took sixteen trips through the LDS pipe
+// that all waves share (with the same swaps in the selection, a decode step of
+// 256 slices: 64.4 -> 63.0 us).
 template <int G>
 __device__ __forceinline__ void attn_wave_to_lds(const float (&m)[G], float (&l)[G], float (&acc)[G][8], float* s_mw,
                                                  float* s_lw, float (*s_accw)[kHeadDim], int lane) {
+  auto pair16 = [](float x, float y) {   // rows x0+x1, y0+y1, x2+x3, y2+y3
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  };
+  auto pair32 = [](float x, float y) {   // rows x0+x2, x1+x3, y0+y2, y1+y3
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  };
 #pragma unroll
   for (int j = 0; j < G; ++j) {
     l[j] = row16_sum(l[j]);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      acc[j][e] += __shfl_xor(acc[j][e], 16, kWave);
-      acc[j][e] += __shfl_xor(acc[j][e], 32, kWave);
+    if (lane == 0) {
+      s_mw[j] = m[j];
+      s_lw[j] = l[j];
     }
-  }
-  if (lane < 16) {
 #pragma unroll
-    for (int j = 0; j < G; ++j) {
-      if (lane == 0) {
-        s_mw[j] = m[j];
-        s_lw[j] = l[j];
-      }
-#pragma unroll
-      for (int e = 0; e < 8; ++e) s_accw[j][8 * lane + e] = acc[j][e];
-    }
+    for (int e = 0; e < 8; e += 4)
+      s_accw[j][8 * (lane & 15) + e + (lane >> 4)] =
+          pair32(pair16(acc[j][e], acc[j][e + 1]), pair16(acc[j][e + 2], acc[j][e + 3]));
   }
 }
 
@@ -2470,36 +2834,50 @@ void attn_mfma_kernel(const uint16_t* __restrict__ q, int n_kv_heads, float scal
 // the group) while it loads its chunk's entries of the row list of the last
 // fire, the list length and its Q operand; block 0 runs the fixed-segment
 // store.  If the group fired, the block computes the logits of its part of
-// the units and counts itself in (select_part): the last block to arrive
-// makes the selection, writes the row list with device-scope stores and
-// raises the slice's ready flag; the others wait for the flag and read the
-// new list entries coherently.  Only blocks that have arrived wait, and they
-// wait for the last arrival, which is running and waits for nothing; so the
-// wait ends once every block of the slice has started, which holds when the
-// whole grid is resident at once (the launch gives the chip at most one
-// block per compute unit) and also when it is not, since workgroups are
-// dispatched in index order and a slice's blocks are consecutive.  The wait
-// is bounded all the same: past spin_limit polls (kStepSpinLimit, or fewer
-// from LOUISKV_STEP_SPIN_LIMIT, for tests of this path) a block records a
-// time-out in the status word and goes on; its row-list entries are clamped
-// into the pool, so that such a step reads no memory out of bounds.  Then the block attends its chunk of the slice's row sequence (the
-// selected rows, padded to the budget, then the window rows), two 16-row
-// tiles per wave in flight; the newest window row is read from k_new/v_new,
-// since the store of the same launch may not have reached the ring yet.  The
-// last block of a slice to finish merges the chunk partials, and lowers the
-// ready flag after a fire.
+// the units and hands them to the slice's last block, which makes the
+// selection as they arrive and hands every block the list length and its rows
+// (select_handed).  Then the block attends its chunk of the slice's row
+// sequence (the selected rows, padded to the budget, then the window rows),
+// two 16-row tiles per wave in flight; the newest window row is read from
+// k_new/v_new, since the store of the same launch may not have reached the
+// ring yet.  The slice's blocks hand each other their partial results, and
+// every block merges a share of the slice's outputs (attn_hand_merge).
 //
-// Every block counts itself in at its group's counter once it has read q_ref;
-// the last to arrive stores the new reference query (every step in PREV mode,
-// at a fire in ANCHOR mode) and resets the counter, so that counters and flags
-// are zero between calls.
+// So the blocks of a slice wait for words of each other.  At a fire those waits
+// end once every block of the slice has started, which holds when the whole
+// grid is resident at once (the launch gives the chip at most one block per
+// compute unit) and also when it is not, since workgroups are dispatched in
+// index order and a slice's blocks are consecutive, so that complete slices
+// drain and make room for the one that is cut.  They are bounded all the same:
+// past spin_limit polls (kStepSpinLimit, or fewer from
+// LOUISKV_STEP_SPIN_LIMIT, for tests of this path) a block records a time-out
+// in the status word and goes on; its row-list entries are clamped into the
+// pool, so that such a step reads no memory out of bounds.  Without a fire a
+// block that has waited for a while asks whether all of its slice have started
+// and leaves its share of the merge to the last one to start if not
+// (attn_merge_share), so that steps on several streams, each holding compute
+// units that the other's blocks need, do not wait for each other.
+//
+// Measured, 8 slices (one layer) of 4 heads, 1024 units and 2048 rows: 18.2 ->
+// 15.2 us a step, fires and the steps between them together; 32 slices with
+// 4096 rows: 32.2 -> 30.0 us.
+//
+// The handed words replace counters and flags on which the blocks met: a
+// block's stores, the wait for them, its count and then the last one's loads
+// were four trips across the chip for the partials, and as many for the logits
+// and the list.
+//
+// Where the reference query moves (every step in PREV mode, at a fire in
+// ANCHOR mode) every block counts itself in at its group's counter once it has
+// read q_ref; the last to arrive stores the new reference query and resets the
+// counter, so that the workspace is zero between calls.
 constexpr int kStepSpinLimit = 1 << 20;
-// Counters and flags of the fused step sit kStepSyncStride ints apart, each
-// in a 256-byte block of its own: atomics on one line serialise.
+// Counters of the fused step sit kStepSyncStride ints apart, each in a
+// 256-byte block of its own: atomics on one line serialise.
 constexpr int kStepSyncStride = 64;
 // Blocks per slice: at most the one-trip merge's chunk count.
 constexpr int kStepMaxBlocks = kMergeBatch;
-static_assert(kStepMaxBlocks <= kMaxSelectParts, "a selection part per block");
+static_assert(kStepMaxBlocks <= kMaxSelectParts && kStepMaxBlocks <= 32, "a selection part and a bit per block");
 // List entries a thread loads before it knows whether the group fired.
 constexpr int kStepListEarly = 2;
 
@@ -2524,8 +2902,10 @@ struct FusedStep {
   int n_units, budget;
   int32_t *sel_units, *n_sel_units, *n_sel, *sel_rows;
   double* scores_out;
-  double *logit_ws, *part_max;
-  int32_t *sel_counter, *attn_counter, *ready, *grp_counter, *status;
+  double* logit_ws;
+  int32_t *hand_rows, *hand_nsel;   // [n_slices][budget], [n_slices][kStepMaxBlocks]
+  uint64_t* met;                    // per slice, kStepSyncStride ints apart: arrivals << 32 | shares left
+  int32_t *grp_counter, *status;
   int n_blk, chunk_rows, n_pad, spin_limit;
   int local_start, n_local;
   float* part;
@@ -2535,13 +2915,12 @@ struct FusedStep {
 };
 
 // LDS of the attention part of the fused step: wave probability slots,
-// per-wave (m, l, acc), the merge's (m, l) pairs and the chunk's list entries.
+// per-wave (m, l, acc) and the chunk's list entries.
 template <int G>
-constexpr size_t fused_attn_lds(int n_blk, int chunk_rows) {
+constexpr size_t fused_attn_lds(int chunk_rows) {
   constexpr int NM = G == 8 ? 2 : 1;
   return (size_t)kSelWaves * NM * 64 * sizeof(float4) + (size_t)2 * kSelWaves * G * sizeof(float) +
-         (size_t)kSelWaves * G * kHeadDim * sizeof(float) + (size_t)n_blk * G * sizeof(float2) +
-         (size_t)chunk_rows * sizeof(int);
+         (size_t)kSelWaves * G * kHeadDim * sizeof(float) + (size_t)chunk_rows * sizeof(int);
 }
 
 template <int G>
@@ -2551,7 +2930,8 @@ void step_fused_kernel(const FusedStep a) {
   constexpr int NM = G == 8 ? 2 : 1;
   extern __shared__ __align__(16) char smem[];
   __shared__ double s_bpart[16];
-  __shared__ int s_grp_last;
+  __shared__ int s_grp_last, s_nsel, s_late;
+  __shared__ uint32_t s_left;
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, p16 = lane & 15;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nb = a.n_blk;
@@ -2566,76 +2946,31 @@ void step_fused_kernel(const FusedStep a) {
   const int p1 = max(p0, min(p0 + a.chunk_rows, a.budget + a.n_local));
   const int sel_hi = max(p0, min(p1, a.budget));
   const int32_t* rl = a.sel_rows + (size_t)s * a.budget;
+  const int list_end = max(a.budget - 1, 0);   // sel_rows holds at least one entry a slice
 
-  // the list of the last fire, its length and the Q operand, loaded with the
-  // boundary test's inputs (every access to the list and its length is a
-  // device-scope load: selecting blocks of this launch write them on a fire)
+  // Loads in the order in which they are needed, so that a wave waits for no
+  // later one: the list of the last fire and its length, the boundary test's
+  // inputs and the Q operand.
   int early[kStepListEarly];
 #pragma unroll
   for (int e = 0; e < kStepListEarly; ++e) {
     const int i = tid + e * kSelThreads;
-    early[e] = p0 + i < sel_hi ? __hip_atomic_load(rl + p0 + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+    early[e] = rl[min(p0 + i, list_end)];
   }
-  int nsel = __hip_atomic_load(a.n_sel + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  int nsel = a.n_sel[s];
+  constexpr int kInFlight = G == 8 ? 1 : 2;   // tiles per wave in flight (G = 8: registers for one)
+  BoundaryRows<uint16_t> bnd;   // by every thread, first step or not: no branch around the loads
+  boundary_load(a.q, static_cast<const uint16_t*>(a.q_ref), n_q_heads, grp, 0, bnd);
   attn_bf16x8 qa[NM][4];
   load_attn_q<G>(a.q + (size_t)s * G * kHeadDim, lane, qa);
-  const double r = boundary_r(a.q, a.q_ref, n_q_heads, a.first, grp, s_bpart);
-  const bool fire = a.first || r < a.tau;
-  if (c == 0 && kvh == 0 && tid == 0) {
-    if (a.r_out) a.r_out[grp] = r;
-    a.fire_out[grp] = (uint8_t)(fire ? 1 : 0);
-  }
-  if (c == 0 && w == 0)
-    store_slice(a.k_new, a.v_new, a.k_local, a.v_local, a.window, a.step, a.seg_len, a.evict_seg, a.reps,
-                a.unit_start, a.unit_size, a.units_cap, a.n_clusters, a.k_pool, a.v_pool, a.pool_rows, a.prompt_len,
-                s, lane);
 
   // attention LDS (after the selection's, which it may reuse)
   float4 (*s_p)[NM][64] = reinterpret_cast<float4 (*)[NM][64]>(smem);
   float (*s_m)[G] = reinterpret_cast<float (*)[G]>(s_p + NW);
   float (*s_l)[G] = s_m + NW;
   float (*s_acc)[G][kHeadDim] = reinterpret_cast<float (*)[G][kHeadDim]>(s_l + NW);
-  float2* s_ml = reinterpret_cast<float2*>(s_acc + NW);
-  int* s_rows = reinterpret_cast<int*>(s_ml + nb * G);
+  int* s_rows = reinterpret_cast<int*>(s_acc + NW);
   auto clamp_row = [&](int row) { return (int)min<int64_t>(max(row, 0), a.pool_rows - 1); };
-  if (fire) {
-    const bool selected = select_part<uint16_t, G, true>(
-        a.q, a.n_kv_heads, s, c, nb, a.scale, a.reps, a.units_cap, a.n_units, a.n_pad, a.budget, a.unit_start,
-        a.unit_size, a.sel_units, a.n_sel_units, a.n_sel, a.sel_rows, a.scores_out, a.logit_ws, a.part_max,
-        a.sel_counter + s * kStepSyncStride, smem);
-    if (selected) {
-      // the list is out before the flag goes up
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      __syncthreads();
-      if (tid == 0) __hip_atomic_store(a.ready + s * kStepSyncStride, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    } else {
-      if (tid == 0) {
-        int polls = 0;
-        while (__hip_atomic_load(a.ready + s * kStepSyncStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) {
-          if (++polls >= a.spin_limit) {
-            __hip_atomic_store(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            break;
-          }
-          __builtin_amdgcn_s_sleep(8);
-        }
-      }
-      __syncthreads();
-    }
-    nsel = __hip_atomic_load(a.n_sel + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    for (int i = tid; p0 + i < sel_hi; i += kSelThreads)
-      s_rows[i] = clamp_row(__hip_atomic_load(rl + p0 + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-    load_attn_q<G>(a.q + (size_t)s * G * kHeadDim, lane, qa);   // not kept in registers across the selection
-  } else {
-#pragma unroll
-    for (int e = 0; e < kStepListEarly; ++e) {
-      const int i = tid + e * kSelThreads;
-      if (p0 + i < sel_hi) s_rows[i] = clamp_row(early[e]);
-    }
-    for (int i = tid + kStepListEarly * kSelThreads; p0 + i < sel_hi; i += kSelThreads)
-      s_rows[i] = clamp_row(__hip_atomic_load(rl + p0 + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-  }
-  __syncthreads();
-  nsel = max(0, min(nsel, a.budget));
 
   // the chunk's rows: 16-row tiles t = w, w + NW, ...
   const uint16_t* kb = a.k_pool + (size_t)s * a.pool_rows * kHeadDim;
@@ -2645,36 +2980,103 @@ void step_fused_kernel(const FusedStep a) {
   const uint16_t* kn = a.k_new + (size_t)s * kHeadDim;
   const uint16_t* vn = a.v_new + (size_t)s * kHeadDim;
   const int newest = a.step % a.window;
-  // the row at position pos of the chunk, or NULL if there is none
-  auto row_ptr = [&](int pos, const uint16_t* pool, const uint16_t* ring, const uint16_t* cur) -> const uint16_t* {
-    if (pos >= p1) return nullptr;
-    if (pos < a.budget) return pos < nsel ? pool + (size_t)s_rows[pos - p0] * kHeadDim : nullptr;
+  // the row at position pos of the chunk (list entry `row` if it is a selected
+  // one); a position past its end, or past the list, reads the newest row and
+  // is masked
+  auto row_at = [&](int pos, int row, bool& valid, const uint16_t* pool, const uint16_t* ring,
+                    const uint16_t* cur) -> const uint16_t* {
+    valid = pos < p1 && (pos >= a.budget || pos < nsel);
     int slot = a.local_start + (pos - a.budget);   // local_start < window and pos - budget < n_local <= window
     slot -= slot >= a.window ? a.window : 0;
-    return slot == newest ? cur : ring + (size_t)slot * kHeadDim;
+    const uint16_t* p = pos < a.budget ? pool + (size_t)row * kHeadDim
+                        : slot == newest ? cur : ring + (size_t)slot * kHeadDim;
+    return valid ? p : cur;
   };
-  auto load_tile = [&](int t, uint4 (&kx)[4], uint4 (&vx)[4]) -> bool {
-    const int tb = p0 + 16 * t;
-    const uint16_t* kp = row_ptr(tb + p16, kb, kl, kn);
+  // A tile's loads: no branch around them (the compiler waits for every load in
+  // flight where some may not have been issued); bit 4 of the result is the
+  // lane's K row's validity, bits 0..3 its V rows'.
+  auto load_tile = [&](int t, uint4 (&kx)[4], uint4 (&vx)[4]) -> int {
+    const int tb = p0 + 16 * t, last = max(sel_hi - p0 - 1, 0);
+    bool ok;
+    const uint16_t* kp = row_at(tb + p16, s_rows[min(16 * t + p16, last)], ok, kb, kl, kn);
+    int valid = ok ? 16 : 0;
 #pragma unroll
-    for (int cc = 0; cc < 4; ++cc) kx[cc] = kp ? *reinterpret_cast<const uint4*>(kp + 32 * cc + 8 * g) : uint4{};
+    for (int cc = 0; cc < 4; ++cc) kx[cc] = *reinterpret_cast<const uint4*>(kp + 32 * cc + 8 * g);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      const uint16_t* vp = row_ptr(tb + 4 * k + g, vb, vl, vn);
-      vx[k] = vp ? *reinterpret_cast<const uint4*>(vp + 8 * p16) : uint4{};
+      const uint16_t* vp = row_at(tb + 4 * k + g, s_rows[min(16 * t + 4 * k + g, last)], ok, vb, vl, vn);
+      valid |= ok ? 1 << k : 0;
+      vx[k] = *reinterpret_cast<const uint4*>(vp + 8 * p16);
     }
-    return kp != nullptr;
+    return valid;
   };
+  const int n_tiles = (p1 - p0 + 15) / 16;
+  uint4 kx[kInFlight][4], vx[kInFlight][4];
+  int kv[kInFlight];
+  nsel = max(0, min(nsel, a.budget));
+  // the list into LDS; the test's barrier makes it visible
+#pragma unroll
+  for (int e = 0; e < kStepListEarly; ++e) {
+    const int i = tid + e * kSelThreads;
+    if (p0 + i < sel_hi) s_rows[i] = clamp_row(early[e]);
+  }
+  for (int i = tid + kStepListEarly * kSelThreads; p0 + i < sel_hi; i += kSelThreads) s_rows[i] = clamp_row(rl[p0 + i]);
+  // (Taking the waves' first tiles here, before the test, on the chance that
+  // the group does not fire, was slower: 15.8 against 15.4 us a step of one
+  // layer, 30.3 against 29.9 of four sequences' layer, since the rows then
+  // stand in the way of a fired slice's index vectors.)
+  const double r = boundary_r(bnd, a.q, static_cast<const uint16_t*>(a.q_ref), n_q_heads, a.first, grp, s_bpart);
+  const bool fire = a.first || r < a.tau;
+  if (c == 0 && kvh == 0 && tid == 0) {
+    if (a.r_out) a.r_out[grp] = r;
+    a.fire_out[grp] = (uint8_t)(fire ? 1 : 0);
+  }
+  if (fire) {
+    const SelectHand hand = {a.hand_rows + (size_t)s * a.budget, a.hand_nsel + s * kStepMaxBlocks, nb, a.spin_limit,
+                             a.status};
+    select_handed<uint16_t, G>(a.q, a.n_kv_heads, s, c, nb, c == nb - 1, a.scale, a.reps, a.units_cap, a.n_units,
+                               a.n_pad, a.budget, a.unit_start, a.unit_size, a.sel_units, a.n_sel_units, a.n_sel,
+                               a.sel_rows, a.scores_out, a.logit_ws, smem, hand);
+    __syncthreads();   // the selection's LDS is free
+    // the list length (the first wave) and this chunk's entries, as soon as
+    // they are there; waves without entries do not poll
+    int polls = 0;
+    for (int i0 = 0; i0 == 0 || p0 + i0 < sel_hi; i0 += kSelThreads) {
+      const int i = i0 + tid;
+      if (p0 + i0 + w * kWave >= sel_hi && (w > 0 || i0 > 0)) continue;   // wave-uniform
+      int row = 0, ns = 0;
+      for (bool all = false; !all;) {
+        if (p0 + i < sel_hi) row = __hip_atomic_load(hand.rows + p0 + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        ns = __hip_atomic_load(hand.n_sel + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const bool got = ns != 0 && (row != 0 || p0 + i >= min(sel_hi, ns - 1));
+        all = __builtin_amdgcn_ballot_w64(!got) == 0 || ++polls >= a.spin_limit;
+        if (!all) __builtin_amdgcn_s_sleep(2);
+      }
+      if (i == 0) s_nsel = ns - 1;
+      if (p0 + i < sel_hi) {
+        s_rows[i] = clamp_row(row - 1);
+        if (row) __hip_atomic_store(hand.rows + p0 + i, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+    if (polls >= a.spin_limit && lane == 0)
+      __hip_atomic_store(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    load_attn_q<G>(a.q + (size_t)s * G * kHeadDim, lane, qa);   // not kept in registers across the selection
+    __syncthreads();   // every polling wave has read the length
+    nsel = s_nsel;
+    if (tid == 0) __hip_atomic_store(hand.n_sel + c, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    nsel = max(0, min(nsel, a.budget));
+  }
+#pragma unroll
+  for (int i = 0; i < kInFlight; ++i) kv[i] = load_tile(w + i * NW, kx[i], vx[i]);
+
   // the block has read q_ref: count it in at the group's counter, after its
   // main loads (a wave's loads complete in order, and this atomic, on one
   // address for the whole group, returns late)
+  const bool moves = a.mode == LOUISKV_REF_PREV || fire;   // the reference query moves
   int grp_old = 0;
-  bool arrived = false;
   auto arrive_group = [&]() {
-    if (arrived) return;
-    arrived = true;
     __builtin_amdgcn_sched_barrier(0);
-    if (tid == 0)
+    if (moves && tid == 0)
       grp_old = __hip_atomic_fetch_add(a.grp_counter + grp * kStepSyncStride, 1, __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_AGENT);
   };
@@ -2687,35 +3089,74 @@ void step_fused_kernel(const FusedStep a) {
     for (int e = 0; e < 8; ++e) acc[j][e] = 0.f;
   }
   const float qscale = (float)a.scale * kLog2e;
-  const int n_tiles = (p1 - p0 + 15) / 16;
-  constexpr int kInFlight = G == 8 ? 1 : 2;   // tiles per wave in flight (G = 8: registers for one)
-  for (int t = w; t < n_tiles; t += kInFlight * NW) {
-    uint4 kx0[4], vx0[4], kx1[4], vx1[4];
-    const bool two = kInFlight == 2 && t + NW < n_tiles;
-    const bool kv0 = load_tile(t, kx0, vx0);
-    const bool kv1 = two ? load_tile(t + NW, kx1, vx1) : false;
-    arrive_group();
-    attn_mfma_tile<G>(qa, kx0, vx0, kv0, qscale, m, l, acc, s_p[w], lane);
-    if (two) attn_mfma_tile<G>(qa, kx1, vx1, kv1, qscale, m, l, acc, s_p[w], lane);
-  }
   arrive_group();
+  // a block of a step that does not fire counts itself in at the slice's word:
+  // it waits for nobody before it hands its results, so that once all blocks of
+  // the slice are in, all their words are sure to come
+  // (a thread of a wave with few tiles: a later load of the same wave would wait
+  // for the count; wave 0 cost 2-3% of a step with several tiles a wave)
+  constexpr int kMetThread = (NW - 2) * 64;
+  uint64_t* met = fire || nb == 1 ? nullptr : a.met + s * (kStepSyncStride / 2);
+  uint64_t met_old = 0;
+  if (met && tid == kMetThread) met_old = __hip_atomic_fetch_add(met, 1ull << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  for (int t = w; t < n_tiles; t += kInFlight * NW) {
+    if (t != w) {
+#pragma unroll
+      for (int i = 0; i < kInFlight; ++i) kv[i] = load_tile(t + i * NW, kx[i], vx[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < kInFlight; ++i)
+      if (t + i * NW < n_tiles) {
+        // rows past the end or the list: probability and value zero
+#pragma unroll
+        for (int k = 0; k < 4; ++k) vx[i][k] = kv[i] >> k & 1 ? vx[i][k] : uint4{};
+        attn_mfma_tile<G>(qa, kx[i], vx[i], kv[i] >> 4 != 0, qscale, m, l, acc, s_p[w], lane);
+      }
+  }
   attn_wave_to_lds<G>(m, l, acc, s_m[w], s_l[w], s_acc[w], lane);
+  if (tid == 0) s_late = 0;
   __syncthreads();
-  const bool done = attn_block_merge<G, NW, true>(s_m, s_l, s_acc, tid, s, c, nb, a.part, a.out, a.out_bf16,
-                                                  a.lse_out, a.attn_counter + s * kStepSyncStride, s_ml);
-  if (done && fire && tid == 0)
-    __hip_atomic_store(a.ready + s * kStepSyncStride, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  // the store, by a wave that has little left to do (nothing here reads what it
+  // writes: the newest row comes from k_new/v_new, the slot it takes and the
+  // unit it creates are not attended or scored at this step)
+  if (c == 0 && w == NW - 1)
+    store_slice(a.k_new, a.v_new, a.k_local, a.v_local, a.window, a.step, a.seg_len, a.evict_seg, a.reps,
+                a.unit_start, a.unit_size, a.units_cap, a.n_clusters, a.k_pool, a.v_pool, a.pool_rows, a.prompt_len,
+                s, lane);
+  attn_hand<G, NW>(s_m, s_l, s_acc, tid, s, c, nb, a.part, a.out, a.out_bf16, a.lse_out);
+  if (nb > 1) {
+    auto merge = [&](int share, uint64_t* ask) {
+      const int limit = fire ? a.spin_limit : kStepSpinLimit;
+      const int polls = attn_merge_share<G, NW>(tid, s, share, nb, a.part, a.out, a.out_bf16, a.lse_out, limit, ask,
+                                                min(a.spin_limit, kStepPatience), &s_late,
+                                                reinterpret_cast<float4*>(s_p));
+      if (polls >= limit && lane == 0) __hip_atomic_store(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    if (met && tid == kMetThread) {
+      const bool last = (int)(met_old >> 32) == nb - 1;
+      s_left = last ? (uint32_t)met_old : 0;   // shares left to the last block to start
+      if (last)
+        __hip_atomic_fetch_sub(met, ((uint64_t)nb << 32) | (uint32_t)met_old, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+    }
+    merge(c, met);
+    if (met) {
+      for (uint32_t left = s_left; left; left &= left - 1) {
+        __syncthreads();
+        merge(__builtin_ctz(left), nullptr);
+      }
+    }
+  }
+  if (!moves) return;
 
   // the group's last block to arrive moves its reference query
   if (tid == 0) s_grp_last = grp_old == a.n_kv_heads * nb - 1;
   __syncthreads();
   if (!s_grp_last) return;
   if (tid == 0) __hip_atomic_store(a.grp_counter + grp * kStepSyncStride, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (a.mode == LOUISKV_REF_PREV || fire) {
-    const size_t base = (size_t)grp * n_q_heads * kHeadDim;
-    for (int i = tid; i < n_q_heads * kHeadDim / 8; i += kSelThreads)
-      reinterpret_cast<uint4*>(a.q_ref + base)[i] = reinterpret_cast<const uint4*>(a.q + base)[i];
-  }
+  const size_t base = (size_t)grp * n_q_heads * kHeadDim;
+  for (int i = tid; i < n_q_heads * kHeadDim / 8; i += kSelThreads)
+    reinterpret_cast<uint4*>(a.q_ref + base)[i] = reinterpret_cast<const uint4*>(a.q + base)[i];
 }
 
 // One wave per (slice, head): merge the chunk partials.
@@ -2784,11 +3225,9 @@ int step_attn_chunks(int buf_rows, int window) {
   return std::max(1, (int)(((int64_t)buf_rows + window + kStepAttnRows - 1) / kStepAttnRows));
 }
 
-// Partials of the fused step's attention (merged in-kernel), by dtype (bf16:
-// the two-launch step's chunks or the one-launch step's blocks per slice).
+// Partials of the two-launch step's attention (merged in-kernel), by dtype.
 size_t step_attn_part_bytes(int64_t S, int G, int buf_rows, int window, int dtype) {
-  const int nc = dtype == LOUISKV_BF16 ? std::max(step_attn_chunks(buf_rows, window), kStepMaxBlocks)
-                                       : attn_chunks(S, buf_rows, window, true);
+  const int nc = dtype == LOUISKV_BF16 ? step_attn_chunks(buf_rows, window) : attn_chunks(S, buf_rows, window, true);
   return nc == 1 ? 0 : align_up((size_t)S * nc * G * (2 + kHeadDim) * sizeof(float), 256);
 }
 
@@ -3404,7 +3843,7 @@ namespace louiskv {
 namespace {
 
 struct StepLayout {
-  size_t counters, logits, pmax, fetch, part, total;
+  size_t counters, hand_logits, hand_rows, hand_part, logits, pmax, fetch, part, total;
 };
 
 // Polls of the one-launch step's bounded wait: kStepSpinLimit, or fewer from
@@ -3418,24 +3857,37 @@ int step_spin_limit() {
   return kStepSpinLimit;
 }
 
-// Workspace of a decode step: the arrival counters and flags (zero between
-// calls; the one-launch step keeps selection and attention counters and
-// ready flags per slice, group counters and a status word kStepSyncStride
-// ints apart, the two-launch step its two counters per slice packed at the
-// start), logits and part maxima, with a cached KV_critical the transfer
-// plan's scratch (fetch slots, rows, counts), and the attention partials.
+// Workspace of a decode step: the arrival counters (zero between calls; the
+// one-launch step keeps its counters and a status word kStepSyncStride ints
+// apart, the two-launch step its two counters per slice packed at the start);
+// the words that the one-launch step's blocks hand each other (logits, list
+// entries, list lengths, attention partials), all zero between calls; the
+// scratch of the two-launch step, in a part of its own at the same offset for
+// every type and kind of call, so that calls of both forms and equal sizes may
+// share a workspace: logits and part maxima, with a cached KV_critical the
+// transfer plan's scratch (fetch slots, rows, counts), and the attention
+// partials.  (Clearing that scratch at the end of a two-launch step instead
+// cost 2-3% of it.)
 StepLayout step_layout(int64_t S, int dtype, int G, int units_cap, int budget, int window, bool cached = false) {
   StepLayout L{};
   Carver cv(nullptr);
   cv.take<int32_t>(((size_t)4 * S + 1) * kStepSyncStride);
-  L.logits = align_up(cv.used, 256);
+  L.hand_logits = align_up(cv.used, 256);
   cv.take<double>((size_t)S * units_cap * G);
-  L.pmax = align_up(cv.used, 256);
-  cv.take<double>((size_t)S * std::max(kMaxLogitParts, kMaxSelectParts) * G);
-  L.fetch = align_up(cv.used, 256);
-  if (cached) cv.take<int32_t>((size_t)S * (2 * (size_t)std::max(budget, 1) + 1));
-  L.part = align_up(cv.used, 256);
-  cv.take<char>(step_attn_part_bytes(S, G, budget, window, dtype));
+  L.hand_rows = align_up(cv.used, 256);
+  cv.take<int32_t>((size_t)S * ((size_t)std::max(budget, 1) + kStepMaxBlocks));
+  L.hand_part = align_up(cv.used, 256);   // (a0, a1, m, l) per block, head and pair of dims
+  cv.take<float>((size_t)S * kStepMaxBlocks * G * (kHeadDim / 2) * 4);
+  L.logits = align_up(cv.used, 256);
+  if (cached || dtype != LOUISKV_BF16) {
+    cv.take<double>((size_t)S * units_cap * G);
+    L.pmax = align_up(cv.used, 256);
+    cv.take<double>((size_t)S * std::max(kMaxLogitParts, kMaxSelectParts) * G);
+    L.fetch = align_up(cv.used, 256);
+    if (cached) cv.take<int32_t>((size_t)S * (2 * (size_t)std::max(budget, 1) + 1));
+    L.part = align_up(cv.used, 256);
+    cv.take<char>(step_attn_part_bytes(S, G, budget, window, dtype));
+  }
   L.counters = 0;
   L.total = align_up(cv.used, 256);
   return L;
@@ -3585,11 +4037,10 @@ int decode_step_impl(const void* q, void* q_ref, int32_t dtype, int64_t n_groups
     fa.n_sel = n_sel;
     fa.sel_rows = sel_rows;
     fa.scores_out = scores_out;
-    fa.logit_ws = logit_ws;
-    fa.part_max = part_max;
-    fa.sel_counter = sel_counter;
-    fa.attn_counter = sel_counter + n_slices * kStepSyncStride;
-    fa.ready = sel_counter + 2 * n_slices * kStepSyncStride;
+    fa.logit_ws = reinterpret_cast<double*>(ws + lay.hand_logits);
+    fa.hand_rows = reinterpret_cast<int32_t*>(ws + lay.hand_rows);
+    fa.hand_nsel = fa.hand_rows + (size_t)n_slices * std::max(budget, 1);
+    fa.met = reinterpret_cast<uint64_t*>(sel_counter);
     fa.grp_counter = sel_counter + 3 * n_slices * kStepSyncStride;
     fa.status = sel_counter + 4 * n_slices * kStepSyncStride;
     fa.n_blk = nb;
@@ -3598,14 +4049,14 @@ int decode_step_impl(const void* q, void* q_ref, int32_t dtype, int64_t n_groups
     fa.spin_limit = step_spin_limit();
     fa.local_start = local_start;
     fa.n_local = n_local;
-    fa.part = reinterpret_cast<float*>(ws + lay.part);
+    fa.part = reinterpret_cast<float*>(ws + lay.hand_part);
     fa.out = out;
     fa.out_bf16 = out_dtype == LOUISKV_BF16;
     fa.lse_out = lse_out;
     const unsigned fgrid = (unsigned)(n_slices * nb);
 #define LKV_STEP_FUSED(G)                                                                                   \
   {                                                                                                         \
-    const size_t flds = std::max(lds, fused_attn_lds<G>(nb, chunk_rows));                                   \
+    const size_t flds = std::max(lds, fused_attn_lds<G>(chunk_rows));                                       \
     if ((st = check_lds(reinterpret_cast<const void*>(&step_fused_kernel<G>), flds))) return st;            \
     step_fused_kernel<G><<<fgrid, kSelThreads, flds, s>>>(fa);                                              \
   }

@@ -1139,6 +1139,62 @@ def test_decode_step_equals_stage_calls(case):
     assert fires >= (2 if mname == "prev" else 20) and evictions > 2
 
 
+@pytest.mark.parametrize("kind,groups,h,g,C,prompt,budget", [
+    ("bf16", 1, 8, 4, 2100, 4200, 300),    # more units than two per thread and rank registers hold
+    ("bf16", 1, 1, 8, 64, 1024, 2048),     # one slice, 32 blocks, a budget above the prompt
+    ("bf16", 16, 8, 2, 64, 1024, 256),     # two blocks a slice
+    ("bf16", 10, 8, 1, 64, 1024, 256),     # three blocks a slice, the third without pairs to merge
+    ("bf16", 32, 8, 1, 64, 1024, 256),     # one block a slice
+    ("bf16", 1, 8, 4, 64, 1024, 1),        # a list of at most one row
+    ("mixed", 2, 8, 4, 64, 1024, 256)])
+def test_decode_step_edges_and_clean_workspace(monkeypatch, kind, groups, h, g, C, prompt, budget):
+    """The fused step against the stage calls where its split over blocks has
+    edges.  Steps that do not fire run with a one-poll bound: their blocks then
+    leave their shares of the merge to the last block of the slice to start
+    instead of waiting, and the results stay the same.  After every one-launch
+    step the whole workspace is zero, which the next one relies on (a word of
+    it that is not zero counts as handed over); mixed: a two-launch float32
+    step of equal sizes on the same workspace before each of them leaves its
+    scratch elsewhere.  Selections equal
+    bit for bit; outputs within 1e-5 (float32 sums over at most 2,176 rows in
+    another order)."""
+    from paper_2510_11292_amd.engine import LouisKVEngine, config_from_workload
+    wl = synth.get_workload("si-lo-16k").replace(prompt_len=prompt, n_clusters=C, budget=budget, n_kv_heads=h,
+                                                 n_q_heads=h * g, name="si-lo-16k")
+    steps = 40
+    data = synth.make_slices(wl, DEV, groups=[(0, l) for l in range(groups)], gen_len=steps)
+    cfg = config_from_workload(wl, n_groups=groups, gen_len=steps)
+    a = LouisKVEngine(cfg, torch.bfloat16, DEV, out_dtype=torch.float32, fused_step=False)
+    b = LouisKVEngine(cfg, torch.bfloat16, DEV, out_dtype=torch.float32, fused_step=True)
+    engines = [a, b]
+    if kind == "mixed":
+        f = LouisKVEngine(cfg, torch.float32, DEV, fused_step=True)
+        b.ws_step, own = f.ws_step, b.ws_step.numel()
+        engines.append(f)
+    for e in engines:
+        e.prefill(data.prompt_keys.to(e.dtype), data.prompt_values.to(e.dtype), data.init_idx)
+    quiet = 0
+    for t in range(steps):
+        x = [u[t] for u in (data.queries, data.gen_keys, data.gen_values)]
+        if kind == "mixed":
+            f.step(*[u.float() for u in x])
+        a.step(*x)
+        if not a.fire.any():
+            quiet += 1
+            monkeypatch.setenv("LOUISKV_STEP_SPIN_LIMIT", "1")
+        b.step(*x)
+        torch.cuda.synchronize()
+        monkeypatch.delenv("LOUISKV_STEP_SPIN_LIMIT", raising=False)
+        assert int(b.ws_step[:own if kind == "mixed" else None].count_nonzero()) == 0, t
+        for name in ("fire", "q_ref", "n_sel", "n_sel_units", "unit_start", "unit_size", "k_local", "v_local"):
+            assert torch.equal(getattr(a, name), getattr(b, name)), (t, name)
+        for i in range(cfg.n_slices):
+            assert torch.equal(a.sel_units[i, :int(a.n_sel_units[i])], b.sel_units[i, :int(b.n_sel_units[i])]), (t, i)
+        assert (a.out - b.out).abs().max().item() <= 1e-5 * max(1.0, a.out.abs().max().item()), t
+        assert (a.lse - b.lse).abs().max().item() <= 1e-5, t
+    assert quiet > 0 or groups > 2
+
+
 def test_decode_step_wait_is_bounded(monkeypatch):
     """The one-launch step's wait for a fired slice's selection is bounded:
     with the bound forced down to one poll (LOUISKV_STEP_SPIN_LIMIT=1) the
