@@ -2034,10 +2034,20 @@ __device__ __forceinline__ void stage_row_list(const int32_t* __restrict__ list,
 // Blocks of 8 waves (attn_mfma_waves; two fit a CU where a wave needs at
 // most 128 VGPRs).  A slice's rows go to one block when there are enough
 // slices to fill the chip; otherwise they are cut into n_chunks equal ranges
-// (split-KV), never below kAttnMinRows rows per block, and a second kernel
+// (split-KV), never below attn_min_rows rows per block, and a second kernel
 // merges the chunk partials.
 constexpr int kAttnTargetBlocks = 256;
-constexpr int kAttnMinRows = 256;
+// The rows per block are what a block has in flight in one pass, a 16-row tile
+// a wave in bf16 and two rows a 16-lane group in float32: over few slices each
+// further pass is another trip to memory that nothing hides.  8 slices, 4
+// heads: bf16, 1152 rows, 256 -> 128 rows a block: attention 8.2 -> 6.9 us;
+// float32, 640 rows: 12.9 us at 256, 9.1 at 64, a decode step of it 15.6 at
+// 128 and 15.1 at 64.  A caller whose workspace holds the partials of
+// kAttnCoarseRows rows a block but not those gets the former.
+constexpr int kAttnRowsBf16 = 128, kAttnRowsF32 = 64;
+constexpr int kAttnMinRows = kAttnRowsF32;   // sizes the workspace for either type
+constexpr int kAttnCoarseRows = 256;
+int attn_min_rows(int dtype) { return dtype == LOUISKV_BF16 ? kAttnRowsBf16 : kAttnRowsF32; }
 // A fused decode step over few slices spreads each slice's rows over many
 // small blocks: kStepAttnRows rows per block of kStepAttnWaves waves.
 #ifndef LKV_STEP_ATTN_ROWS
@@ -2417,6 +2427,20 @@ __device__ __forceinline__ int attn_merge_share(int tid, int64_t s, int chunk, i
   return polls;
 }
 
+// Sums over the four 16-lane rows of a wave, lane by lane: row r of the result
+// holds those of the r-th argument.
+__device__ __forceinline__ float rows_sum4(float x0, float x1, float x2, float x3) {
+  auto pair16 = [](float x, float y) {   // rows x0+x1, y0+y1, x2+x3, y2+y3
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  };
+  auto pair32 = [](float x, float y) {   // rows x0+x2, x1+x3, y0+y2, y1+y3
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  };
+  return pair32(pair16(x0, x1), pair16(x2, x3));
+}
+
 // With boundary-delimited segments the window of slice s holds the tokens
 // from its first token (state) to n_tokens - 1; otherwise the arguments hold.
 __device__ __forceinline__ void slice_window(const int32_t* seg_state, int seg_stride, int64_t s, int window,
@@ -2553,36 +2577,24 @@ void attn_partial_kernel(const T* __restrict__ q, int n_kv_heads, float scale, c
     __builtin_amdgcn_sched_barrier(0);   // keep every load of the pass ahead of its first use
     compute_pass(kx, vx, valid);
   }
-  // merge the 4 row groups of each wave (lanes l, l^16, l^32, l^48 share sub)
+  // merge the 4 row groups of each wave (lanes l, l^16, l^32, l^48 share sub):
+  // one rescale to the wave's maximum, then sums by lane swaps, four
+  // accumulators at a time
+  const int w = tid >> 6;
 #pragma unroll
   for (int j = 0; j < G; ++j) {
-#pragma unroll
-    for (int o = 16; o <= 32; o <<= 1) {
-      const float mo = __shfl_xor(m[j], o, kWave);
-      const float lo = __shfl_xor(l[j], o, kWave);
-      const float mn = fmaxf(m[j], mo);
-      const float ca = mn == -__builtin_inff() ? 0.f : __builtin_amdgcn_exp2f(m[j] - mn);
-      const float cb = mn == -__builtin_inff() ? 0.f : __builtin_amdgcn_exp2f(mo - mn);
-      l[j] = l[j] * ca + lo * cb;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float ao = __shfl_xor(acc[j][e], o, kWave);
-        acc[j][e] = acc[j][e] * ca + ao * cb;
-      }
-      m[j] = mn;
+    float mn = fmaxf(m[j], __uint_as_float(xor16_u32(__float_as_uint(m[j]), tid & 63)));
+    mn = fmaxf(mn, __uint_as_float(xor32_u32(__float_as_uint(mn), tid & 63)));
+    const float c = mn == -__builtin_inff() ? 0.f : __builtin_amdgcn_exp2f(m[j] - mn);
+    const float lj = l[j] * c, ls = rows_sum4(lj, lj, lj, lj);
+    if ((tid & 63) == 0) {
+      s_m[w][j] = mn;
+      s_l[w][j] = ls;
     }
-  }
-  const int w = tid >> 6;
-  if ((tid & 63) < 16) {
 #pragma unroll
-    for (int j = 0; j < G; ++j) {
-      if (sub == 0) {
-        s_m[w][j] = m[j];
-        s_l[w][j] = l[j];
-      }
-#pragma unroll
-      for (int e = 0; e < 8; ++e) s_acc[w][j][8 * sub + e] = acc[j][e];
-    }
+    for (int e = 0; e < 8; e += 4)
+      s_acc[w][j][8 * sub + e + (tid >> 4 & 3)] =
+          rows_sum4(acc[j][e] * c, acc[j][e + 1] * c, acc[j][e + 2] * c, acc[j][e + 3] * c);
   }
   __syncthreads();
   attn_block_merge<G, kAttnWaves>(s_m, s_l, s_acc, tid, s, chunk, n_chunks, part, out, out_bf16, lse_out,
@@ -2709,14 +2721,6 @@ __device__ __forceinline__ void attn_mfma_tile(const attn_bf16x8 (&qa)[NM][4], c
 template <int G>
 __device__ __forceinline__ void attn_wave_to_lds(const float (&m)[G], float (&l)[G], float (&acc)[G][8], float* s_mw,
                                                  float* s_lw, float (*s_accw)[kHeadDim], int lane) {
-  auto pair16 = [](float x, float y) {   // rows x0+x1, y0+y1, x2+x3, y2+y3
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-  };
-  auto pair32 = [](float x, float y) {   // rows x0+x2, x1+x3, y0+y2, y1+y3
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-  };
 #pragma unroll
   for (int j = 0; j < G; ++j) {
     l[j] = row16_sum(l[j]);
@@ -2727,7 +2731,7 @@ __device__ __forceinline__ void attn_wave_to_lds(const float (&m)[G], float (&l)
 #pragma unroll
     for (int e = 0; e < 8; e += 4)
       s_accw[j][8 * (lane & 15) + e + (lane >> 4)] =
-          pair32(pair16(acc[j][e], acc[j][e + 1]), pair16(acc[j][e + 2], acc[j][e + 3]));
+          rows_sum4(acc[j][e], acc[j][e + 1], acc[j][e + 2], acc[j][e + 3]);
   }
 }
 
@@ -3159,7 +3163,11 @@ void step_fused_kernel(const FusedStep a) {
     reinterpret_cast<uint4*>(a.q_ref + base)[i] = reinterpret_cast<const uint4*>(a.q + base)[i];
 }
 
-// One wave per (slice, head): merge the chunk partials.
+// One wave per (slice, head): merge the chunk partials, in chunk order.  Lane c
+// takes chunk c's (m, l); the accumulators of the first kCombineBatch chunks
+// are on their way meanwhile (a chunk's loads at a time: 4.4 us for 5 chunks
+// of 32 rows; now 2.8 for 9).
+constexpr int kCombineBatch = 16;
 template <class TO>
 __global__ __launch_bounds__(256)
 void attn_combine_kernel(const float* __restrict__ part, int n_chunks, int G, int64_t n_rows,
@@ -3169,18 +3177,40 @@ void attn_combine_kernel(const float* __restrict__ part, int n_chunks, int G, in
   const int lane = threadIdx.x & 63;
   const int64_t s = row / G;
   const int j = (int)(row - s * G);
-  const size_t pstride = 2 + kHeadDim;
+  constexpr size_t pstride = 2 + kHeadDim;
   const float* p = part + (size_t)s * n_chunks * G * pstride + (size_t)j * pstride;
-  float mm = -__builtin_inff();
-  for (int c = 0; c < n_chunks; ++c) mm = fmaxf(mm, p[(size_t)c * G * pstride]);
+  const size_t cstride = (size_t)G * pstride;
+  float2 x[kCombineBatch];
+  auto load_batch = [&](int c0) {
+#pragma unroll
+    for (int b = 0; b < kCombineBatch; ++b)
+      x[b] = *reinterpret_cast<const float2*>(p + (size_t)min(c0 + b, n_chunks - 1) * cstride + 2 + 2 * lane);
+  };
+  float2 ml = *reinterpret_cast<const float2*>(p + (size_t)min(lane, n_chunks - 1) * cstride);
+  load_batch(0);
+  float mm = ml.x;
+  for (int c0 = kWave; c0 < n_chunks; c0 += kWave)
+    mm = fmaxf(mm, p[(size_t)min(c0 + lane, n_chunks - 1) * cstride]);
+  mm = wave_max(mm);
   float ll = 0.f, a0 = 0.f, a1 = 0.f;
   if (mm != -__builtin_inff()) {
-    for (int c = 0; c < n_chunks; ++c) {
-      const float* pc = p + (size_t)c * G * pstride;
-      const float w = __builtin_amdgcn_exp2f(pc[0] - mm);
-      ll += pc[1] * w;
-      a0 += pc[2 + 2 * lane] * w;
-      a1 += pc[2 + 2 * lane + 1] * w;
+    for (int c0 = 0; c0 < n_chunks; c0 += kCombineBatch) {
+      if (c0 > 0) {
+        load_batch(c0);
+        if (c0 % kWave == 0) ml = *reinterpret_cast<const float2*>(p + (size_t)min(c0 + lane, n_chunks - 1) * cstride);
+      }
+      const float e = __builtin_amdgcn_exp2f(ml.x - mm);
+#pragma unroll
+      for (int b = 0; b < kCombineBatch; ++b) {
+        if (c0 + b < n_chunks) {
+          const int src = (c0 + b) % kWave;
+          const float w = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(e), src));
+          const float lb = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(ml.y), src));
+          ll += lb * w;
+          a0 += x[b].x * w;
+          a1 += x[b].y * w;
+        }
+      }
     }
   }
   const float inv = ll > 0.f ? 1.f / ll : 0.f;
@@ -3205,17 +3235,17 @@ size_t retrieve_ws_bytes(int64_t S, int units_cap, int budget) {
 
 constexpr int kAttnMaxListRows = 8192;   // row-list entries one block stages in LDS (32 KB)
 
-int attn_chunks(int64_t S, int buf_rows, int window, bool indexed) {
+int attn_chunks(int64_t S, int buf_rows, int window, bool indexed, int min_rows) {
   const int64_t cap = (int64_t)buf_rows + window;
-  const int64_t by_rows = std::max<int64_t>(1, (cap + kAttnMinRows - 1) / kAttnMinRows);
+  const int64_t by_rows = std::max<int64_t>(1, (cap + min_rows - 1) / min_rows);
   const int64_t by_grid = std::max<int64_t>(1, (kAttnTargetBlocks + S - 1) / S);
   int64_t nc = std::min(by_rows, by_grid);
   if (indexed) nc = std::max<int64_t>(nc, (cap + kAttnMaxListRows - 1) / kAttnMaxListRows);
   return (int)nc;
 }
 
-size_t attn_ws_bytes(int64_t S, int G, int buf_rows, int window, bool indexed) {
-  const int nc = attn_chunks(S, buf_rows, window, indexed);
+size_t attn_ws_bytes(int64_t S, int G, int buf_rows, int window, bool indexed, int min_rows = kAttnMinRows) {
+  const int nc = attn_chunks(S, buf_rows, window, indexed, min_rows);
   return nc == 1 ? 0 : align_up((size_t)S * nc * G * (2 + kHeadDim) * sizeof(float), 256);
 }
 
@@ -3227,7 +3257,8 @@ int step_attn_chunks(int buf_rows, int window) {
 
 // Partials of the two-launch step's attention (merged in-kernel), by dtype.
 size_t step_attn_part_bytes(int64_t S, int G, int buf_rows, int window, int dtype) {
-  const int nc = dtype == LOUISKV_BF16 ? step_attn_chunks(buf_rows, window) : attn_chunks(S, buf_rows, window, true);
+  const int nc = dtype == LOUISKV_BF16 ? step_attn_chunks(buf_rows, window)
+                                        : attn_chunks(S, buf_rows, window, true, attn_min_rows(dtype));
   return nc == 1 ? 0 : align_up((size_t)S * nc * G * (2 + kHeadDim) * sizeof(float), 256);
 }
 
@@ -3762,10 +3793,15 @@ int sparse_decode_attn(const void* q, int32_t dtype, int64_t n_slices, int32_t n
                 n_local);
   if (indexed && buf_rows > 0 && src_rows < 1) return fail(LOUISKV_ERR_SHAPE, "pool_rows=%lld", (long long)src_rows);
   const bool step_bf16 = step_sync && indexed && dtype == LOUISKV_BF16;
-  const int n_chunks = step_bf16 ? step_attn_chunks(buf_rows, window) : attn_chunks(n_slices, buf_rows, window, indexed);
+  int min_rows = attn_min_rows(dtype);
+  if (!step_sync && (!workspace || workspace_bytes < attn_ws_bytes(n_slices, group_size, buf_rows, window, indexed,
+                                                                   min_rows)))
+    min_rows = kAttnCoarseRows;   // what fewer partials need
+  const int n_chunks = step_bf16 ? step_attn_chunks(buf_rows, window)
+                                 : attn_chunks(n_slices, buf_rows, window, indexed, min_rows);
   if ((int64_t)n_slices * n_chunks > INT32_MAX) return fail(LOUISKV_ERR_SHAPE, "problem too large for one launch");
   const size_t need = step_sync ? step_attn_part_bytes(n_slices, group_size, buf_rows, window, dtype)
-                                : attn_ws_bytes(n_slices, group_size, buf_rows, window, indexed);
+                                : attn_ws_bytes(n_slices, group_size, buf_rows, window, indexed, min_rows);
   if (need > 0 && (!workspace || workspace_bytes < need))
     return fail(LOUISKV_ERR_WORKSPACE, "workspace needs %zu bytes, got %zu", need, workspace_bytes);
   AttnArgs a;
@@ -4202,7 +4238,7 @@ extern "C" int louiskv_sparse_decode_attn_rows_noalloc(const void* q, int32_t dt
                                                        float* lse_out, void* stream) {
   if (!sel_rows) return fail(LOUISKV_ERR_NULL, "sel_rows is required");
   if (n_slices >= 1 && group_size >= 1 && budget >= 0 && window >= 0) {
-    const size_t need = attn_ws_bytes(n_slices, group_size, budget, window, true);
+    const size_t need = attn_ws_bytes(n_slices, group_size, budget, window, true, kAttnCoarseRows);
     if (need > LOUISKV_NOALLOC_SCRATCH_BYTES)
       return fail(LOUISKV_ERR_WORKSPACE,
                   "the allocation-free call holds at most %zu bytes of partials and this launch needs %zu; "

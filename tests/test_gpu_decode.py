@@ -415,6 +415,37 @@ def test_sparse_decode_attn_rows(dtype, odt, G, H, g, B, PR, W, nl, ls):
         np.testing.assert_allclose(to64(lse[grp, h * g:(h + 1) * g]), l, rtol=1e-5, atol=1e-5)
 
 
+@pytest.mark.parametrize("dtype,H,B,W", [
+    (torch.bfloat16, 1, 2048, 1),     # 17 chunks of one slice: a second batch of the merge, ragged
+    (torch.bfloat16, 1, 8192, 128),   # 65: a second lane round
+    (torch.float32, 1, 64, 1),        # two chunks
+    (torch.float32, 1, 4096, 64),     # 65 chunks
+    (torch.bfloat16, 256, 300, 20)])  # one block per slice
+def test_split_kv_chunk_counts(dtype, H, B, W):
+    """Split-KV attention at the edges of its merge (chunk counts around a
+    batch of loads and around a wave) against the oracle, and the same call
+    with a workspace for 256-row chunks only (larger chunks, the same result to
+    float32 rounding) and with one byte less (refused)."""
+    test_sparse_decode_attn_rows(dtype, torch.float32, 1, H, 1, B, B + 9, W, W, 0)
+    L = _L()
+    gen = _gen(B + W)
+    q = torch.randn(1, H, 128, generator=gen, device=DEV).to(dtype)
+    kp, vp = (torch.randn(H, B, 128, generator=gen, device=DEV).to(dtype) for _ in range(2))
+    kl, vl = (torch.randn(H, W, 128, generator=gen, device=DEV).to(dtype) for _ in range(2))
+    rows = torch.arange(B, device=DEV, dtype=torch.int32).repeat(H, 1)
+    nsel = torch.full((H,), B, device=DEV, dtype=torch.int32)
+    out = [torch.empty(1, H, 128, dtype=torch.float32, device=DEV) for _ in range(2)]
+    coarse = max(1, min(-(-(B + W) // 256), -(-256 // H)))
+    need = 0 if coarse == 1 else -(-H * coarse * 130 * 4 // 256) * 256
+    ws = torch.empty(max(need, 1), dtype=torch.uint8, device=DEV)
+    L.sparse_decode_attn_rows(q, H, kp, vp, rows, nsel, kl, vl, 0, W, out[0], None)
+    L.sparse_decode_attn_rows(q, H, kp, vp, rows, nsel, kl, vl, 0, W, out[1], None, workspace=ws[:need])
+    assert (out[0] - out[1]).abs().max().item() <= 2e-6
+    if need:
+        with pytest.raises(RuntimeError, match="workspace"):
+            L.sparse_decode_attn_rows(q, H, kp, vp, rows, nsel, kl, vl, 0, W, out[1], None, workspace=ws[:need - 1])
+
+
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 def test_split_kv_merge_repeats_on_one_workspace(dtype):
     """Split-KV attention keeps the chunk partials in the workspace between its
