@@ -1718,17 +1718,23 @@ void delta_plan_kernel(const int32_t* __restrict__ row_ws, const int32_t* __rest
 //    the smallest (slot_step, slot), paired in slot order: empty slots first,
 //    then the rows selected longest ago;
 //  - slot_list lists the n_sel slots holding the selection, in slot order.
-// Thread t holds slots [R t, R t + R) in registers for the whole plan.  The
+// A slice's plan is one block's work, bound by its compute unit's vector ALU
+// and by its loads: every pass over the slots costs 1024 x R slot tests.  So a
+// thread holds its slots' states as bits, in pieces of 16 consecutive slots
+// (a wave's loads then cover whole lines: with 64 consecutive slots a thread
+// each line was fetched several times), the few marked ones are walked bit by
+// bit, and while there are k empty slots those are the victims.  Otherwise the
 // k-th smallest key slot_step + 1 among the candidates (slots not selected
 // now) comes from a radix select by 8-bit digits (per-wave histograms), the
-// ties at the threshold in slot order from block scans.
+// ties at the threshold in slot order from block scans.  A fired plan of 65536
+// slots, 4096 rows: 70 -> 34 us; a decode step over such a host cache, fires
+// and the steps between them, 54 -> 45.
 constexpr int kCacheMaxStep = (1 << 24) - 2;
 constexpr int kCacheMaxSlotsPerThread = 64;
 constexpr int kCacheMaxRows = kPlanThreads * kCacheMaxSlotsPerThread;
 
 // x[j] = a[i0 + j] for j < R (fill past n), in 16-byte loads where the run
-// is aligned and whole (a thread's run is consecutive, so a wave's plain
-// loads would each touch 64 lines)
+// is aligned and whole
 template <int R>
 __device__ __forceinline__ void load_run(const int32_t* a, int i0, int n, int fill, int (&x)[R]) {
   const bool vec = ((reinterpret_cast<uintptr_t>(a + i0) & 15u) == 0) && i0 + R <= n;
@@ -1747,6 +1753,62 @@ __device__ __forceinline__ void load_run(const int32_t* a, int i0, int n, int fi
   }
 }
 
+// Block-wide counts of a thread's flags (bit j: slot j % kPiece of piece
+// j / kPiece, pieces one after another over the block's threads): how many
+// precede the thread's first of each piece in slot order, and the total.  The
+// pieces are scanned together, 16 bits each (at most 16 x 1024 a piece).
+template <int kPiece, int kPieces>
+__device__ __forceinline__ int block_scan_pieces(uint64_t flags, uint64_t* s_w, int (&before)[kPieces]) {
+  static_assert(kPieces <= 4 && kPiece * kPlanThreads < 65536, "16 bits a piece");
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  uint64_t x = 0;
+#pragma unroll
+  for (int p = 0; p < kPieces; ++p)
+    x |= (uint64_t)__popc((uint32_t)(flags >> (p * kPiece)) & ((1u << kPiece) - 1)) << (16 * p);
+  uint64_t incl = x;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint64_t y = __shfl_up((unsigned long long)incl, o, kWave);
+    if (lane >= o) incl += y;
+  }
+  if (lane == 63) s_w[w] = incl;
+  __syncthreads();
+  uint64_t pre = 0, total = 0;
+  for (int q = 0; q < kPlanWaves; ++q) {
+    const uint64_t c = s_w[q];
+    pre += q < w ? c : 0;
+    total += c;
+  }
+  __syncthreads();
+  pre += incl - x;
+  int sum = 0;
+#pragma unroll
+  for (int p = 0; p < kPieces; ++p) {
+    before[p] = sum + (int)(pre >> (16 * p) & 0xffff);
+    sum += (int)(total >> (16 * p) & 0xffff);
+  }
+  return sum;
+}
+
+// f(j, rank) for every set flag.
+template <int kPiece, int kPieces, class F>
+__device__ __forceinline__ void for_ranks(uint64_t flags, const int (&before)[kPieces], F f) {
+#pragma unroll
+  for (int p = 0; p < kPieces; ++p) {
+    int o = before[p];
+    for (uint32_t m = (uint32_t)(flags >> (p * kPiece)) & ((1u << kPiece) - 1); m; m &= m - 1)
+      f(p * kPiece + __builtin_ctz(m), o++);
+  }
+}
+
+// The flags with rank < limit.
+template <int kPiece, int kPieces>
+__device__ __forceinline__ uint64_t ranks_below(uint64_t flags, const int (&before)[kPieces], int limit) {
+  uint64_t r = 0;
+  for_ranks<kPiece>(flags, before, [&](int j, int o) { r |= (uint64_t)(o < limit) << j; });
+  return r;
+}
+
 template <int R>
 __global__ __launch_bounds__(kPlanThreads)
 void cache_plan_kernel(const int32_t* __restrict__ row_ws, const int32_t* __restrict__ n_sel,
@@ -1757,6 +1819,7 @@ void cache_plan_kernel(const int32_t* __restrict__ row_ws, const int32_t* __rest
                        int32_t* __restrict__ n_fetch_out) {
   extern __shared__ uint32_t s_bits[];   // one bit per pool row
   __shared__ int s_w[kPlanWaves];
+  __shared__ uint64_t s_w64[kPlanWaves];
   __shared__ int s_hist[kPlanWaves][256];
   __shared__ int s_k, s_below, s_thr;
   const int64_t s = blockIdx.x;
@@ -1773,13 +1836,10 @@ void cache_plan_kernel(const int32_t* __restrict__ row_ws, const int32_t* __rest
   const int32_t* rows = row_ws + (size_t)s * budget;
   int32_t* brow = buf_row + (size_t)s * cache_rows;
   int32_t* bstep = slot_step + (size_t)s * cache_rows;
-  const int i0 = tid * R;
-  // key[j] = slot_step + 1 of slot i0 + j (0: empty); slots past the end
-  // take step + 1, which is never a candidate
-  int key[R];
-  load_run<R>(bstep, i0, cache_rows, step, key);
-#pragma unroll
-  for (int j = 0; j < R; ++j) key[j] += 1;
+  constexpr int kPiece = R < 16 ? R : 16, kPieces = R / kPiece;
+  static_assert(R % kPiece == 0, "a thread's slots are whole pieces");
+  // bit or index j of a thread: its slot j % kPiece of piece j / kPiece
+  auto slot_of = [&](int j) { return (j / kPiece * kPlanThreads + tid) * kPiece + j % kPiece; };
   for (int i = tid; i < words; i += kPlanThreads) s_bits[i] = 0u;
   if (tid == 0) s_k = 0;
   __syncthreads();
@@ -1788,30 +1848,28 @@ void cache_plan_kernel(const int32_t* __restrict__ row_ws, const int32_t* __rest
     if (r >= 0 && r < pool_rows) atomicOr(&s_bits[r >> 5], 1u << (r & 31));
   }
   __syncthreads();
-  // hits: slots whose row is selected again (test and clear its bit); the
-  // thread's own run only, read in pieces of up to 16 slots
-  constexpr int kPiece = R < 16 ? R : 16;
-  static_assert(R % kPiece == 0, "a run splits into whole pieces");
-  uint64_t hit = 0;
-#pragma unroll
-  for (int j0 = 0; j0 < R; j0 += kPiece) {
-    int row[kPiece];
-    load_run<kPiece>(brow, i0 + j0, cache_rows, -1, row);
+  // hits: slots whose row is selected again (test and clear its bit; a slot
+  // without a row clears none, so that a piece's tests are all in flight);
+  // eq: the empty slots
+  uint64_t hit = 0, eq = 0;
+#pragma unroll 2
+  for (int p = 0; p < kPieces; ++p) {
+    int row[kPiece], x[kPiece];
+    load_run<kPiece>(brow, slot_of(p * kPiece), cache_rows, -1, row);
+    load_run<kPiece>(bstep, slot_of(p * kPiece), cache_rows, step, x);
+    uint32_t h = 0, e = 0;
 #pragma unroll
     for (int j = 0; j < kPiece; ++j) {
-      const int r = row[j];
-      if (r >= 0 && r < pool_rows) {
-        const uint32_t bit = 1u << (r & 31);
-        if (atomicAnd(&s_bits[r >> 5], ~bit) & bit) hit |= 1ull << (j0 + j);
-      }
+      const bool ok = row[j] >= 0 && row[j] < pool_rows;
+      const int b = row[j] & 31;
+      const uint32_t old = atomicAnd(&s_bits[ok ? row[j] >> 5 : 0], ok ? ~(1u << b) : ~0u);
+      h |= (ok ? old >> b & 1u : 0u) << j;
+      e |= (uint32_t)(x[j] == -1) << j;
     }
+    hit |= (uint64_t)h << (p * kPiece);
+    eq |= (uint64_t)e << (p * kPiece);
   }
-#pragma unroll
-  for (int j = 0; j < R; ++j)
-    if (hit >> j & 1ull) {
-      key[j] = step + 1;
-      bstep[i0 + j] = step;
-    }
+  for (uint64_t m = hit; m; m &= m - 1) bstep[slot_of(__builtin_ctzll(m))] = step;
   __syncthreads();
   // the new rows: still marked
   int kk = 0;
@@ -1823,116 +1881,118 @@ void cache_plan_kernel(const int32_t* __restrict__ row_ws, const int32_t* __rest
   if (lane == 0) atomicAdd(&s_k, kk);
   __syncthreads();
   const int k = s_k;
-  // radix select of the k-th smallest candidate key, from the highest digit
-  // that step + 1 uses
-  int below = 0;   // candidates with a key below the prefix's range, taken whole
-  int prefix = 0;
-  const int top = step < 255 ? 0 : step < 65535 ? 8 : 16;
-  for (int shift = top; shift >= 0 && k > 0; shift -= 8) {
-    for (int i = tid; i < kPlanWaves * 256; i += kPlanThreads) (&s_hist[0][0])[i] = 0;
-    __syncthreads();
-    // runs of one digit are counted in a register and added once; a thread's
-    // last run is added once per wave when the wave's agree
-    int cur = -1, cnt = 0;
+  // Victims: the k smallest candidate keys, equal ones in slot order.  While
+  // the cache has k empty slots those are the first of them.
+  eq &= ~hit;
+  uint64_t lt = 0;
+  int eq_before[kPieces];
+  int take_eq = k;
+  if (block_scan_pieces<kPiece>(eq, s_w64, eq_before) < k) {
+    // f(piece, j, key) for the thread's slots, read again: 64 of them in registers
+    // across the passes left no room; key = slot_step + 1, that of hits and of
+    // slots past the end step + 1, which is never a candidate
+    auto each_key = [&](auto f) {
+#pragma unroll 1
+      for (int p = 0; p < kPieces; ++p) {
+        int x[kPiece];
+        load_run<kPiece>(bstep, slot_of(p * kPiece), cache_rows, step, x);
 #pragma unroll
-    for (int j = 0; j < R; ++j) {
-      const int x = key[j];
-      if (x <= step && (x >> (shift + 8)) == prefix) {
-        const int dg = (x >> shift) & 255;
-        if (dg != cur) {
-          if (cnt) atomicAdd(&s_hist[wv][cur], cnt);
-          cur = dg;
-          cnt = 0;
+        for (int j = 0; j < kPiece; ++j) f(p, j, x[j] + 1);
+      }
+    };
+    // radix select of the k-th smallest candidate key, from the highest digit
+    // that step + 1 uses
+    int below = 0;   // candidates with a key below the prefix's range, taken whole
+    int prefix = 0;
+    const int top = step < 255 ? 0 : step < 65535 ? 8 : 16;
+    for (int shift = top; shift >= 0; shift -= 8) {
+      for (int i = tid; i < kPlanWaves * 256; i += kPlanThreads) (&s_hist[0][0])[i] = 0;
+      __syncthreads();
+      // runs of one digit are counted in a register and added once; a thread's
+      // last run is added once per wave when the wave's agree
+      int cur = -1, cnt = 0;
+      each_key([&](int, int, int x) {
+        if (x <= step && (x >> (shift + 8)) == prefix) {
+          const int dg = (x >> shift) & 255;
+          if (dg != cur) {
+            if (cnt) atomicAdd(&s_hist[wv][cur], cnt);
+            cur = dg;
+            cnt = 0;
+          }
+          ++cnt;
         }
-        ++cnt;
-      }
-    }
-    const uint64_t m = __builtin_amdgcn_ballot_w64(cnt > 0);
-    if (m) {
-      const int lead = (int)__builtin_ctzll(m);
-      const int d0 = __shfl(cur, lead, kWave);
-      if (__builtin_amdgcn_ballot_w64(cnt > 0 && cur != d0) == 0) {
-        const int tot = wave_sum_int(cnt);
-        if (lane == lead) atomicAdd(&s_hist[wv][d0], tot);
-      } else if (cnt > 0) {
-        atomicAdd(&s_hist[wv][cur], cnt);
-      }
-    }
-    __syncthreads();
-    if (wv == 0) {
-      // lane l holds digits 4l .. 4l + 3, lowest first
-      int c[4], tot = 0;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        int h = 0;
-        for (int q2 = 0; q2 < kPlanWaves; ++q2) h += s_hist[q2][4 * lane + i];
-        c[i] = h;
-        tot += h;
-      }
-      int incl = tot;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(incl, o, kWave);
-        if (lane >= o) incl += y;
-      }
-      int cum = below + incl - tot;
-      int hit_d = -1, before = 0;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if (hit_d < 0 && cum + c[i] >= k) {
-          hit_d = 4 * lane + i;
-          before = cum;
+      });
+      const uint64_t m = __builtin_amdgcn_ballot_w64(cnt > 0);
+      if (m) {
+        const int lead = (int)__builtin_ctzll(m);
+        const int d0 = __shfl(cur, lead, kWave);
+        if (__builtin_amdgcn_ballot_w64(cnt > 0 && cur != d0) == 0) {
+          const int tot = wave_sum_int(cnt);
+          if (lane == lead) atomicAdd(&s_hist[wv][d0], tot);
+        } else if (cnt > 0) {
+          atomicAdd(&s_hist[wv][cur], cnt);
         }
-        cum += c[i];
       }
-      const uint64_t found = __builtin_amdgcn_ballot_w64(hit_d >= 0);
-      const int all = __shfl(incl, 63, kWave);
-      if (found && lane == (int)__builtin_ctzll(found)) {
-        s_below = before;
-        s_thr = (prefix << 8) | hit_d;
-      } else if (!found && lane == 0) {
-        // fewer than k candidates (only a stale slot_step leaves that): every
-        // candidate is a victim, the threshold above them all
-        s_below = below + all;
-        s_thr = (prefix << 8) + 256;
+      __syncthreads();
+      if (wv == 0) {
+        // lane l holds digits 4l .. 4l + 3, lowest first
+        int c[4], tot = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          int h = 0;
+          for (int q2 = 0; q2 < kPlanWaves; ++q2) h += s_hist[q2][4 * lane + i];
+          c[i] = h;
+          tot += h;
+        }
+        int incl = tot;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const int y = __shfl_up(incl, o, kWave);
+          if (lane >= o) incl += y;
+        }
+        int cum = below + incl - tot;
+        int hit_d = -1, before = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          if (hit_d < 0 && cum + c[i] >= k) {
+            hit_d = 4 * lane + i;
+            before = cum;
+          }
+          cum += c[i];
+        }
+        const uint64_t found = __builtin_amdgcn_ballot_w64(hit_d >= 0);
+        const int all = __shfl(incl, 63, kWave);
+        if (found && lane == (int)__builtin_ctzll(found)) {
+          s_below = before;
+          s_thr = (prefix << 8) | hit_d;
+        } else if (!found && lane == 0) {
+          // fewer than k candidates (only a stale slot_step leaves that): every
+          // candidate is a victim, the threshold above them all
+          s_below = below + all;
+          s_thr = (prefix << 8) + 256;
+        }
       }
+      __syncthreads();
+      below = s_below;
+      prefix = s_thr;
     }
-    __syncthreads();
-    below = s_below;
-    prefix = s_thr;
+    // victims: keys below the threshold, then the first (k - below) slots with
+    // the threshold key
+    take_eq = k - below;
+    eq = 0;
+    each_key([&](int p, int j, int x) {
+      lt |= (uint64_t)(x <= step && x < prefix) << (p * kPiece + j);
+      eq |= (uint64_t)(x <= step && x == prefix) << (p * kPiece + j);
+    });
+    block_scan_pieces<kPiece>(eq, s_w64, eq_before);
   }
-  // victims: keys below the threshold, then the first (k - below) slots with
-  // the threshold key, in slot order; the q-th new row (selection order) goes
-  // to the q-th victim (slot order)
-  const int thr = prefix;
-  const int take_eq = k - below;
-  uint64_t victim = 0;
-  int n_victims = 0, v_first = 0;
-  if (k > 0) {
-    int n_lt = 0, n_eq = 0;
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-      n_lt += key[j] <= step && key[j] < thr;
-      n_eq += key[j] <= step && key[j] == thr;
-    }
-    int eq_before;
-    block_scan_count(n_eq, s_w, eq_before);
-    int e = eq_before;
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-      const int x = key[j];
-      if (x > step) continue;
-      if (x < thr || (x == thr && e < take_eq)) victim |= 1ull << j;
-      e += x == thr;
-    }
-    n_victims = block_scan_count(__popcll(victim), s_w, v_first);
-#pragma unroll
-    for (int j = 0, o = v_first; j < R; ++j)
-      if (victim >> j & 1ull) {
-        if (o < budget) fetch_slot[(size_t)s * budget + o] = i0 + j;
-        ++o;
-      }
-  }
+  // the q-th new row (selection order) goes to the q-th victim (slot order)
+  const uint64_t victim = lt | ranks_below<kPiece>(eq, eq_before, take_eq);
+  int v_first[kPieces];
+  int n_victims = block_scan_pieces<kPiece>(victim, s_w64, v_first);
+  for_ranks<kPiece>(victim, v_first, [&](int j, int o) {
+    if (o < budget) fetch_slot[(size_t)s * budget + o] = slot_of(j);
+  });
   n_victims = min(n_victims, budget);
   __syncthreads();
   // the new rows in selection order: the q-th takes victim q's slot (rows
@@ -1966,24 +2026,12 @@ void cache_plan_kernel(const int32_t* __restrict__ row_ws, const int32_t* __rest
   }
   // the slots that hold the selection, in slot order: hits and the victims
   // that took a new row
-  uint64_t held = hit;
-  {
-    int o = v_first;
-#pragma unroll
-    for (int j = 0; j < R; ++j)
-      if (victim >> j & 1ull) {
-        if (o < min(k, n_victims)) held |= 1ull << j;
-        ++o;
-      }
-  }
-  int before;
-  block_scan_count(__popcll(held), s_w, before);
-#pragma unroll
-  for (int j = 0, o = before; j < R; ++j)
-    if (held >> j & 1ull) {
-      if (o < budget) slot_list[(size_t)s * budget + o] = i0 + j;
-      ++o;
-    }
+  const uint64_t held = hit | ranks_below<kPiece>(victim, v_first, min(k, n_victims));
+  int before[kPieces];
+  block_scan_pieces<kPiece>(held, s_w64, before);
+  for_ranks<kPiece>(held, before, [&](int j, int o) {
+    if (o < budget) slot_list[(size_t)s * budget + o] = slot_of(j);
+  });
 }
 
 // Copy the planned rows pool -> buffer slot: 16 lanes per row, 16 rows per pass.

@@ -549,6 +549,49 @@ def _lru_model(buf_row, slot_step, rows, step):
     return buf_row, slot_step, [i for i in range(len(buf_row)) if slot_step[i] == step], len(new)
 
 
+@pytest.mark.parametrize("C,filled", [
+    (65536, 65536), (65536, 40000), (65535, 65400),   # 64 slots a thread; the last one's run is not whole
+    (33000, 33000), (20001, 20001), (9000, 8900), (700, 700)])   # 64, 32, 16 and 8 slots a thread
+def test_cache_plan_pieces(C, filled):
+    """The LRU plan on a given cache state, against the policy written out:
+    slots in pieces over the block's threads, with as many empty slots as new
+    rows and without (the radix select), keys of one and two digits."""
+    L = _L()
+    H, U, B, PR = 2, 300, 600, 70000
+    rng = np.random.default_rng(C + filled)
+    reps = torch.randn(H, U, 128, generator=_gen(C), device=DEV)
+    q = torch.randn(1, H, 128, generator=_gen(C + 1), device=DEV).to(torch.bfloat16)
+    start = torch.from_numpy(np.stack([rng.permutation(U) * 10 for _ in range(H)]).astype(np.int32)).to(DEV)
+    size = torch.full((H, U), 10, dtype=torch.int32, device=DEV)
+    kp, vp = (torch.randn(H, PR, 128, generator=_gen(C + i), device=DEV).to(torch.bfloat16) for i in (2, 3))
+    i32 = dict(dtype=torch.int32, device=DEV)
+    for step in (200, 3000):
+        buf, stp = np.full((H, C), -1, np.int32), np.full((H, C), -1, np.int32)
+        for h in range(H):
+            # a third of the selectable rows cached, anywhere among the filled slots
+            rows = np.concatenate([rng.permutation(3000)[:min(1000, filled)], 3000 + rng.permutation(PR - 3000)])[:filled]
+            at = np.sort(rng.permutation(C)[:filled])
+            buf[h, at] = rng.permutation(rows)
+            stp[h, at] = rng.integers(0, step, filled)
+        sel_a, sel_b = (torch.zeros(H, U, **i32) for _ in range(2))
+        rows_sel = torch.zeros(H, B, **i32)
+        nu, ns, nu2, ns2, nf = (torch.zeros(H, **i32) for _ in range(5))
+        L.retrieve_rows(q, H, reps, start, size, U, B, sel_a, nu, ns, rows_sel)
+        kb, vb = (torch.zeros(H, C, 128, dtype=torch.bfloat16, device=DEV) for _ in range(2))
+        bt, st, sl = torch.from_numpy(buf).to(DEV), torch.from_numpy(stp).to(DEV), torch.zeros(H, B, **i32)
+        L.retrieve_cached(q, H, reps, start, size, U, kp, vp, B, step, sel_b, nu2, ns2, kb, vb, bt, st, sl, n_fetched=nf)
+        torch.cuda.synchronize()
+        for h in range(H):
+            n = int(ns[h])
+            rows = to_np(rows_sel[h, :n]).tolist()
+            want_buf, want_step, want_list, new = _lru_model(buf[h], stp[h], rows, step)
+            assert int(ns2[h]) == n and int(nf[h]) == new and new > 0
+            assert np.array_equal(to_np(bt[h]), want_buf) and np.array_equal(to_np(st[h]), want_step), (step, h)
+            assert to_np(sl[h, :n]).tolist() == want_list, (step, h)
+            got = np.flatnonzero(want_buf != buf[h])
+            assert torch.equal(kb[h, got], kp[h, want_buf[got]]) and torch.equal(vb[h, got], vp[h, want_buf[got]])
+
+
 def _check_delta_buffers(eng, gi, H, before=None, t=None):
     """KV_critical kept as a cache of pool rows: the listed slots hold exactly
     the selected rows (as copies of their pool rows), every slot at most once;
