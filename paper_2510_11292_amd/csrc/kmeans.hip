@@ -1689,10 +1689,16 @@ bool scatter_in_lds(int C) { return (size_t)C * 8 <= kMaxHistLds; }
 // left-over keys (8-10 us) takes back what the shorter sweeps give (8 slices of
 // 20011 keys, 625 clusters, 1.0e8 pairs: 707 us without, 735 with; 8 of 32768
 // keys, 1024 clusters, 2.7e8 pairs: 946 without, 824 with).
+// Nor does one of few clusters: what recording costs is per key, what it saves
+// per (key, centroid) pair (a whole call with against without: 10% longer at
+// 166 clusters, 256 slices of 4000 keys; 2% longer at 520, 40 of 25000; 5-8%
+// shorter at 944 and 1041).
 constexpr int kFirstRecord = 2;
 constexpr double kRecordPairs = 1.5e8;
+constexpr int kRecordClusters = 640;
 bool records(int64_t S, int N, int C, int dtype) {
-  return dtype == LOUISKV_BF16 && scatter_in_lds(C) && (double)S * N * C >= kRecordPairs;
+  return dtype == LOUISKV_BF16 && scatter_in_lds(C) && C >= kRecordClusters &&
+         (double)S * N * C >= kRecordPairs;
 }
 
 Ws carve(void* base, int64_t n_slices, int n_tokens, int n_clusters, int dtype) {
