@@ -2893,7 +2893,7 @@ void attn_mfma_kernel(const uint16_t* __restrict__ q, int n_kv_heads, float scal
 // two 16-row tiles per wave in flight; the newest window row is read from
 // k_new/v_new, since the store of the same launch may not have reached the
 // ring yet.  The slice's blocks hand each other their partial results, and
-// every block merges a share of the slice's outputs (attn_hand_merge).
+// every block merges a share of the slice's outputs (attn_merge_share).
 //
 // So the blocks of a slice wait for words of each other.  At a fire those waits
 // end once every block of the slice has started, which holds when the whole
