@@ -464,8 +464,9 @@ int louiskv_sparse_decode_attn_rows(const void* q, int32_t dtype, int64_t n_slic
  *            before its first use (for example allocated zeroed); every call
  *            leaves its arrival counters and the words its blocks handed each
  *            other at zero again, so it is reused without clearing, also by
- *            calls of the other dtype or louiskv_decode_step_cached with the
- *            same sizes.  Calls that share it must not overlap.
+ *            calls of the other dtype, of other sizes (budget, units_cap,
+ *            window, group size) or of louiskv_decode_step_cached with the
+ *            same n_slices.  Calls that share it must not overlap.
  *            Its first (4 * n_slices + 1) * 64 int32 words are those
  *            counters and flags; the last of them is a status word that a
  *            block sets to 1 if its wait for a selection ever gave up (after

@@ -3927,7 +3927,7 @@ namespace louiskv {
 namespace {
 
 struct StepLayout {
-  size_t counters, hand_logits, hand_rows, hand_part, logits, pmax, fetch, part, total;
+  size_t hand_logits, hand_rows, hand_part, logits, pmax, fetch, part, total;
 };
 
 // Polls of the one-launch step's bounded wait: kStepSpinLimit, or fewer from
@@ -3943,37 +3943,52 @@ int step_spin_limit() {
 
 // Workspace of a decode step: the arrival counters (zero between calls; the
 // one-launch step keeps its counters and a status word kStepSyncStride ints
-// apart, the two-launch step its two counters per slice packed at the start);
-// the words that the one-launch step's blocks hand each other (logits, list
-// entries, list lengths, attention partials), all zero between calls; the
-// scratch of the two-launch step, in a part of its own at the same offset for
-// every type and kind of call, so that calls of both forms and equal sizes may
-// share a workspace: logits and part maxima, with a cached KV_critical the
-// transfer plan's scratch (fetch slots, rows, counts), and the attention
-// partials.  (Clearing that scratch at the end of a two-launch step instead
-// cost 2-3% of it.)
+// apart, the two-launch step its two counters per slice packed at the start),
+// whose place depends on the slices alone; then, for the one-launch step, the
+// words that its blocks hand each other (logits, list entries, list lengths,
+// attention partials), all zero between calls; for the two-launch step its
+// scratch, which it does not clear: logits and part maxima, with a cached
+// KV_critical the transfer plan's scratch (fetch slots, rows, counts), and the
+// attention partials.  (Clearing it at the end of the step cost 2-3% of it.)
+//
+// Calls of one slice count but of both forms and any other sizes may share a
+// workspace, so no scratch may lie where any call's handed words do.  Behind
+// the counters the space is cut into zones of kStepZone, kStepZone, twice,
+// twice, four times, four times that, .., every other one for handed words and
+// the rest for scratch, and a call's lie whole in one zone of their kind: that
+// of the first pair whose zones hold the handed words and the scratch of a
+// call of its sizes (so a workspace for float32 serves bf16 of equal sizes).
+constexpr size_t kStepZone = 256u << 10;
+
 StepLayout step_layout(int64_t S, int dtype, int G, int units_cap, int budget, int window, bool cached = false) {
   StepLayout L{};
-  Carver cv(nullptr);
-  cv.take<int32_t>(((size_t)4 * S + 1) * kStepSyncStride);
-  L.hand_logits = align_up(cv.used, 256);
-  cv.take<double>((size_t)S * units_cap * G);
-  L.hand_rows = align_up(cv.used, 256);
-  cv.take<int32_t>((size_t)S * ((size_t)std::max(budget, 1) + kStepMaxBlocks));
-  L.hand_part = align_up(cv.used, 256);   // (a0, a1, m, l) per block, head and pair of dims
-  cv.take<float>((size_t)S * kStepMaxBlocks * G * (kHeadDim / 2) * 4);
-  L.logits = align_up(cv.used, 256);
-  if (cached || dtype != LOUISKV_BF16) {
-    cv.take<double>((size_t)S * units_cap * G);
-    L.pmax = align_up(cv.used, 256);
-    cv.take<double>((size_t)S * std::max(kMaxLogitParts, kMaxSelectParts) * G);
-    L.fetch = align_up(cv.used, 256);
-    if (cached) cv.take<int32_t>((size_t)S * (2 * (size_t)std::max(budget, 1) + 1));
-    L.part = align_up(cv.used, 256);
-    cv.take<char>(step_attn_part_bytes(S, G, budget, window, dtype));
-  }
-  L.counters = 0;
-  L.total = align_up(cv.used, 256);
+  size_t used = 0;
+  auto take = [&](size_t bytes) {
+    const size_t at = align_up(used, 256);
+    used = at + bytes;
+    return at;
+  };
+  auto carve_hand = [&](size_t base) {
+    used = base;
+    L.hand_logits = take((size_t)S * units_cap * G * sizeof(double));
+    L.hand_rows = take((size_t)S * ((size_t)std::max(budget, 1) + kStepMaxBlocks) * sizeof(int32_t));
+    // (a0, a1, m, l) per block, head and pair of dims
+    L.hand_part = take((size_t)S * kStepMaxBlocks * G * (kHeadDim / 2) * 4 * sizeof(float));
+    return align_up(used, 256);
+  };
+  auto carve_scratch = [&](size_t base) {
+    used = base;
+    L.logits = take((size_t)S * units_cap * G * sizeof(double));
+    L.pmax = take((size_t)S * std::max(kMaxLogitParts, kMaxSelectParts) * G * sizeof(double));
+    L.fetch = take(cached ? (size_t)S * (2 * (size_t)std::max(budget, 1) + 1) * sizeof(int32_t) : 0);
+    L.part = take(step_attn_part_bytes(S, G, budget, window, cached ? dtype : LOUISKV_F32));
+    return align_up(used, 256);
+  };
+  const size_t most = std::max(carve_hand(0), carve_scratch(0));
+  size_t at = ((size_t)4 * S + 1) * kStepSyncStride * sizeof(int32_t), zone = kStepZone;
+  for (; zone < most; zone *= 2) at += 2 * zone;
+  const size_t hand_end = carve_hand(at), scratch_end = carve_scratch(at + zone);
+  L.total = !cached && dtype == LOUISKV_BF16 ? hand_end : scratch_end;
   return L;
 }
 
@@ -4062,7 +4077,7 @@ int decode_step_impl(const void* q, void* q_ref, int32_t dtype, int64_t n_groups
   if (!workspace || workspace_bytes < lay.total)
     return fail(LOUISKV_ERR_WORKSPACE, "workspace needs %zu bytes, got %zu", lay.total, workspace_bytes);
   char* ws = static_cast<char*>(workspace);
-  int32_t* sel_counter = reinterpret_cast<int32_t*>(ws + lay.counters);
+  int32_t* sel_counter = reinterpret_cast<int32_t*>(ws);
   int32_t* attn_counter = sel_counter + n_slices;
   double* logit_ws = reinterpret_cast<double*>(ws + lay.logits);
   double* part_max = reinterpret_cast<double*>(ws + lay.pmax);

@@ -1269,6 +1269,49 @@ def test_decode_step_edges_and_clean_workspace(monkeypatch, kind, groups, h, g, 
     assert quiet > 0 or groups > 2
 
 
+def test_step_workspace_is_shared_by_other_sizes():
+    """One workspace serves decode steps of every form and of any sizes with
+    the same number of slices: two-launch steps (float32, and the row cache)
+    of larger and smaller budgets and unit tables leave their scratch where no
+    one-launch step takes it for handed words.  The one-launch steps between
+    them equal the stage calls (selections bit for bit, outputs within 1e-5:
+    float32 sums over at most 4,224 rows in another order)."""
+    from paper_2510_11292_amd.engine import LouisKVEngine, config_from_workload
+    steps, groups = 24, 1   # eight slices: up to 32 blocks each hand partials over
+
+    def make(C, budget, dtype, **kw):
+        wl = synth.get_workload("si-lo-16k").replace(prompt_len=8192, n_clusters=C, budget=budget, name="si-lo-16k")
+        data = synth.make_slices(wl, DEV, groups=[(0, l) for l in range(groups)], gen_len=steps)
+        cfg = config_from_workload(wl, n_groups=groups, gen_len=steps)
+        e = LouisKVEngine(cfg, dtype, DEV, out_dtype=torch.float32, **kw)
+        e.prefill(data.prompt_keys.to(dtype), data.prompt_values.to(dtype), data.init_idx)
+        return e, data
+    cache = dict(pool_on_host=True, fused_step=True)
+    others = [make(512, 2048, torch.float32, fused_step=True), make(24, 64, torch.float32, fused_step=True),
+              make(300, 1024, torch.bfloat16, cache_rows=2048, **cache),
+              make(16, 32, torch.bfloat16, cache_rows=256, **cache)]
+    pairs = [(make(C, budget, torch.bfloat16, fused_step=False)[0], *make(C, budget, torch.bfloat16, fused_step=True))
+             for C, budget in ((64, 256), (500, 4096), (17, 1))]
+    sizes = [e.ws_step.numel() for e, _ in others] + [b.ws_step.numel() for _, b, _ in pairs]
+    ws = torch.zeros(max(sizes), dtype=torch.uint8, device=DEV)
+    for e in [e for e, _ in others] + [b for _, b, _ in pairs]:
+        e.ws_step = ws
+    for t in range(steps):
+        for i, (a, b, data) in enumerate(pairs):
+            for e, d in others:
+                e.t = t
+                e.step(d.queries[t].to(e.dtype), d.gen_keys[t].to(e.dtype), d.gen_values[t].to(e.dtype))
+            for e in (a, b):
+                e.step(data.queries[t], data.gen_keys[t], data.gen_values[t])
+            torch.cuda.synchronize()
+            for name in ("fire", "q_ref", "n_sel", "n_sel_units"):
+                assert torch.equal(getattr(a, name), getattr(b, name)), (t, i, name)
+            for s in range(a.cfg.n_slices):
+                assert torch.equal(a.sel_units[s, :int(a.n_sel_units[s])], b.sel_units[s, :int(b.n_sel_units[s])]), (t, i, s)
+            assert (a.out - b.out).abs().max().item() <= 1e-5 * max(1.0, a.out.abs().max().item()), (t, i)
+            assert (a.lse - b.lse).abs().max().item() <= 1e-5, (t, i)
+
+
 def test_decode_step_wait_is_bounded(monkeypatch):
     """The one-launch step's wait for a fired slice's selection is bounded:
     with the bound forced down to one poll (LOUISKV_STEP_SPIN_LIMIT=1) the
