@@ -1091,7 +1091,9 @@ void scatter_kernel(const int32_t* __restrict__ assign, const int32_t* __restric
 // from it) and their flags cleared for the next assignment; with dlist (many
 // clusters in all) each wave takes every `stride_e`-th cluster of the slice's
 // list, without it a wave or block per cluster looks at its flag, which is one
-// dependent load less (8192 clusters: 13.3 us against 16.7).
+// dependent load less (8192 clusters: 13.3 us against 16.7).  The flag is the
+// place in the list, or where the scatter wrote none (more clusters than it
+// scans in LDS) `dirty` itself.
 // With frag given, the wave also writes the next iteration's matrix operand
 // for this centroid (-2 op(c) in A-fragment order, and ||op(c)||^2), the work
 // prep_operand_kernel does for the first iteration.  The clusters' scatter
@@ -1135,7 +1137,8 @@ void centroid_update_kernel(const UpdateArgs<T> a) {
     const int c = a.dlist ? a.dlist[crow + e] : e;
     const int n = a.counts[crow + c];
     const int off = a.offsets[(size_t)s * (a.n_clusters + 1) + c];
-    const int slot = !track ? 0 : a.dlist ? e : a.dmap[crow + c];   // place in the slice's list
+    // place in the slice's list, or -1
+    const int slot = !track ? 0 : a.dlist ? e : a.dmap ? a.dmap[crow + c] : a.dirty[crow + c] ? 0 : -1;
     const bool clean = slot < 0;
     float* dst = a.cout + ((size_t)s * a.stride + c) * kHeadDim;
     if constexpr (kSplit > 1) __syncthreads();   // every wave has read the count and the flag before one clears them
@@ -1680,7 +1683,7 @@ int n_ctiles_for(int n_clusters, int dtype) {
 constexpr size_t kMaxHistLds = 64 * 1024;
 
 // Whether the scatter scans the counts in LDS (two ints a cluster); above,
-// the scan is a launch of its own and every cluster is updated every time.
+// the scan is a launch of its own and no list of the flagged clusters is made.
 bool scatter_in_lds(int C) { return (size_t)C * 8 <= kMaxHistLds; }
 
 // Assignments record (and sweep the recomputed clusters alone) from this
@@ -1862,11 +1865,12 @@ int launch_scan_scatter(const int32_t* assign, int64_t S, int N, int C, const Ws
 
 // Centroid update; with prep_next, also the next iteration's operand (the
 // work of launch_prep for the iterations after the first).  zero_counts: the
-// next assignment counts from zero.  list: only the clusters listed by the
-// scatter (the others keep centroid and operand).
+// next assignment counts from zero.  flagged: only the clusters that the
+// assignment flagged (the others keep centroid and operand).
 template <class T>
 int launch_sum_t(const void* keys, int64_t S, int N, int C, int n_ctiles, const Ws& w, const float* cin, float* cout,
-                 int stride, bool prep_next, bool zero_counts, bool list, hipStream_t st) {
+                 int stride, bool prep_next, bool zero_counts, bool flagged, hipStream_t st) {
+  const bool list = flagged && scatter_in_lds(C);
   UpdateArgs<T> a{};
   a.keys = static_cast<const T*>(keys);
   a.members = w.members;
@@ -1882,9 +1886,9 @@ int launch_sum_t(const void* keys, int64_t S, int N, int C, int n_ctiles, const 
   a.cnorm = w.cnorm;
   a.n_ctiles = n_ctiles;
   a.zero_counts = zero_counts ? 1 : 0;
-  a.dirty = list ? w.dirty : nullptr;
+  a.dirty = flagged ? w.dirty : nullptr;
   a.ndirty = w.ndirty;
-  a.dmap = w.dmap;
+  a.dmap = list ? w.dmap : nullptr;
   a.cfrag = list && records(S, N, C, LOUISKV_BF16) ? w.cfrag : nullptr;
   a.ccnorm = w.ccnorm;
   const int64_t rows = S * C;
@@ -1906,11 +1910,11 @@ int launch_sum_t(const void* keys, int64_t S, int N, int C, int n_ctiles, const 
 }
 
 int launch_sum(const void* keys, int dtype, int64_t S, int N, int C, const Ws& w, const float* cin, float* cout,
-               int stride, bool prep_next, bool zero_counts, bool list, hipStream_t st) {
+               int stride, bool prep_next, bool zero_counts, bool flagged, hipStream_t st) {
   const int n_ctiles = n_ctiles_for(C, dtype);
   return dtype == LOUISKV_BF16
-             ? launch_sum_t<uint16_t>(keys, S, N, C, n_ctiles, w, cin, cout, stride, prep_next, zero_counts, list, st)
-             : launch_sum_t<float>(keys, S, N, C, n_ctiles, w, cin, cout, stride, prep_next, zero_counts, list, st);
+             ? launch_sum_t<uint16_t>(keys, S, N, C, n_ctiles, w, cin, cout, stride, prep_next, zero_counts, flagged, st)
+             : launch_sum_t<float>(keys, S, N, C, n_ctiles, w, cin, cout, stride, prep_next, zero_counts, flagged, st);
 }
 
 constexpr int64_t kMaxPackGrid = 1 << 20;   // blocks a pool; they stride over more rows
@@ -1986,7 +1990,7 @@ int run_cluster(const void* keys, int dtype, int64_t S, int N, int C, int n_iter
       return st;
     if (iter_events) LKV_CHECK_HIP(hipEventRecord(reinterpret_cast<hipEvent_t>(iter_events[2 * it + 1]), s));
     if ((st = launch_scan_scatter(assign, S, N, C, w, list, last, it < kFirstRecord, s))) return st;
-    if ((st = launch_sum(keys, dtype, S, N, C, w, reps, reps, units_cap, !last, !last && dtype != LOUISKV_BF16, list,
+    if ((st = launch_sum(keys, dtype, S, N, C, w, reps, reps, units_cap, !last, !last && dtype != LOUISKV_BF16, track,
                          s)))
       return st;
   }

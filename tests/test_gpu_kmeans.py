@@ -187,6 +187,8 @@ def test_cluster_prefill_matches_oracle_end_to_end():
     (8, 20000, 1024, "ties"),            # few distinct keys and values: equal distances
     (8, 20011, 1000, "nonfinite"),       # NaN and infinite keys among the others
     (2, 16384, 8192, "clusters"),        # the most clusters the scatter scans in LDS
+    (2, 16400, 8200, "clusters"),        # more: the flagged clusters without a list, a wave each
+    (9, 9000, 8193, "overlapping"),      # the same, four clusters a wave in turn
     (3, 1024, 128, "clusters"),          # the largest clustering that one block a slice runs
     (2, 1025, 128, "clusters"),          # one key, one cluster more: a launch per stage
     (2, 1024, 129, "clusters"),
