@@ -551,6 +551,7 @@ def _lru_model(buf_row, slot_step, rows, step):
 
 @pytest.mark.parametrize("C,filled", [
     (65536, 65536), (65536, 40000), (65535, 65400),   # 64 slots a thread; the last one's run is not whole
+    (65536, 0), (65535, 900),                         # (nearly) empty, as at a generation's first fires
     (33000, 33000), (20001, 20001), (9000, 8900), (700, 700)])   # 64, 32, 16 and 8 slots a thread
 def test_cache_plan_pieces(C, filled):
     """The LRU plan on a given cache state, against the policy written out:
