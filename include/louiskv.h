@@ -470,11 +470,21 @@ int louiskv_sparse_decode_attn_rows(const void* q, int32_t dtype, int64_t n_slic
  *            Its first (4 * n_slices + 1) * 64 int32 words are those
  *            counters and flags; the last of them is a status word that a
  *            block sets to 1 if its wait for a selection ever gave up (after
- *            about a million polls, which a correct launch never reaches;
+ *            about a million polls, which a call that keeps the rule under
+ *            Concurrency never reaches;
  *            the environment variable LOUISKV_STEP_SPIN_LIMIT lowers that
  *            bound, for tests of this path), and that the library never
  *            clears.  The outputs of a step that set it are undefined and
  *            the workspace must be zeroed before its next use.
+ *
+ * Concurrency  One-launch calls (bf16) whose groups may fire must not run at
+ *            the same time on one GPU (several streams, threads, processes or
+ *            graphs), whatever workspaces they use: the blocks of a fired
+ *            slice wait for each other, and two such launches can each hold
+ *            compute units that the other's blocks need until the waits give
+ *            up.  Other kernels may run beside one.  Callers that need
+ *            concurrent steps use the calls that this one replaces, whose
+ *            blocks wait for nothing.
  */
 size_t louiskv_decode_step_workspace_size(int64_t n_slices, int32_t dtype, int32_t group_size,
                                           int32_t units_cap, int32_t budget, int32_t window);

@@ -2907,19 +2907,22 @@ void attn_mfma_kernel(const uint16_t* __restrict__ q, int n_kv_heads, float scal
 // every block merges a share of the slice's outputs (attn_merge_share).
 //
 // So the blocks of a slice wait for words of each other.  At a fire those waits
-// end once every block of the slice has started, which holds when the whole
-// grid is resident at once (the launch gives the chip at most one block per
-// compute unit) and also when it is not, since workgroups are dispatched in
-// index order and a slice's blocks are consecutive, so that complete slices
-// drain and make room for the one that is cut.  They are bounded all the same:
-// past spin_limit polls (kStepSpinLimit, or fewer from
+// end once every block of the slice has started.  That holds for one such
+// launch at a time: it has at most one block per compute unit, so all of them
+// are resident as soon as kernels of other kinds that hold units have drained.
+// It does not hold for two fired steps at once on one GPU (two streams, two
+// processes): each can hold compute units that blocks of the other's slices
+// need, and none of them leaves.  Callers must not run them so (the stage
+// calls and the two-launch step wait for nothing).  The waits are bounded all
+// the same: past spin_limit polls (kStepSpinLimit, or fewer from
 // LOUISKV_STEP_SPIN_LIMIT, for tests of this path) a block records a time-out
 // in the status word and goes on; its row-list entries are clamped into the
 // pool, so that such a step reads no memory out of bounds.  Without a fire a
 // block that has waited for a while asks whether all of its slice have started
 // and leaves its share of the merge to the last one to start if not
-// (attn_merge_share), so that steps on several streams, each holding compute
-// units that the other's blocks need, do not wait for each other.
+// (attn_merge_share), so that steps that do not fire, on several streams, each
+// holding compute units that the other's blocks need, do not wait for each
+// other.
 //
 // Measured, 8 slices (one layer) of 4 heads, 1024 units and 2048 rows: 18.2 ->
 // 15.2 us a step, fires and the steps between them together; 32 slices with

@@ -23,7 +23,10 @@ paper's Algorithm 1:
 
 A call over few slices (a layer at a time, the group views below) runs the
 whole step as louiskv_decode_step: the same stages in one launch (bf16; two
-in float32) that spreads each slice over many blocks.
+in float32) that spreads each slice over many blocks.  Such bf16 steps of
+several engines must not run at the same time on one GPU (their blocks wait
+for each other when a group fires); engines that step concurrently take
+fused_step=False.  step_timed_out() reports a wait that gave up.
 
 With the pool in device memory the engine runs zero-copy by default:
 louiskv_retrieve_rows keeps KV_critical as a list of pool rows and
@@ -279,6 +282,25 @@ class LouisKVEngine:
         if self.seg_state is None:
             return False
         return bool((self.seg_state[:, 4] != 0).any())
+
+    def step_timed_out(self) -> bool:
+        """True if a one-launch decode step of this engine (or of its group
+        views) gave up waiting since the last call: the outputs of that step
+        and of the steps since are undefined.  Clears the workspaces it finds
+        so, and later steps are right again (after a fresh prefill, since the
+        steps in doubt moved the state).  Reads a word per workspace, a
+        device-to-host copy."""
+        h = self.cfg.n_kv_heads
+        found = False
+        for n, ws in [(self.cfg.n_slices, self.ws_step)] + [(h * n, w) for n, w in
+                                                            getattr(self, "_view_ws_step", {}).items()]:
+            if ws is None:
+                continue
+            at = 256 * 4 * n   # the status word, after the arrival counters (256 bytes apart)
+            if int(ws[at:at + 4].view(torch.int32)) != 0:
+                ws.zero_()
+                found = True
+        return found
 
     def _use_fused_step(self) -> bool:
         if not self._fused_ok or self.fused_step is False:

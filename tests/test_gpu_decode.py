@@ -1353,6 +1353,37 @@ def test_decode_step_wait_is_bounded(monkeypatch):
         assert int(b.ws_step[:status_at + 4].view(torch.int32).abs().sum()) == 0, t
 
 
+def test_step_time_out_is_reported_and_cleared(monkeypatch):
+    """A one-launch step whose wait gave up (a one-poll bound on a fired first
+    step) is reported by the engine, for its own steps and its group views',
+    once; the report clears the workspaces, so that steps after a fresh prefill
+    equal the stage calls."""
+    from paper_2510_11292_amd.engine import LouisKVEngine, config_from_workload
+    wl = synth.get_workload("si-lo-16k").replace(prompt_len=8192, n_clusters=1024, budget=2048, name="si-lo-16k")
+    steps, groups = 4, 2
+    data = synth.make_slices(wl, DEV, groups=[(0, l) for l in range(groups)], gen_len=steps)
+    cfg = config_from_workload(wl, n_groups=groups, gen_len=steps)
+    a = LouisKVEngine(cfg, torch.bfloat16, DEV, out_dtype=torch.float32, fused_step=False)
+    b = LouisKVEngine(cfg, torch.bfloat16, DEV, out_dtype=torch.float32, fused_step=True)
+    assert not a.step_timed_out()
+    for by_layer in (False, True):
+        run = b.step_layer_by_layer if by_layer else b.step
+        for e in (a, b):
+            e.prefill(data.prompt_keys, data.prompt_values, data.init_idx)
+        monkeypatch.setenv("LOUISKV_STEP_SPIN_LIMIT", "1")
+        run(data.queries[0], data.gen_keys[0], data.gen_values[0])
+        torch.cuda.synchronize()
+        monkeypatch.delenv("LOUISKV_STEP_SPIN_LIMIT")
+        assert b.step_timed_out() and not b.step_timed_out()
+        b.prefill(data.prompt_keys, data.prompt_values, data.init_idx)
+        for t in range(steps):
+            a.step(data.queries[t], data.gen_keys[t], data.gen_values[t])
+            run(data.queries[t], data.gen_keys[t], data.gen_values[t])
+            assert torch.equal(a.n_sel, b.n_sel) and torch.equal(a.q_ref, b.q_ref), (by_layer, t)
+            assert (a.out - b.out).abs().max().item() <= 1e-5 * max(1.0, a.out.abs().max().item()), (by_layer, t)
+        assert not b.step_timed_out()
+
+
 @pytest.mark.parametrize("case", ["host-delta", "fused-device"])
 def test_layer_by_layer_step_graphs_match_eager(case):
     """The group-by-group decode captured as one HIP graph per step (as the
