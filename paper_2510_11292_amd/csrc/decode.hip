@@ -2395,14 +2395,16 @@ __device__ __forceinline__ void attn_hand(const float (*s_m)[G], const float (*s
 // the word.  All started: it goes on waiting, for words that are then sure to
 // come.  Otherwise it leaves its bit there for the last block to start, which
 // merges its share, and returns.  s_late: zero, a barrier before this call.
+// Without patience (a test's setting) the block does not wait at all: `left`, in
+// the thread that counts the arrival, says that its bit went there with it.
 // Returns the polls, for the caller's bound.
 constexpr int kStepPatience = 64;
 
 template <int G, int NW>
 __device__ __forceinline__ int attn_merge_share(int tid, int64_t s, int chunk, int n_chunks, float* __restrict__ part,
                                                 void* __restrict__ out, int out_bf16, float* __restrict__ lse_out,
-                                                int spin_limit, uint64_t* met, int patience, int* s_late,
-                                                float4* s_hand) {
+                                                int spin_limit, uint64_t* met, int patience, bool left,
+                                                int* s_late, float4* s_hand) {
   constexpr int kPairs = G * (kHeadDim / 2);
   float* ps = part + (size_t)s * n_chunks * kPairs * 4;
   int at_once = NW * 64, P = kPairs;                       // pairs merged at once; the share's pairs
@@ -2439,7 +2441,7 @@ __device__ __forceinline__ int attn_merge_share(int tid, int64_t s, int chunk, i
                                 __uint_as_float((uint32_t)y), __uint_as_float((uint32_t)(y >> 32)));
     };
     const bool ask = met && r == 0;                        // later rounds: every block has handed words
-    const bool all = collect(ask ? patience : spin_limit);
+    const bool all = (!ask || patience > 0) && collect(ask ? patience : spin_limit);
     if (ask && !all && lane == 0) *s_late = 1;
     if (r > 0) __syncthreads();                            // the last round's sums are done
     stage();
@@ -2449,9 +2451,12 @@ __device__ __forceinline__ int attn_merge_share(int tid, int64_t s, int chunk, i
       if (tid == (NW - 2) * 64) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this block's own arrival is counted
         const uint64_t bit = 1ull << chunk;
-        const int n = (int)(__hip_atomic_fetch_or(met, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 32);
-        const bool leave = n > 0 && n < n_chunks;          // zero again: counted to the end and reset
-        if (!leave) __hip_atomic_fetch_and(met, ~bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        bool leave = left;
+        if (patience > 0) {
+          const int n = (int)(__hip_atomic_fetch_or(met, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 32);
+          leave = n > 0 && n < n_chunks;                   // zero again: counted to the end and reset
+          if (!leave) __hip_atomic_fetch_and(met, ~bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
         *s_late = leave ? 2 : 1;
       }
       __syncthreads();
@@ -2972,7 +2977,7 @@ struct FusedStep {
   int32_t *hand_rows, *hand_nsel;   // [n_slices][budget], [n_slices][kStepMaxBlocks]
   uint64_t* met;                    // per slice, kStepSyncStride ints apart: arrivals << 32 | shares left
   int32_t *grp_counter, *status;
-  int n_blk, chunk_rows, n_pad, spin_limit;
+  int n_blk, chunk_rows, n_pad, spin_limit, patience;
   int local_start, n_local;
   float* part;
   void* out;
@@ -3164,7 +3169,8 @@ void step_fused_kernel(const FusedStep a) {
   constexpr int kMetThread = (NW - 2) * 64;
   uint64_t* met = fire || nb == 1 ? nullptr : a.met + s * (kStepSyncStride / 2);
   uint64_t met_old = 0;
-  if (met && tid == kMetThread) met_old = __hip_atomic_fetch_add(met, 1ull << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const uint64_t arrival = (1ull << 32) + (a.patience > 0 ? 0 : 1ull << c);
+  if (met && tid == kMetThread) met_old = __hip_atomic_fetch_add(met, arrival, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   for (int t = w; t < n_tiles; t += kInFlight * NW) {
     if (t != w) {
 #pragma unroll
@@ -3191,25 +3197,25 @@ void step_fused_kernel(const FusedStep a) {
                 s, lane);
   attn_hand<G, NW>(s_m, s_l, s_acc, tid, s, c, nb, a.part, a.out, a.out_bf16, a.lse_out);
   if (nb > 1) {
-    auto merge = [&](int share, uint64_t* ask) {
+    auto merge = [&](int share, uint64_t* ask, bool left) {
       const int limit = fire ? a.spin_limit : kStepSpinLimit;
       const int polls = attn_merge_share<G, NW>(tid, s, share, nb, a.part, a.out, a.out_bf16, a.lse_out, limit, ask,
-                                                min(a.spin_limit, kStepPatience), &s_late,
-                                                reinterpret_cast<float4*>(s_p));
+                                                a.patience, left, &s_late, reinterpret_cast<float4*>(s_p));
       if (polls >= limit && lane == 0) __hip_atomic_store(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
+    bool left = false;
     if (met && tid == kMetThread) {
       const bool last = (int)(met_old >> 32) == nb - 1;
       s_left = last ? (uint32_t)met_old : 0;   // shares left to the last block to start
-      if (last)
-        __hip_atomic_fetch_sub(met, ((uint64_t)nb << 32) | (uint32_t)met_old, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
+      left = !last && a.patience <= 0;
+      if (last)   // back to zero; a bit that is set from here on is taken back by its block
+        __hip_atomic_fetch_sub(met, met_old + arrival, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    merge(c, met);
+    merge(c, met, left);
     if (met) {
       for (uint32_t left = s_left; left; left &= left - 1) {
         __syncthreads();
-        merge(__builtin_ctz(left), nullptr);
+        merge(__builtin_ctz(left), nullptr, false);
       }
     }
   }
@@ -3945,12 +3951,14 @@ struct StepLayout {
 };
 
 // Polls of the one-launch step's bounded wait: kStepSpinLimit, or fewer from
-// LOUISKV_STEP_SPIN_LIMIT (tests of the time-out path).
+// LOUISKV_STEP_SPIN_LIMIT (tests of the time-out path; 0, for tests of the
+// shares left: one poll, and no patience at all).
 int step_spin_limit() {
   const char* e = getenv("LOUISKV_STEP_SPIN_LIMIT");
   if (e && *e) {
-    const long v = strtol(e, nullptr, 10);
-    if (v >= 1 && v <= kStepSpinLimit) return (int)v;
+    char* end;
+    const long v = strtol(e, &end, 10);
+    if (end != e && v >= 0 && v <= kStepSpinLimit) return (int)v;
   }
   return kStepSpinLimit;
 }
@@ -4159,7 +4167,9 @@ int decode_step_impl(const void* q, void* q_ref, int32_t dtype, int64_t n_groups
     fa.n_blk = nb;
     fa.chunk_rows = chunk_rows;
     fa.n_pad = n_pad;
-    fa.spin_limit = step_spin_limit();
+    const int polls = step_spin_limit();
+    fa.spin_limit = std::max(polls, 1);
+    fa.patience = std::min(polls, kStepPatience);
     fa.local_start = local_start;
     fa.n_local = n_local;
     fa.part = reinterpret_cast<float*>(ws + lay.hand_part);
