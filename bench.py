@@ -49,6 +49,10 @@ ASSIGN_SOURCES = [os.path.join(ROOT, "paper_2510_11292_amd", "csrc", f) for f in
 # the assignments that sweep every centroid whatever the keys (later ones
 # evaluate the centroids that moved alone, so they have no fixed FLOP count)
 FULL_SWEEPS = 2
+# bf16 prompts of at most these tokens and clusters are clustered in one launch
+# unless iteration events are asked for: their assignments are timed in a pass
+# of their own
+ONE_LAUNCH_TOKENS, ONE_LAUNCH_CLUSTERS = 1024, 128
 ATTN_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "attention_traffic_li-so-32k.md")
 ATTN_SOURCES = [os.path.join(ROOT, "paper_2510_11292_amd", "csrc", f) for f in ("decode.hip", "common.h")]
 
@@ -449,10 +453,15 @@ def time_pipelined_prefill(eng, data, chunk: int, copy_engine: bool, reps: int =
     return total / reps
 
 
+def one_launch_clustering(wl) -> bool:
+    return wl.dtype == "bf16" and wl.prompt_len <= ONE_LAUNCH_TOKENS and wl.n_clusters <= ONE_LAUNCH_CLUSTERS
+
+
 def workload_pass(name: str, dev: str, layer_steps: int = 512) -> dict:
     """One stated timed pass of a workload other than the headline one, after
-    one untimed pass: the clustering (keys/s and the assignment kernel's MFMA
-    fraction, from HIP events on its stream), the decode loop as one HIP graph
+    one untimed pass: the clustering (keys/s; the assignment kernel's MFMA
+    fraction, from HIP events on its stream, of the untimed pass where a prompt
+    is short enough for events to change its route), the decode loop as one HIP graph
     (steps/s), the attention kernel on the final state (GB/s and HBM
     fraction), the last `layer_steps` decode steps group by group (steps/s)
     and, for a host-resident pool, the host-link rates of the same run."""
@@ -472,6 +481,7 @@ def workload_pass(name: str, dev: str, layer_steps: int = 512) -> dict:
     for evs in ev:
         for e in evs:
             e.record()
+    timed_ev = 0 if one_launch_clustering(wl) else 1   # the pass whose assignments are timed
     ph = [[torch.cuda.Event(enable_timing=True) for _ in range(4)] for _ in range(2)]
 
     def decode_all():
@@ -501,7 +511,8 @@ def workload_pass(name: str, dev: str, layer_steps: int = 512) -> dict:
         decode_all()
     for i in range(2):
         ph[i][0].record()
-        eng.prefill(data.prompt_keys, data.prompt_values, data.init_idx, iter_events=ev[i], pack_event=ph[i][3])
+        eng.prefill(data.prompt_keys, data.prompt_values, data.init_idx, iter_events=ev[i] if i <= timed_ev else None,
+                    pack_event=ph[i][3])
         ph[i][1].record()
         graph.replay()
         ph[i][2].record()
@@ -510,7 +521,7 @@ def workload_pass(name: str, dev: str, layer_steps: int = 512) -> dict:
     t_pre = ph[1][0].elapsed_time(ph[1][1]) / 1e3
     t_dec = ph[1][1].elapsed_time(ph[1][2]) / 1e3
     full = min(FULL_SWEEPS, iters)
-    t_assign = sum(ev[1][2 * k].elapsed_time(ev[1][2 * k + 1]) for k in range(full)) / full / 1e3
+    t_assign = sum(ev[timed_ev][2 * k].elapsed_time(ev[timed_ev][2 * k + 1]) for k in range(full)) / full / 1e3
     flops = 2.0 * wl.prompt_len * wl.n_clusters * wl.head_dim * wl.n_slices
     peak = PEAK_BF16_TFLOPS if wl.dtype == "bf16" else PEAK_FP32_TFLOPS
     t_attn, attn_bytes = time_attention(eng, wl)
@@ -643,6 +654,9 @@ def main() -> int:
         torch.cuda.synchronize()
 
     fires = []
+    if one_launch_clustering(wl):
+        for i in range(args.warmup, total):
+            eng.prefill(data.prompt_keys, data.prompt_values, data.init_idx, iter_events=assign_ev[i])
     torch.cuda.synchronize()
     wall0 = None
     for i in range(total):
@@ -650,8 +664,8 @@ def main() -> int:
             torch.cuda.synchronize()
             wall0 = time.perf_counter()
         ph[i][0].record()
-        eng.prefill(data.prompt_keys, data.prompt_values, data.init_idx, iter_events=assign_ev[i],
-                    pack_event=ph[i][3])
+        eng.prefill(data.prompt_keys, data.prompt_values, data.init_idx,
+                    iter_events=None if one_launch_clustering(wl) else assign_ev[i], pack_event=ph[i][3])
         ph[i][1].record()
         if graph is not None:
             graph.replay()

@@ -154,7 +154,10 @@ size_t louiskv_cluster_prefill_workspace_size(int64_t n_slices, int32_t n_tokens
  *             `values`; v_pool requires values).  pool_on_host: see Pointers.
  * iter_events NULL or an array of 2*n_iters hipEvent_t recorded on `stream`
  *             just before and after each iteration's assignment, for
- *             callers that time it.
+ *             callers that time it.  Given, they select a launch per stage
+ *             also for short prompts (bf16, up to 1024 tokens and 128
+ *             clusters), which are otherwise clustered in one launch with
+ *             the same results, two to six times as fast.
  * Requires 1 <= n_clusters <= n_tokens, n_clusters <= units_cap, n_iters >= 1,
  * pool_rows >= n_tokens when a pool is given.
  */
