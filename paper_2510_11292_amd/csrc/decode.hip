@@ -3963,6 +3963,16 @@ int step_spin_limit() {
   return kStepSpinLimit;
 }
 
+// Blocks a slice of the one-launch step has at most: one per kStepAttnRows rows
+// (a 16-row tile per wave), kStepMaxBlocks, and one block per compute unit over
+// the launch (kStepBlocks: gfx950 has 256).
+constexpr int64_t kStepBlocks = 256;
+int step_max_blocks(int64_t S, int budget, int window, int64_t cus = kStepBlocks) {
+  return (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)kStepMaxBlocks,
+                                                      (int64_t)step_attn_chunks(budget, window),
+                                                      std::min(cus, kStepBlocks) / S}));
+}
+
 // Workspace of a decode step: the arrival counters (zero between calls; the
 // one-launch step keeps its counters and a status word kStepSyncStride ints
 // apart, the two-launch step its two counters per slice packed at the start),
@@ -3994,8 +4004,9 @@ StepLayout step_layout(int64_t S, int dtype, int G, int units_cap, int budget, i
     used = base;
     L.hand_logits = take((size_t)S * units_cap * G * sizeof(double));
     L.hand_rows = take((size_t)S * ((size_t)std::max(budget, 1) + kStepMaxBlocks) * sizeof(int32_t));
-    // (a0, a1, m, l) per block, head and pair of dims
-    L.hand_part = take((size_t)S * kStepMaxBlocks * G * (kHeadDim / 2) * 4 * sizeof(float));
+    // (a0, a1, m, l) per block, head and pair of dims, where a slice has several
+    const size_t nb = step_max_blocks(S, budget, window);
+    L.hand_part = take(nb > 1 ? (size_t)S * nb * G * (kHeadDim / 2) * 4 * sizeof(float) : 0);
     return align_up(used, 256);
   };
   auto carve_scratch = [&](size_t base) {
@@ -4110,16 +4121,12 @@ int decode_step_impl(const void* q, void* q_ref, int32_t dtype, int64_t n_groups
   const double scale = 1.0 / sqrt((double)kHeadDim);
   hipStream_t s = as_stream(stream);
   if (!cache && dtype == LOUISKV_BF16) {   // the whole step in one launch
-    // blocks per slice: one per kStepAttnRows rows (a 16-row tile per wave),
-    // at most kStepMaxBlocks, and at most one block per compute unit over the
-    // launch (a block of the selection's register footprint fills one), so
-    // that every block can be resident at once whenever blocks wait (two or
-    // more per slice; a slice's only block never waits)
+    // at most one block per compute unit over the launch (a block of the
+    // selection's register footprint fills one), so that every block can be
+    // resident at once whenever blocks wait (two or more per slice; a slice's
+    // only block never waits)
     const int cus = device_cu_count();
-    const int64_t step_cus = cus > 0 ? cus : 256;
-    const int nb = (int)std::max<int64_t>(
-        1, std::min<int64_t>({(int64_t)kStepMaxBlocks, (int64_t)step_attn_chunks(budget, window),
-                              step_cus / n_slices}));
+    const int nb = step_max_blocks(n_slices, budget, window, cus > 0 ? cus : kStepBlocks);
     const int64_t total_rows = (int64_t)budget + window;
     const int chunk_rows = (int)(((total_rows + nb - 1) / nb + 15) / 16 * 16);
     if (n_slices * nb > INT32_MAX) return fail(LOUISKV_ERR_SHAPE, "problem too large for one launch");

@@ -267,12 +267,14 @@ class LouisKVEngine:
                              "zero-copy retrieval over a device pool or an LRU cache of pool rows")
         self.fused_step = fused_step
         self.ws_step = None
-        if self._fused_ok and fused_step is not False:
+        if self._use_fused_step():
+            # calls over more slices take the stage calls: their group views
+            # get workspaces of their own size
             size = (L.decode_step_cached_workspace_size if self._fused_cached else L.decode_step_workspace_size)
             self.ws_step = torch.zeros(size(S, dc, g, cap, cfg.budget, cfg.window), **u8)
-            if self._fused_cached:
-                # the selected pool rows, the plan's input
-                self.sel_rows_step = torch.zeros(S, cfg.budget, **i32)
+        if self._fused_cached and fused_step is not False:
+            # the selected pool rows, the plan's input
+            self.sel_rows_step = torch.zeros(S, cfg.budget, **i32)
         self.t = 0
 
     def segment_overflow(self) -> bool:
@@ -385,7 +387,7 @@ class LouisKVEngine:
         v.ws_attn = self._view_ws_attn[n]
         # the fused step's workspace (counters zero between calls) sized for
         # the view, shared by the views of n groups, which run one at a time
-        if self.ws_step is not None:
+        if self._fused_ok and self.fused_step is not False:
             if not hasattr(self, "_view_ws_step"):
                 self._view_ws_step = {}
             if n not in self._view_ws_step:

@@ -224,6 +224,8 @@ def test_workspace_sizes_are_positive(lib):
     step = lib.louiskv_decode_step_workspace_size(S, 1, G, cap, budget, window)
     assert step >= 256 * (4 * S + 1) + S * cap * G * 8 + S * 32 * G * 8 + S * 32 * G * 130 * 4
     assert lib.louiskv_decode_step_workspace_size(S, 1, 9, cap, budget, window) == 0
+    # 256 slices have one block each, which hands no partials (32 blocks' were 67 MB)
+    assert lib.louiskv_decode_step_workspace_size(256, 1, 8, 100, 256, 128) < 16 << 20
 
 
 def test_bench_refuses_more_than_one_gpu():

@@ -1357,6 +1357,21 @@ def test_step_workspace_is_shared_by_other_sizes():
             assert (a.lse - b.lse).abs().max().item() <= 1e-5, (t, i)
 
 
+def test_step_workspace_only_where_used():
+    """An engine whose calls take the stage calls (more slices than a fused step
+    is used for) holds no step workspace; its group views, which step fused, do."""
+    from paper_2510_11292_amd.engine import FUSED_STEP_MAX_SLICES, LouisKVEngine, config_from_workload
+    wl = synth.get_workload("si-lo-16k").replace(prompt_len=256, n_clusters=16, budget=64, name="si-lo-16k")
+    groups = FUSED_STEP_MAX_SLICES // wl.n_kv_heads + 1
+    cfg = config_from_workload(wl, n_groups=groups, gen_len=8)
+    for kw in (dict(), dict(pool_on_host=True, cache_rows=128)):
+        e = LouisKVEngine(cfg, torch.bfloat16, DEV, **kw)
+        v = e.group_view(0)
+        assert not e._use_fused_step() and e.ws_step is None
+        assert v._use_fused_step() and int(v.ws_step.count_nonzero()) == 0
+        assert LouisKVEngine(cfg, torch.bfloat16, DEV, fused_step=True, **kw).ws_step is not None
+
+
 def test_decode_step_wait_is_bounded(monkeypatch):
     """The one-launch step's wait for a fired slice's selection is bounded:
     with the bound forced down to one poll (LOUISKV_STEP_SPIN_LIMIT=1) the
