@@ -405,6 +405,7 @@ struct AssignArgs {
   const int32_t *ndirty, *dmap, *dlist;   // the clusters recomputed since the last assignment
   int32_t* recorded;       // per slice, two entries used in turn: the last assignment left `best` and `sec`
   int turn;
+  int part_percent, record_percent;
   const uint4* cfrag;      // their operands, compacted in ascending order
   const float* ccnorm;
   int32_t *fail, *nfail;   // out: keys left to assign_rest_kernel
@@ -424,9 +425,17 @@ __device__ __forceinline__ void move_key(const AssignArgs& a, size_t row, int fr
 // Sweep over the recomputed clusters alone up to this share of all of them
 // (percent); above, the full sweep costs no more and leaves no key over.
 // Above the second share the next one will most likely be full too, and a full
-// sweep that records takes 5-12% longer, so it records nothing.
-constexpr int kPartPercent = 80;
-constexpr int kRecordPercent = 95;
+// sweep that records takes 5-12% longer, so it records nothing.  The shares fall
+// by about ten points an iteration, by more at first where the clusters are well
+// apart.  In calls of few (key, centroid) pairs a sweep is short against the
+// launch for the left-over keys, and both lines lie lower: a whole call at 70
+// and 82 against 80 and 95, keys with noise 0.65 around their centres: 1002 us
+// against 1035 for 16 slices of 20480 keys in 640 clusters, 858 against 876 for
+// 10 of 25600 in 800, 962 against 978 for 8 of 32768 in 1024, the same for 40 of
+// 20480 in 640; noise 0.45, 64 of 32768 in 1024: 5.01 ms against 4.88.
+constexpr int kPartPercent = 80, kPartPercentFew = 70;
+constexpr int kRecordPercent = 95, kRecordPercentFew = 82;
+constexpr double kFewPairs = 1e9;
 
 // Modes of the bf16 assignment: on its own or first of a clustering; later
 // iterations, which start from the last assignment (kTrack in the kernel); and
@@ -489,8 +498,8 @@ void assign_bf16_kernel(const AssignArgs a) {
   if constexpr (kRecord) {
     const int nd = __builtin_amdgcn_readfirstlane(a.ndirty[slice]);
     const int had = __builtin_amdgcn_readfirstlane(a.recorded[2 * slice + (a.turn ^ 1)]);
-    some = had && nd * 100 <= n_clusters * kPartPercent;
-    record = some || nd * 100 <= n_clusters * kRecordPercent;
+    some = had && nd * 100 <= n_clusters * a.part_percent;
+    record = some || nd * 100 <= n_clusters * a.record_percent;
     if (kb == 0 && tid == 0) a.recorded[2 * slice + a.turn] = record ? 1 : 0;
     if (some) {
       if (nd == 0) return;                        // no centroid changed, so no key does
@@ -1347,7 +1356,9 @@ void finalize_kernel(const int32_t* __restrict__ members, const int32_t* __restr
 // in 32: 445 -> 181 us (sixteen waves; eight took 74 and 202).  It serves what
 // fits one block's registers (1024 keys) and a few operand tiles; a block per
 // slice is also fastest where slices are few, as the launches it replaces are
-// latency alone there.
+// latency alone there, and at its limits: 1024 keys in 128 clusters, 1, 8, 64,
+// 256 and 512 slices: 218 -> 157, 229 -> 166, 281 -> 178, 499 -> 209 and 853 ->
+// 382 us; 512 keys in 128: 202 -> 102, .., 556 -> 247.
 struct SmallArgs {
   const uint16_t* keys;
   const int32_t* init_idx;
@@ -1689,13 +1700,23 @@ bool scatter_in_lds(int C) { return (size_t)C * 8 <= kMaxHistLds; }
 // Assignments record (and sweep the recomputed clusters alone) from this
 // iteration on, where nearly every cluster moves before; a call of fewer
 // (key, centroid) pairs does not: its sweep is short, and the launch for the
-// left-over keys (8-10 us) takes back what the shorter sweeps give (8 slices of
-// 20011 keys, 625 clusters, 1.0e8 pairs: 707 us without, 735 with; 8 of 32768
-// keys, 1024 clusters, 2.7e8 pairs: 946 without, 824 with).
+// left-over keys (8-10 us) takes back what the shorter sweeps give.  A whole
+// call with against without, by the noise of the keys around their centres:
+//                                     pairs    0.3    0.45    0.65    1.0
+//    8 slices of 20011 keys in  625   1.0e8   0.93    0.99    1.05   1.02
+//   16           16640          520   1.4e8   0.92    1.00    1.05   1.01
+//   16           20480          640   2.1e8   0.92    1.01    1.04   1.01
+//   10           25600          800   2.0e8   0.91    0.99    1.03   1.00
+//   24           20480          640   3.1e8   0.90    0.96    1.00   0.99
+//    8           32768         1024   2.7e8   0.88    0.97    1.01   0.98
+//   40           20480          640   5.2e8   0.88    0.94    0.99   0.98
+//   64           32768         1024   2.1e9   0.79    0.86    0.95   0.93
+// The line lies where the gain on keys well apart begins to outweigh what
+// overlapping ones lose.
 // Nor does one of few clusters: what recording costs is per key, what it saves
-// per (key, centroid) pair (a whole call with against without: 10% longer at
-// 166 clusters, 256 slices of 4000 keys; 2% longer at 520, 40 of 25000; 5-8%
-// shorter at 944 and 1041).
+// per (key, centroid) pair (10% longer at 166 clusters, 256 slices of 4000 keys;
+// 2% longer at 520, 40 of 25000 keys; 11, 6, 0 and 1% shorter at 520, 40 of
+// 16640, for the four noises above).
 constexpr int kFirstRecord = 2;
 constexpr double kRecordPairs = 1.5e8;
 constexpr int kRecordClusters = 640;
@@ -1800,6 +1821,9 @@ int launch_assign(const void* keys, int dtype, int64_t S, int N, int C, const Ws
     a.ndirty = w.ndirty;
     a.recorded = w.recorded;
     a.turn = it & 1;
+    const bool few = (double)S * N * C < kFewPairs;
+    a.part_percent = few ? kPartPercentFew : kPartPercent;
+    a.record_percent = few ? kRecordPercentFew : kRecordPercent;
     a.dmap = w.dmap;
     a.dlist = w.dlist;
     a.cfrag = w.cfrag;

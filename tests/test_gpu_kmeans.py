@@ -183,6 +183,7 @@ def test_cluster_prefill_matches_oracle_end_to_end():
 @pytest.mark.parametrize("S,N,C,kind", [
     (8, 20011, 1000, "clusters"),        # ragged tokens and clusters; left-over keys 32 a block
     (8, 20011, 1000, "overlapping"),     # most clusters move on every iteration
+    (48, 20480, 1024, "overlapping"),    # 1e9 pairs: the later lines between full and partial sweeps
     (64, 2563, 960, "clusters"),         # many slices: left-over keys 64 a block
     (8, 20000, 1024, "ties"),            # few distinct keys and values: equal distances
     (8, 20011, 1000, "nonfinite"),       # NaN and infinite keys among the others
