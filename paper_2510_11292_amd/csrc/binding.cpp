@@ -7,7 +7,9 @@
 // step took 14 us of host time, and one of boundary-delimited segments, in
 // four calls, 51.  Here the parameter types are read off the ABI function and
 // each argument is converted in place:
-//   pointers   a tensor (must be contiguous), an address, or None (NULL)
+//   pointers   a tensor (must be contiguous) or None (NULL); an array of
+//              handles (void* const*) is passed by its address.  Numbers are
+//              refused where a tensor belongs: a kernel would read there
 //   stream     the last parameter(s): None (the current stream), a
 //              torch.cuda.Stream or a handle
 //   numbers    int, bool or float
@@ -48,7 +50,6 @@ void* to_pointer(PyObject* o) {
     if (!t.is_contiguous()) not_contiguous();
     return t.data_ptr();
   }
-  if (PyLong_Check(o)) return reinterpret_cast<void*>(PyLong_AsUnsignedLongLongMask(o));
   // anything else that behaves like a tensor
   PyObject* c = PyObject_CallMethod(o, "is_contiguous", nullptr);
   if (!c) throw PyError();
@@ -63,6 +64,10 @@ void* to_pointer(PyObject* o) {
   return reinterpret_cast<void*>(v);
 }
 
+void* to_array(PyObject* o) {
+  return o == Py_None ? nullptr : reinterpret_cast<void*>(to_int(o));
+}
+
 void* to_stream(PyObject* o) {
   if (o == Py_None) return c10::hip::getCurrentHIPStream().stream();
   if (PyLong_Check(o)) return reinterpret_cast<void*>(PyLong_AsUnsignedLongLongMask(o));
@@ -75,7 +80,9 @@ void* to_stream(PyObject* o) {
 
 template <class T>
 T convert(PyObject* o, bool stream) {
-  if constexpr (std::is_pointer_v<T>) {
+  if constexpr (std::is_same_v<T, void* const*>) {
+    return (T)to_array(o);
+  } else if constexpr (std::is_pointer_v<T>) {
     return (T)(stream ? to_stream(o) : to_pointer(o));
   } else if constexpr (std::is_floating_point_v<T>) {
     const double v = PyFloat_AsDouble(o);

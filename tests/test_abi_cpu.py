@@ -256,3 +256,15 @@ def test_native_binding_marshals_like_the_abi(lib):
         L.pack_pool(x.view(1, 4, 128), None, torch.zeros(1, 4, dtype=torch.int32), torch.zeros(1, 128, 4).mT, stream=0)
     with pytest.raises(L.LouisKVError, match="pool_rows"):    # status and text of a refused call
         L.pack_pool(x.view(1, 4, 128), None, torch.zeros(1, 4, dtype=torch.int32), torch.zeros(1, 3, 128), stream=0)
+
+
+def test_native_binding_refuses_numbers_for_tensors(lib):
+    """A number where a tensor belongs is refused, as by anything that takes
+    tensors, instead of being taken as an address that a kernel then reads."""
+    import torch
+    from paper_2510_11292_amd import louiskv as L
+    x = torch.zeros(1, 4, 128)
+    perm = torch.zeros(1, 4, dtype=torch.int32)
+    for args in ((x, None, 4096, x), (x, None, True, x), (x, 4096, perm, x)):
+        with pytest.raises(AttributeError):
+            L.pack_pool(*args, stream=0)
