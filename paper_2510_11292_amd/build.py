@@ -49,13 +49,16 @@ def build_binding() -> str:
 
     import torch
     from torch.utils import cpp_extension
+    # DT_RPATH (old tags): the library beside the binding comes before any
+    # other of its name on LD_LIBRARY_PATH
     torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
     tmp = BINDING + ".tmp"
     cmd = [shutil.which("g++") or "g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__",
            "-DUSE_ROCM", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", INCLUDE,
            *[x for p in cpp_extension.include_paths() for x in ("-I", p)], "-I", "/opt/rocm/include",
            "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "binding.cpp"), "-o", tmp, "-L", PKG, "-llouiskv",
-           "-L", torch_lib, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python", "-Wl,-rpath,$ORIGIN"]
+           "-L", torch_lib, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python", "-Wl,--disable-new-dtags",
+           "-Wl,-rpath,$ORIGIN"]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"g++ failed for binding.cpp:\n{r.stderr}")

@@ -13,7 +13,8 @@
 //   stream     the last parameter(s): None (the current stream), a
 //              torch.cuda.Stream or a handle
 //   numbers    int, bool or float
-// The status (or size) comes back as an int; the GIL is released for the call.
+// The status (or size) comes back as an int, text as a str; the GIL is released
+// for the call.
 #include <torch/csrc/autograd/python_variable.h>
 #include <c10/hip/HIPStream.h>
 
@@ -114,7 +115,8 @@ PyObject* call(R (*fn)(A...), PyObject* const* args, std::index_sequence<I...>) 
   Py_BEGIN_ALLOW_THREADS
   r = fn(std::get<I>(a)...);
   Py_END_ALLOW_THREADS
-  if constexpr (std::is_unsigned_v<R>) return PyLong_FromSize_t(r);
+  if constexpr (std::is_same_v<R, const char*>) return PyUnicode_FromString(r);
+  else if constexpr (std::is_unsigned_v<R>) return PyLong_FromSize_t(r);
   else return PyLong_FromLong(r);
 }
 
@@ -152,6 +154,9 @@ PyObject* window_info(PyObject*, PyObject* const* args, Py_ssize_t n) {
 
 PyMethodDef methods[] = {
     {"window_info", reinterpret_cast<PyCFunction>(&window_info), METH_FASTCALL, nullptr},
+    LKV_ENTRY(abi_version, 0),
+    LKV_ENTRY(status_str, 0),
+    LKV_ENTRY(last_error, 0),
     LKV_ENTRY(cluster_prefill_workspace_size, 0),
     LKV_ENTRY(cluster_prefill, 1),
     LKV_ENTRY(pack_pool, 1),

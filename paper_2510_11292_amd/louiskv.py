@@ -145,7 +145,9 @@ class LouisKVError(RuntimeError):
 
 
 def load_library(path: Optional[str] = None) -> ctypes.CDLL:
-    """Load (once) and return the library; raises if it has not been built."""
+    """The library for ctypes callers of its C ABI (loaded once; another build's
+    by path); raises if it has not been built.  The functions of this module
+    do not call through it: _native() does, into the in-tree library."""
     global _lib
     if _lib is not None and path is None:
         return _lib
@@ -182,8 +184,7 @@ def _native():
 
 def _check(status: int) -> None:
     if status != 0:
-        lib = load_library()
-        raise LouisKVError(status, lib.louiskv_last_error().decode())
+        raise LouisKVError(status, _native().last_error())   # the text of the library that ran the call
 
 
 def _dtype_code(t: torch.Tensor) -> int:
@@ -203,7 +204,7 @@ def _ws(workspace: Optional[torch.Tensor], device, size, *args):
 
 
 def abi_version() -> int:
-    return load_library().louiskv_abi_version()
+    return _native().abi_version()
 
 
 def window_info(step: int, window: int, seg_len: int):

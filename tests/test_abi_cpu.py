@@ -268,3 +268,20 @@ def test_native_binding_refuses_numbers_for_tensors(lib):
     for args in ((x, None, 4096, x), (x, None, True, x), (x, 4096, perm, x)):
         with pytest.raises(AttributeError):
             L.pack_pool(*args, stream=0)
+
+
+def test_calls_and_their_errors_use_the_library_beside_the_binding(lib, tmp_path):
+    """Status, text and version of a call come from the in-tree library, also
+    where another build of that name comes first on LD_LIBRARY_PATH."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    src = tmp_path / "other.c"
+    src.write_text("".join(f"int {n}(void) {{ return 77; }}\n" for n in declared_functions()))
+    subprocess.run(["gcc", "-shared", "-fPIC", "-o", str(tmp_path / "liblouiskv.so"), str(src)], check=True)
+    code = ("from paper_2510_11292_amd import louiskv as L\n"
+            "assert L.abi_version() == 1 and L._native().status_str(99) == 'unknown status'\n"
+            "try:\n    L.window_info(3, 0, 32)\n"
+            "except L.LouisKVError as e:\n    print(e.status, e)\n")
+    env = dict(os.environ, LD_LIBRARY_PATH=f"{tmp_path}:{os.environ.get('LD_LIBRARY_PATH', '')}")
+    r = subprocess.run([sys.executable, "-c", code], cwd=root, env=env, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr
+    assert "window=0 must be a positive multiple of seg_len=32" in r.stdout and "77" not in r.stdout, r.stdout
