@@ -2107,6 +2107,17 @@ constexpr int kAttnRowsBf16 = 128, kAttnRowsF32 = 64;
 constexpr int kAttnMinRows = kAttnRowsF32;   // sizes the workspace for either type
 constexpr int kAttnCoarseRows = 256;
 int attn_min_rows(int dtype) { return dtype == LOUISKV_BF16 ? kAttnRowsBf16 : kAttnRowsF32; }
+// Up to these rows a slice takes one block and no merge launch: a second pass
+// costs less than that launch, and many slices fill the chip anyway (us with one
+// block against chunks; 4 heads).  bf16, 200 and 256 rows: 8 slices 6.7 and 7.0
+// against 8.0 and 8.1, 200 slices 7.4 and 8.0 against 10.9 and 11.1 (300 rows, 8
+// slices: 8.4 against 7.9).  float32, 160 and 200 rows: 8 slices 8.0 and 9.0
+// against 7.9 and 8.0, 64 slices 8.1 and 9.1 against 8.3 and 8.4; 256 rows: 128
+// slices 10.6 against 10.8, 200 slices 12.7 against 18.5.
+constexpr int kAttnOneBlockRows = 160, kAttnOneBlockSlices = 128;
+int attn_one_block_rows(int dtype, int64_t S) {
+  return dtype == LOUISKV_BF16 || S >= kAttnOneBlockSlices ? kAttnCoarseRows : kAttnOneBlockRows;
+}
 // A fused decode step over few slices spreads each slice's rows over many
 // small blocks: kStepAttnRows rows per block of kStepAttnWaves waves.
 #ifndef LKV_STEP_ATTN_ROWS
@@ -2946,8 +2957,9 @@ constexpr int kStepSpinLimit = 1 << 20;
 // Counters of the fused step sit kStepSyncStride ints apart, each in a
 // 256-byte block of its own: atomics on one line serialise.
 constexpr int kStepSyncStride = 64;
-// Blocks per slice: at most the one-trip merge's chunk count.
-constexpr int kStepMaxBlocks = kMergeBatch;
+// Blocks per slice at most: more read the boundary inputs again and add chunks
+// to every merge (32 blocks a slice for 2176 rows were slower than 17).
+constexpr int kStepMaxBlocks = 32;
 static_assert(kStepMaxBlocks <= kMaxSelectParts && kStepMaxBlocks <= 32, "a selection part and a bit per block");
 // List entries a thread loads before it knows whether the group fired.
 constexpr int kStepListEarly = 2;
@@ -3862,9 +3874,10 @@ int sparse_decode_attn(const void* q, int32_t dtype, int64_t n_slices, int32_t n
   if (indexed && buf_rows > 0 && src_rows < 1) return fail(LOUISKV_ERR_SHAPE, "pool_rows=%lld", (long long)src_rows);
   const bool step_bf16 = step_sync && indexed && dtype == LOUISKV_BF16;
   int min_rows = attn_min_rows(dtype);
-  if (!step_sync && (!workspace || workspace_bytes < attn_ws_bytes(n_slices, group_size, buf_rows, window, indexed,
-                                                                   min_rows)))
-    min_rows = kAttnCoarseRows;   // what fewer partials need
+  if (!step_sync &&
+      ((int64_t)buf_rows + window <= attn_one_block_rows(dtype, n_slices) || !workspace ||
+       workspace_bytes < attn_ws_bytes(n_slices, group_size, buf_rows, window, indexed, min_rows)))
+    min_rows = kAttnCoarseRows;   // one block, or what fewer partials need
   const int n_chunks = step_bf16 ? step_attn_chunks(buf_rows, window)
                                  : attn_chunks(n_slices, buf_rows, window, indexed, min_rows);
   if ((int64_t)n_slices * n_chunks > INT32_MAX) return fail(LOUISKV_ERR_SHAPE, "problem too large for one launch");

@@ -419,7 +419,8 @@ def test_sparse_decode_attn_rows(dtype, odt, G, H, g, B, PR, W, nl, ls):
 @pytest.mark.parametrize("dtype,H,B,W", [
     (torch.bfloat16, 1, 2048, 1),     # 17 chunks of one slice: a second batch of the merge, ragged
     (torch.bfloat16, 1, 8192, 128),   # 65: a second lane round
-    (torch.float32, 1, 64, 1),        # two chunks
+    (torch.float32, 1, 64, 1),        # one block, although a second chunk would have a row
+    (torch.float32, 1, 160, 1),       # one row more than that: three chunks
     (torch.float32, 1, 4096, 64),     # 65 chunks
     (torch.bfloat16, 256, 300, 20)])  # one block per slice
 def test_split_kv_chunk_counts(dtype, H, B, W):
@@ -445,6 +446,46 @@ def test_split_kv_chunk_counts(dtype, H, B, W):
     if need:
         with pytest.raises(RuntimeError, match="workspace"):
             L.sparse_decode_attn_rows(q, H, kp, vp, rows, nsel, kl, vl, 0, W, out[1], None, workspace=ws[:need - 1])
+
+
+@pytest.mark.parametrize("dtype,S,rows,one", [
+    (torch.bfloat16, 8, 129, True), (torch.bfloat16, 8, 256, True), (torch.bfloat16, 200, 256, True),
+    (torch.bfloat16, 8, 257, None), (torch.float32, 8, 65, True), (torch.float32, 8, 160, True),
+    (torch.float32, 8, 161, False), (torch.float32, 127, 161, False), (torch.float32, 128, 256, True)])
+@pytest.mark.parametrize("indexed", [True, False])
+def test_few_rows_take_one_block(dtype, S, rows, one, indexed):
+    """A slice of few rows is one block's work also where the workspace holds
+    partials: bit for bit the call without a workspace, which has no other way
+    (one None: the call without one takes larger chunks and is refused).  Past
+    the line the chunks' sums are in another order."""
+    L = _L()
+    gen = _gen(rows)
+    W, g = 32, 4
+    B = rows - W
+    q = torch.randn(S, g, 128, generator=gen, device=DEV).to(dtype)
+    kp, vp = (torch.randn(S, B, 128, generator=gen, device=DEV).to(dtype) for _ in range(2))
+    kl, vl = (torch.randn(S, W, 128, generator=gen, device=DEV).to(dtype) for _ in range(2))
+    sel = torch.stack([torch.randperm(B, generator=gen, device=DEV) for _ in range(S)]).int()
+    nsel = torch.full((S,), B, device=DEV, dtype=torch.int32)
+    out = [torch.empty(S, g, 128, dtype=torch.float32, device=DEV) for _ in range(2)]
+    lse = [torch.empty(S, g, dtype=torch.float32, device=DEV) for _ in range(2)]
+    none = torch.empty(1, dtype=torch.uint8, device=DEV)
+
+    def call(i, **ws):
+        if indexed:
+            L.sparse_decode_attn_rows(q, 1, kp, vp, sel, nsel, kl, vl, 0, W, out[i], lse[i], **ws)
+        else:
+            L.sparse_decode_attn(q, 1, kp, vp, nsel, kl, vl, 0, W, out[i], lse[i], **ws)
+
+    call(0)
+    if one is None:
+        with pytest.raises(L.LouisKVError, match="workspace"):
+            call(1, workspace=none[:0])
+        return
+    call(1, workspace=none[:0])
+    same = torch.equal(out[0], out[1]) and torch.equal(lse[0], lse[1])
+    assert same == one
+    assert (out[0] - out[1]).abs().max().item() <= 2e-6
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
