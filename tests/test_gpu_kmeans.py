@@ -312,6 +312,7 @@ PIPELINE_CASES = [
     (torch.float32, 8, 4096, 64, 3, False, True),     # ragged last chunk (3, 3, 2)
     (torch.bfloat16, 10, 5003, 77, 4, True, True),    # host pool through the copy engines
     (torch.bfloat16, 10, 5003, 77, 4, True, False),   # host pool written by the pack kernel
+    (torch.bfloat16, 18, 32768, 32, 16, False, False),   # device pool: keys and values in one launch, then apart
     (torch.bfloat16, 4, 4096, 128, 1, False, True),   # one slice per chunk
     (torch.bfloat16, 4, 4096, 128, 8, True, True),    # one chunk holds every slice
 ]
