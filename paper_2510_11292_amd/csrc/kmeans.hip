@@ -1089,9 +1089,14 @@ void scatter_kernel(const int32_t* __restrict__ assign, const int32_t* __restric
 
 // Mean of a cluster's member keys, float64 sum; kSplit waves per (slice,
 // cluster).  A key row is read as 16-byte pieces: kLpr lanes per row, so one
-// wave load covers kRpl rows and kUnroll loads are in flight, the next batch's
-// member ids with them; each lane accumulates its dims in float64, the row
-// groups are summed across lanes and the waves' parts through LDS at the end.
+// wave load covers kRpl rows and kUnroll loads are in flight; each lane
+// accumulates its dims in float64, the row groups are summed across lanes and
+// the waves' parts through LDS at the end.  One wave a cluster loads 64 member
+// ids at a time, a lane each, and hands them out by shuffles; where waves share
+// a cluster each loads its batch's ids, the next batch's with the rows.  (One
+// wave with ids loaded per batch, eight rows unrolled in float32 and four
+// clusters a wave: 70000 clusters of 48 keys 494 us in float32 and 241 in bf16
+// against 383 and 222.)
 // One wave a cluster reads the rows at the rate HBM gives them once there are
 // clusters enough to fill the chip; below that the longest member list is the
 // kernel's time, and a block's waves share it.
@@ -1131,7 +1136,7 @@ void centroid_update_kernel(const UpdateArgs<T> a) {
   constexpr int kDims = 16 / sizeof(T);          // dims per 16-byte piece (8 bf16, 4 fp32)
   constexpr int kLpr = kHeadDim / kDims;         // lanes per row
   constexpr int kRpl = kWave / kLpr;             // rows per wave load
-  constexpr int kUnroll = sizeof(T) == 2 ? 4 : 8;
+  constexpr int kUnroll = sizeof(T) == 2 || kSplit == 1 ? 4 : 8;
   constexpr int kBatch = kRpl * kUnroll;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t s = blockIdx.x / a.blocks_per_slice;
@@ -1179,28 +1184,47 @@ void centroid_update_kernel(const UpdateArgs<T> a) {
     double acc[kDims];
 #pragma unroll
     for (int d = 0; d < kDims; ++d) acc[d] = 0.0;
-    int tok[kUnroll];
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      const int r = part * kBatch + u * kRpl + grp;
-      tok[u] = r < n ? mem[r] : -1;
-    }
-    for (int m0 = part * kBatch; m0 < n; m0 += kSplit * kBatch) {
-      uint4 x[kUnroll];
-#pragma unroll
-      for (int u = 0; u < kUnroll; ++u)
-        x[u] = tok[u] >= 0 ? reinterpret_cast<const uint4*>(kslice + (size_t)tok[u] * kHeadDim)[sub]
-                           : make_uint4(0, 0, 0, 0);
-#pragma unroll
-      for (int u = 0; u < kUnroll; ++u) {
-        const int r = m0 + kSplit * kBatch + u * kRpl + grp;
-        tok[u] = r < n ? mem[r] : -1;
-      }
+    auto load_row = [&](int id, bool ok) {
+      return ok ? reinterpret_cast<const uint4*>(kslice + (size_t)id * kHeadDim)[sub] : make_uint4(0, 0, 0, 0);
+    };
+    auto add_rows = [&](const uint4 (&x)[kUnroll]) {
 #pragma unroll
       for (int u = 0; u < kUnroll; ++u) {
         const T* v = reinterpret_cast<const T*>(&x[u]);
 #pragma unroll
         for (int d = 0; d < kDims; ++d) acc[d] += (double)load_as_f32(v, d);
+      }
+    };
+    if constexpr (kSplit == 1) {
+      for (int m0 = 0; m0 < n; m0 += kWave) {   // 64 member ids at a time, a lane each
+        const int mine = m0 + lane < n ? mem[m0 + lane] : 0;
+        const int cnt = min(kWave, n - m0);
+        for (int q = 0; q < cnt; q += kBatch) {
+          uint4 x[kUnroll];
+#pragma unroll
+          for (int u = 0; u < kUnroll; ++u) {
+            const int r = q + u * kRpl + grp;
+            x[u] = load_row(__shfl(mine, r & (kWave - 1), kWave), r < cnt);
+          }
+          add_rows(x);
+        }
+      }
+    } else {
+      int tok[kUnroll];
+      auto load_ids = [&](int m0) {
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+          const int r = m0 + u * kRpl + grp;
+          tok[u] = r < n ? mem[r] : -1;
+        }
+      };
+      load_ids(part * kBatch);
+      for (int m0 = part * kBatch; m0 < n; m0 += kSplit * kBatch) {
+        uint4 x[kUnroll];
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) x[u] = load_row(tok[u], tok[u] >= 0);
+        load_ids(m0 + kSplit * kBatch);
+        add_rows(x);
       }
     }
 #pragma unroll
@@ -1755,18 +1779,32 @@ Ws carve(void* base, int64_t n_slices, int n_tokens, int n_clusters, int dtype) 
   return w;
 }
 
-// Waves per cluster of the update, by the clusters of the whole call: one
-// each fills the chip from kSplit4Clusters on; below that the four waves of a
-// block share a cluster's members.  Below kSplit16Clusters sixteen do where a
-// cluster has kSplit16Members on average, so that most of them have rows to
-// read (512 clusters of 64 float32 keys: 47 us with one wave, 19 with four,
-// 12.6 with sixteen; 128 clusters of 31 bf16 keys: 6.2, 4.7 and 6.0).
+// Waves per cluster of the update, by the clusters of the whole call: one each
+// fills the chip from kSplit4Clusters on.  Below that the four waves of a block
+// share a cluster's members where it has enough on average for the longest lists
+// to be the kernel's time: one per kSplit4Bf16 or kSplit4F32 clusters of the
+// call (fewer clusters leave the waves' places empty anyway).  Below
+// kSplit16Clusters sixteen waves do from kSplit16Bf16 or kSplit16F32 members on.
+// Whole clusterings, us with one / four / sixteen waves (keys 0.3 around their
+// centres; overlapping keys gain more from the split), by members on average:
+//   clusters          4               16               64               300
+//   bf16   512                  200/ 188/ 219   240/ 212/ 239    669/ 427/ 430
+//         1000   333/337/398    202/ 195/ 260   287/ 231/ 283    827/ 557/ 592
+//         2000   242/256/376    269/ 267/ 390   431/ 353/ 464   1365/1039/1143
+//         4000   352/380/619    395/ 405/ 648   794/ 652/ 875   3454/2604/2710
+//   f32    512   198/195/236    256/ 216/ 251   640/ 365/ 315   3338/1370/ 873
+//         1000   270/267/363    363/ 299/ 399  1263/ 625/ 604   4525/2214/1683
+//         2000   401/432/624    600/ 504/ 768  1891/1278/1363   8984/5392/4763
+//         4000   723/784/1204  1238/1181/1719  4489/3432/3775
+// (An update of clusters of one size gains less: 4000 of 16 float32 keys take 20
+// us with one wave and 31 with four; 1000 of 64 25 and 19.)
 constexpr int64_t kSplit4Clusters = 4096;
+constexpr int kSplit4Bf16 = 128, kSplit4F32 = 256;
 constexpr int64_t kSplit16Clusters = 1024;
-constexpr int kSplit16Members = 64;
-// From this many clusters on a wave takes four of the listed clusters in turn:
-// late iterations list a few percent of them, and waves that find nothing to
-// do are then a quarter as many.
+constexpr int kSplit16Bf16 = 256, kSplit16F32 = 64;
+// From this many clusters on a wave takes four of a list's clusters in turn (not
+// where every cluster is recomputed): late iterations list a few percent of
+// them, and waves that find nothing to do are then a quarter as many.
 constexpr int64_t kShareClusters = 65536;
 // Scatter blocks of 4096 keys instead of 1024 once that leaves the chip full.
 constexpr int64_t kWideScatterBlocks = 4096;
@@ -1916,15 +1954,17 @@ int launch_sum_t(const void* keys, int64_t S, int N, int C, int n_ctiles, const 
   a.cfrag = list && records(S, N, C, LOUISKV_BF16) ? w.cfrag : nullptr;
   a.ccnorm = w.ccnorm;
   const int64_t rows = S * C;
-  if (rows < kSplit4Clusters) {
+  const int members = N / C;
+  constexpr bool kBf16 = sizeof(T) == 2;
+  if (rows < kSplit4Clusters && (int64_t)members * (kBf16 ? kSplit4Bf16 : kSplit4F32) >= rows) {
     a.blocks_per_slice = a.stride_e = C;
-    if (rows < kSplit16Clusters && N / C >= kSplit16Members)
+    if (rows < kSplit16Clusters && members >= (kBf16 ? kSplit16Bf16 : kSplit16F32))
       centroid_update_kernel<T, 16><<<(unsigned)rows, 1024, 0, st>>>(a);
     else
       centroid_update_kernel<T, 4><<<(unsigned)rows, 256, 0, st>>>(a);
   } else {
-    const int per = rows >= kShareClusters ? 4 : 1;   // clusters a wave takes when all are listed
-    a.dlist = list && per > 1 ? w.dlist : nullptr;
+    const int per = list && rows >= kShareClusters ? 4 : 1;   // clusters a wave takes when all are listed
+    a.dlist = per > 1 ? w.dlist : nullptr;
     a.blocks_per_slice = ceil_div(C, 4 * per);
     a.stride_e = 4 * a.blocks_per_slice;
     centroid_update_kernel<T, 1><<<(unsigned)(S * a.blocks_per_slice), 256, 0, st>>>(a);

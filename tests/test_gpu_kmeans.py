@@ -241,6 +241,11 @@ def test_prefill_equals_full_sweeps(S, N, C, kind):
     (torch.float32, 2, 2047, 32),        # one fewer: four waves
     (torch.bfloat16, 1, 130, 2),         # around 64 members: the two ways of ordering them
     (torch.bfloat16, 16, 8192, 256),     # 4096 clusters: one wave each
+    # the members from which four and sixteen waves share a cluster, and one fewer
+    (torch.bfloat16, 8, 3999, 250), (torch.bfloat16, 8, 4000, 250),
+    (torch.float32, 8, 1999, 250), (torch.float32, 8, 2000, 250),
+    (torch.bfloat16, 1, 8191, 32), (torch.bfloat16, 1, 8192, 32),
+    (torch.bfloat16, 65, 1030, 1024),    # about one key a cluster, lists shared four clusters a wave
 ])
 def test_member_order_and_means(dtype, S, N, C):
     """perm is the stable order of the assignment and the centroids are the
