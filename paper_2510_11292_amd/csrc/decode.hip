@@ -687,14 +687,41 @@ __device__ __forceinline__ double load_logit(const double* p) {
 //  instead of written back (the results are the same, bit for bit).
 //  kHanded (the one-launch decode step): the logits are still on their way
 //  from the other blocks of the slice, so the block polls for them and takes
-//  their maxima itself; the rows and their number go to the slice's blocks
+//  their maxima itself; where they don't stay in registers the blocks hand
+//  the maxima of their parts over too, so that the block reads the logits no
+//  more often than it would anyway (8 slices of 8000 units, one step in four
+//  fired: 34.0 us a step with a pass for the maxima and the words handed back
+//  in pass 3, 28.4 now).  The rows and their number go to the slice's blocks
 //  through `hand` as well as to the outputs.
+constexpr int kSelRegUnits = 4;   // units whose logits a thread of the selection holds
 struct SelectHand {
+  double* max;        // [blocks of the slice][G]: maxima of their parts, above kSelRegUnits units a thread
   int32_t* rows;      // [budget]: row + 1
   int32_t* n_sel;     // one word per block of the slice: n_sel + 1
   int n_blk, spin_limit;
   int32_t* status;
 };
+
+// The handed logits of units u, u + NT, .. (R of them, those below n_units)
+// into ev, as soon as the wave's are all there; returns the polls so far.
+template <int G, int R, int NT>
+__device__ __forceinline__ int poll_logits(const double* lg, int u, int n_units, int polls, int limit,
+                                           double (&ev)[R][G]) {
+  for (bool all = false; !all;) {
+    bool got = true;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int j = 0; j < G; ++j)
+        ev[r][j] = u + r * NT < n_units ? load_logit<true>(lg + (size_t)(u + r * NT) * G + j) : 1.0;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int j = 0; j < G; ++j) got = got && __double_as_longlong(ev[r][j]) != 0;
+    all = __builtin_amdgcn_ballot_w64(!got) == 0 || ++polls >= limit;
+  }
+  return polls;
+}
 
 template <int G, bool kShared, bool kHanded = false, int NT = kSelThreads>
 __device__ __forceinline__ void select_after_max(double* __restrict__ lg, double* s_m, int n_units, int n_pad,
@@ -726,7 +753,7 @@ __device__ __forceinline__ void select_after_max(double* __restrict__ lg, double
   // the logit workspace (recomputed in pass 3 when other blocks wrote them).
   // The units' token count is summed on the way (it decides below which
   // search runs first).
-  constexpr int kRegUnits = 4;
+  constexpr int kRegUnits = kSelRegUnits;
   constexpr int NV = kSumThreads / NT;   // virtual threads per thread
   constexpr int RV = kRegUnits / NV;     // register units per virtual thread
   static_assert(RV * NV == kRegUnits, "register units");
@@ -738,41 +765,29 @@ __device__ __forceinline__ void select_after_max(double* __restrict__ lg, double
   for (int k = 0; k < NV; ++k)
 #pragma unroll
     for (int j = 0; j < G; ++j) zs[k][j] = 0.0;
+  int polls = 0;
   if constexpr (kHanded) {
-    // every logit of the slice, as soon as it is there, and the maxima
-    __shared__ double s_rm[G][NW];
-    double mx[G];
-#pragma unroll
-    for (int j = 0; j < G; ++j) mx[j] = -__builtin_inf();
-    int polls = 0;
+    static_assert(NV == 1, "a thread's units in the order of its sum");
     if (in_regs) {
+      // every logit of the slice, as soon as it is there, and the maxima
+      __shared__ double s_rm[G][NW];
+      double mx[G];
+#pragma unroll
+      for (int j = 0; j < G; ++j) mx[j] = -__builtin_inf();
       // the last head's words first: a poll is then one load a unit
       for (bool all = false; !all;) {
         bool got = true;
 #pragma unroll
         for (int r = 0; r < kRegUnits; ++r) {
-          const int u = tid + (r / RV) * NT + (r % RV) * kSumThreads;
+          const int u = tid + r * NT;
           if (u < n_units) got = got && __double_as_longlong(load_logit<true>(lg + (size_t)u * G + G - 1)) != 0;
         }
         all = __builtin_amdgcn_ballot_w64(!got) == 0 || ++polls >= hand.spin_limit;
       }
-      for (bool all = false; !all;) {
-        bool got = true;
-#pragma unroll
-        for (int r = 0; r < kRegUnits; ++r) {
-          const int u = tid + (r / RV) * NT + (r % RV) * kSumThreads;
-#pragma unroll
-          for (int j = 0; j < G; ++j) ev[r][j] = u < n_units ? load_logit<true>(lg + (size_t)u * G + j) : 1.0;
-        }
-#pragma unroll
-        for (int r = 0; r < kRegUnits; ++r)
-#pragma unroll
-          for (int j = 0; j < G; ++j) got = got && __double_as_longlong(ev[r][j]) != 0;
-        all = __builtin_amdgcn_ballot_w64(!got) == 0 || ++polls >= hand.spin_limit;
-      }
+      polls = poll_logits<G, kRegUnits, NT>(lg, tid, n_units, polls, hand.spin_limit, ev);
 #pragma unroll
       for (int r = 0; r < kRegUnits; ++r) {
-        const int u = tid + (r / RV) * NT + (r % RV) * kSumThreads;
+        const int u = tid + r * NT;
         if (u < n_units) {
 #pragma unroll
           for (int j = 0; j < G; ++j) {
@@ -781,38 +796,39 @@ __device__ __forceinline__ void select_after_max(double* __restrict__ lg, double
           }
         }
       }
-    } else {
-      for (int u0 = 0; u0 < n_units; u0 += NT) {   // uniform trips: the polls are wave-uniform
-        const int u = u0 + tid;
-        double x[G];
-        for (bool all = false; !all;) {
-          bool got = true;
 #pragma unroll
-          for (int j = 0; j < G; ++j) x[j] = u < n_units ? load_logit<true>(lg + (size_t)u * G + j) : 1.0;
-#pragma unroll
-          for (int j = 0; j < G; ++j) got = got && __double_as_longlong(x[j]) != 0;
-          all = __builtin_amdgcn_ballot_w64(!got) == 0 || ++polls >= hand.spin_limit;
-        }
-        if (u < n_units) {
-#pragma unroll
-          for (int j = 0; j < G; ++j) mx[j] = fmax(mx[j], x[j]);
-        }
+      for (int j = 0; j < G; ++j) {
+        const double m = lane_max_f64(mx[j], lane);
+        if (lane == 0) s_rm[j][w] = m;
       }
+      __syncthreads();
+      if (tid < G) {
+        double m = s_rm[tid][0];
+        for (int q2 = 1; q2 < NW; ++q2) m = fmax(m, s_rm[tid][q2]);
+        s_m[tid] = m;
+      }
+      __syncthreads();
+    } else {
+      // the parts' maxima, a word a thread
+      __shared__ double s_pm[kMaxSelectParts * G];
+      static_assert(kMaxSelectParts * G <= NT, "a word a thread");
+      const bool mine = tid < hand.n_blk * G;
+      double m = 0.0;
+      for (bool all = false; !all;) {
+        if (mine) m = load_logit<true>(hand.max + tid);
+        all = __builtin_amdgcn_ballot_w64(mine && __double_as_longlong(m) == 0) == 0 || ++polls >= hand.spin_limit;
+      }
+      if (mine) {
+        s_pm[tid] = m;
+        __hip_atomic_store(hand.max + tid, 0.0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      __syncthreads();
+      if (tid < G) {
+        for (int q2 = 0; q2 < hand.n_blk; ++q2) m = fmax(m, s_pm[q2 * G + tid]);
+        s_m[tid] = m;
+      }
+      __syncthreads();
     }
-    if (polls >= hand.spin_limit && lane == 0)
-      __hip_atomic_store(hand.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-    for (int j = 0; j < G; ++j) {
-      const double m = lane_max_f64(mx[j], lane);
-      if (lane == 0) s_rm[j][w] = m;
-    }
-    __syncthreads();
-    if (tid < G) {
-      double m = s_rm[tid][0];
-      for (int q2 = 1; q2 < NW; ++q2) m = fmax(m, s_rm[tid][q2]);
-      s_m[tid] = m;
-    }
-    __syncthreads();
   }
   if (in_regs) {
     if constexpr (!kHanded) {
@@ -835,6 +851,19 @@ __device__ __forceinline__ void select_after_max(double* __restrict__ lg, double
         }
       }
     }
+  } else if constexpr (kHanded) {
+    for (int u0 = 0; u0 < n_units; u0 += kRegUnits * NT) {   // uniform trips: the polls are wave-uniform
+      polls = poll_logits<G, kRegUnits, NT>(lg, u0 + tid, n_units, polls, hand.spin_limit, ev);
+#pragma unroll
+      for (int r = 0; r < kRegUnits; ++r) {
+        const int u = u0 + r * NT + tid;
+        if (u < n_units) {
+          tok += s_size[u];
+#pragma unroll
+          for (int j = 0; j < G; ++j) zs[0][j] += exp(ev[r][j] - s_m[j]);
+        }
+      }
+    }
   } else {
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
@@ -848,6 +877,10 @@ __device__ __forceinline__ void select_after_max(double* __restrict__ lg, double
         }
       }
     }
+  }
+  if constexpr (kHanded) {
+    if (polls >= hand.spin_limit && lane == 0)
+      __hip_atomic_store(hand.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 #pragma unroll
   for (int k = 0; k < NV; ++k)
@@ -898,11 +931,6 @@ __device__ __forceinline__ void select_after_max(double* __restrict__ lg, double
 #pragma unroll
         for (int j = 0; j < G; ++j)
           a += (kShared ? exp(load_logit<kShared>(lg + (size_t)u * G + j) - s_m[j]) : lg[(size_t)u * G + j]) / s_z[j];
-        if constexpr (kHanded) {
-#pragma unroll
-          for (int j = 0; j < G; ++j)
-            __hip_atomic_store(lg + (size_t)u * G + j, 0.0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
         a /= (double)G;
         key = unit_key(a, u);
         if (scores_out) scores_out[(size_t)s * units_cap + u] = a;
@@ -1258,6 +1286,13 @@ __device__ __forceinline__ void select_after_max(double* __restrict__ lg, double
     n_sel_units[s] = ntake;
     n_sel[s] = nsel;
   }
+  if constexpr (kHanded) {
+    // the logits that did not stay in registers are handed back last: in pass 3
+    // every trip's loads waited for the stores of the one before
+    if (!in_regs)
+      for (int i = tid; i < n_units * G; i += NT)
+        __hip_atomic_store(lg + i, 0.0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
 }
 
 // One block per fired slice: the float64 group-consistent scores (Appendix B),
@@ -1466,15 +1501,29 @@ __device__ __forceinline__ void select_handed(const T* __restrict__ q, int n_kv_
       s_incl[u] = ust[u];
     }
   }
-  if (u_begin < u_end) {
-    double mx[G];   // unused: the selector takes the maxima
+  double mx[G];
 #pragma unroll
-    for (int j = 0; j < G; ++j) mx[j] = -__builtin_inf();
+  for (int j = 0; j < G; ++j) mx[j] = -__builtin_inf();
+  if (u_begin < u_end) {
     double qd[G][LogitLayout<G>::kDims];
     load_q_f64<G>(q, (size_t)grp * n_kv_heads * G + (size_t)kvh * G, lane, qd);
     const float* rs = reps + (size_t)s * units_cap * kHeadDim;
     for (int u0 = u_begin + w * kLogitUnitsPerIter; u0 < u_end; u0 += kSelWaves * kLogitUnitsPerIter)
       wave_unit_logits<G, true>(qd, rs, u0, u_end, scale, lg, mx, lane);
+  }
+  if (n_units > kSelRegUnits * kSelThreads) {   // the selector does not take the maxima itself
+    __shared__ double s_rm[G][kSelWaves];
+#pragma unroll
+    for (int j = 0; j < G; ++j) {
+      const double m = lane_max_f64(mx[j], lane);
+      if (lane == 0) s_rm[j][w] = m;
+    }
+    __syncthreads();
+    if (tid < G) {
+      double m = s_rm[tid][0];
+      for (int q2 = 1; q2 < kSelWaves; ++q2) m = fmax(m, s_rm[tid][q2]);
+      hand_f64(hand.max + part * G + tid, m);
+    }
   }
   if (!selector) return;
   __syncthreads();
@@ -2985,7 +3034,7 @@ struct FusedStep {
   int n_units, budget;
   int32_t *sel_units, *n_sel_units, *n_sel, *sel_rows;
   double* scores_out;
-  double* logit_ws;
+  double *logit_ws, *hand_max;      // hand_max: [n_slices][kStepMaxBlocks][G]
   int32_t *hand_rows, *hand_nsel;   // [n_slices][budget], [n_slices][kStepMaxBlocks]
   uint64_t* met;                    // per slice, kStepSyncStride ints apart: arrivals << 32 | shares left
   int32_t *grp_counter, *status;
@@ -3115,8 +3164,8 @@ void step_fused_kernel(const FusedStep a) {
     a.fire_out[grp] = (uint8_t)(fire ? 1 : 0);
   }
   if (fire) {
-    const SelectHand hand = {a.hand_rows + (size_t)s * a.budget, a.hand_nsel + s * kStepMaxBlocks, nb, a.spin_limit,
-                             a.status};
+    const SelectHand hand = {a.hand_max + (size_t)s * kStepMaxBlocks * G, a.hand_rows + (size_t)s * a.budget,
+                             a.hand_nsel + s * kStepMaxBlocks, nb, a.spin_limit, a.status};
     select_handed<uint16_t, G>(a.q, a.n_kv_heads, s, c, nb, c == nb - 1, a.scale, a.reps, a.units_cap, a.n_units,
                                a.n_pad, a.budget, a.unit_start, a.unit_size, a.sel_units, a.n_sel_units, a.n_sel,
                                a.sel_rows, a.scores_out, a.logit_ws, smem, hand);
@@ -3960,7 +4009,7 @@ namespace louiskv {
 namespace {
 
 struct StepLayout {
-  size_t hand_logits, hand_rows, hand_part, logits, pmax, fetch, part, total;
+  size_t hand_logits, hand_max, hand_rows, hand_part, logits, pmax, fetch, part, total;
 };
 
 // Polls of the one-launch step's bounded wait: kStepSpinLimit, or fewer from
@@ -4016,6 +4065,7 @@ StepLayout step_layout(int64_t S, int dtype, int G, int units_cap, int budget, i
   auto carve_hand = [&](size_t base) {
     used = base;
     L.hand_logits = take((size_t)S * units_cap * G * sizeof(double));
+    L.hand_max = take(units_cap > kSelRegUnits * kSelThreads ? (size_t)S * kStepMaxBlocks * G * sizeof(double) : 0);
     L.hand_rows = take((size_t)S * ((size_t)std::max(budget, 1) + kStepMaxBlocks) * sizeof(int32_t));
     // (a0, a1, m, l) per block, head and pair of dims, where a slice has several
     const size_t nb = step_max_blocks(S, budget, window);
@@ -4179,6 +4229,7 @@ int decode_step_impl(const void* q, void* q_ref, int32_t dtype, int64_t n_groups
     fa.sel_rows = sel_rows;
     fa.scores_out = scores_out;
     fa.logit_ws = reinterpret_cast<double*>(ws + lay.hand_logits);
+    fa.hand_max = reinterpret_cast<double*>(ws + lay.hand_max);
     fa.hand_rows = reinterpret_cast<int32_t*>(ws + lay.hand_rows);
     fa.hand_nsel = fa.hand_rows + (size_t)n_slices * std::max(budget, 1);
     fa.met = reinterpret_cast<uint64_t*>(sel_counter);

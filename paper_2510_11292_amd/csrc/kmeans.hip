@@ -1157,12 +1157,17 @@ void centroid_update_kernel(const UpdateArgs<T> a) {
     float* dst = a.cout + ((size_t)s * a.stride + c) * kHeadDim;
     if constexpr (kSplit > 1) __syncthreads();   // every wave has read the count and the flag before one clears them
     if (clean) continue;
-    if (lane == 0 && part == 0) {
-      if (track) a.dirty[crow + c] = 0;
-      if (a.cursor) a.cursor[crow + c] = 0;
-      if (a.zero_counts) a.counts[crow + c] = 0;
-    }
+    // after the row loads, which would otherwise wait for these stores (a wave's
+    // memory operations complete in order)
+    auto clear = [&]() {
+      if (lane == 0 && part == 0) {
+        if (track) a.dirty[crow + c] = 0;
+        if (a.cursor) a.cursor[crow + c] = 0;
+        if (a.zero_counts) a.counts[crow + c] = 0;
+      }
+    };
     if (n == 0) {
+      clear();
       // empty: the centroid (and its operand from the previous preparation) stay
       if (a.cin != a.cout && part == 0) {
         const float* src = a.cin + ((size_t)s * a.stride + c) * kHeadDim;
@@ -1227,6 +1232,7 @@ void centroid_update_kernel(const UpdateArgs<T> a) {
         add_rows(x);
       }
     }
+    clear();
 #pragma unroll
     for (int o = kLpr; o < kWave; o <<= 1)
 #pragma unroll

@@ -1258,6 +1258,9 @@ def test_decode_step_equals_stage_calls(case):
 
 @pytest.mark.parametrize("kind,groups,h,g,C,prompt,budget", [
     ("bf16", 1, 8, 4, 2100, 4200, 300),    # more units than two per thread and rank registers hold
+    ("bf16", 1, 8, 1, 2048, 4200, 300),    # the most units whose logits stay in the selector's registers
+    ("bf16", 1, 4, 8, 2049, 4200, 300),    # one more: the parts' maxima are handed over
+    ("bf16", 1, 2, 2, 8192, 9000, 300),    # the most units
     ("bf16", 1, 1, 8, 64, 1024, 2048),     # one slice, 32 blocks, a budget above the prompt
     ("bf16", 16, 8, 2, 64, 1024, 256),     # two blocks a slice
     ("bf16", 10, 8, 1, 64, 1024, 256),     # three blocks a slice, the third without pairs to merge
