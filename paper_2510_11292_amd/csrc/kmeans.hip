@@ -1149,11 +1149,12 @@ void centroid_update_kernel(const UpdateArgs<T> a) {
   const size_t crow = (size_t)s * a.n_clusters;
   for (int e = kSplit > 1 ? blk : blk * 4 + w; e < n_entries; e += a.stride_e) {
     const int c = a.dlist ? a.dlist[crow + e] : e;
-    const int n = a.counts[crow + c];
-    const int off = a.offsets[(size_t)s * (a.n_clusters + 1) + c];
     // place in the slice's list, or -1
     const int slot = !track ? 0 : a.dlist ? e : a.dmap ? a.dmap[crow + c] : a.dirty[crow + c] ? 0 : -1;
     const bool clean = slot < 0;
+    if (kSplit == 1 && clean) continue;   // before anything else is loaded: most waves of late iterations end here
+    const int n = a.counts[crow + c];
+    const int off = a.offsets[(size_t)s * (a.n_clusters + 1) + c];
     float* dst = a.cout + ((size_t)s * a.stride + c) * kHeadDim;
     if constexpr (kSplit > 1) __syncthreads();   // every wave has read the count and the flag before one clears them
     if (clean) continue;
