@@ -1091,12 +1091,10 @@ void scatter_kernel(const int32_t* __restrict__ assign, const int32_t* __restric
 // cluster).  A key row is read as 16-byte pieces: kLpr lanes per row, so one
 // wave load covers kRpl rows and kUnroll loads are in flight; each lane
 // accumulates its dims in float64, the row groups are summed across lanes and
-// the waves' parts through LDS at the end.  One wave a cluster loads 64 member
-// ids at a time, a lane each, and hands them out by shuffles; where waves share
-// a cluster each loads its batch's ids, the next batch's with the rows.  (One
-// wave with ids loaded per batch, eight rows unrolled in float32 and four
-// clusters a wave: 70000 clusters of 48 keys 494 us in float32 and 241 in bf16
-// against 383 and 222.)
+// the waves' parts through LDS at the end.  Where waves share a cluster, and in
+// bf16 where one has kBatchIdsMembers members or more on average, a wave loads
+// each batch's ids with the rows of the batch before; otherwise 64 ids at a time,
+// a lane each, handed out by shuffles.
 // One wave a cluster reads the rows at the rate HBM gives them once there are
 // clusters enough to fill the chip; below that the longest member list is the
 // kernel's time, and a block's waves share it.
@@ -1130,7 +1128,7 @@ struct UpdateArgs {
   float* ccnorm;
 };
 
-template <class T, int kSplit>
+template <class T, int kSplit, bool kBatchIds = (kSplit > 1)>
 __global__ __launch_bounds__((kSplit > 4 ? 64 * kSplit : 256))
 void centroid_update_kernel(const UpdateArgs<T> a) {
   constexpr int kDims = 16 / sizeof(T);          // dims per 16-byte piece (8 bf16, 4 fp32)
@@ -1201,10 +1199,13 @@ void centroid_update_kernel(const UpdateArgs<T> a) {
         for (int d = 0; d < kDims; ++d) acc[d] += (double)load_as_f32(v, d);
       }
     };
-    if constexpr (kSplit == 1) {
+    if constexpr (!kBatchIds) {
+      static_assert(kSplit == 1, "a wave's own members");
+      int next = lane < n ? mem[lane] : 0;
       for (int m0 = 0; m0 < n; m0 += kWave) {   // 64 member ids at a time, a lane each
-        const int mine = m0 + lane < n ? mem[m0 + lane] : 0;
+        const int mine = next;
         const int cnt = min(kWave, n - m0);
+        if (m0 + kWave < n) next = m0 + kWave + lane < n ? mem[m0 + kWave + lane] : 0;   // ahead of the rows
         for (int q = 0; q < cnt; q += kBatch) {
           uint4 x[kUnroll];
 #pragma unroll
@@ -1809,6 +1810,13 @@ constexpr int64_t kSplit4Clusters = 4096;
 constexpr int kSplit4Bf16 = 128, kSplit4F32 = 256;
 constexpr int64_t kSplit16Clusters = 1024;
 constexpr int kSplit16Bf16 = 256, kSplit16F32 = 64;
+// One wave a cluster in bf16: ids a batch at a time from this many members on
+// (long lists end sooner: clusterings of 16 slices of 20000 keys in 256 clusters
+// 804 us against 818 with 64 ids at a time, 8 of 20011 in 625 705 against 712;
+// an update of 16000 clusters of 4 keys 26.1 against 25.2, of 20 34.7 and 34.6).
+// Float32 rows are two a load, and 64 ids at a time are faster throughout (16000
+// clusters of 48 keys 108 us against 122).
+constexpr int kBatchIdsMembers = 20;
 // From this many clusters on a wave takes four of a list's clusters in turn (not
 // where every cluster is recomputed): late iterations list a few percent of
 // them, and waves that find nothing to do are then a quarter as many.
@@ -1974,7 +1982,15 @@ int launch_sum_t(const void* keys, int64_t S, int N, int C, int n_ctiles, const 
     a.dlist = per > 1 ? w.dlist : nullptr;
     a.blocks_per_slice = ceil_div(C, 4 * per);
     a.stride_e = 4 * a.blocks_per_slice;
-    centroid_update_kernel<T, 1><<<(unsigned)(S * a.blocks_per_slice), 256, 0, st>>>(a);
+    const unsigned grid = (unsigned)(S * a.blocks_per_slice);
+    if constexpr (kBf16) {
+      if (members >= kBatchIdsMembers)
+        centroid_update_kernel<T, 1, true><<<grid, 256, 0, st>>>(a);
+      else
+        centroid_update_kernel<T, 1><<<grid, 256, 0, st>>>(a);
+    } else {
+      centroid_update_kernel<T, 1><<<grid, 256, 0, st>>>(a);
+    }
   }
   LKV_CHECK_LAUNCH();
   return LOUISKV_OK;

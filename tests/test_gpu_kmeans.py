@@ -246,6 +246,8 @@ def test_prefill_equals_full_sweeps(S, N, C, kind):
     (torch.float32, 8, 1999, 250), (torch.float32, 8, 2000, 250),
     (torch.bfloat16, 1, 8191, 32), (torch.bfloat16, 1, 8192, 32),
     (torch.bfloat16, 65, 1030, 1024),    # about one key a cluster, lists shared four clusters a wave
+    # the members from which one bf16 wave loads ids a batch at a time, and fewer
+    (torch.bfloat16, 17, 4864, 256), (torch.bfloat16, 17, 5120, 256),
 ])
 def test_member_order_and_means(dtype, S, N, C):
     """perm is the stable order of the assignment and the centroids are the
