@@ -2455,12 +2455,12 @@ __device__ __forceinline__ void attn_hand(const float (*s_m)[G], const float (*s
 // the word.  All started: it goes on waiting, for words that are then sure to
 // come.  Otherwise it leaves its bit there for the last block to start, which
 // merges its share, and returns.  s_late: zero, a barrier before this call.
-// Without patience (a test's setting) the block does not wait at all: `left`, in
-// the thread that counts the arrival, says that its bit went there with it.
+// kLeave (a test's setting): the block does not wait at all; `left`, in the
+// thread that counts the arrival, says that its bit went there with it.
 // Returns the polls, for the caller's bound.
 constexpr int kStepPatience = 64;
 
-template <int G, int NW>
+template <int G, int NW, bool kLeave>
 __device__ __forceinline__ int attn_merge_share(int tid, int64_t s, int chunk, int n_chunks, float* __restrict__ part,
                                                 void* __restrict__ out, int out_bf16, float* __restrict__ lse_out,
                                                 int spin_limit, uint64_t* met, int patience, bool left,
@@ -2501,7 +2501,7 @@ __device__ __forceinline__ int attn_merge_share(int tid, int64_t s, int chunk, i
                                 __uint_as_float((uint32_t)y), __uint_as_float((uint32_t)(y >> 32)));
     };
     const bool ask = met && r == 0;                        // later rounds: every block has handed words
-    const bool all = (!ask || patience > 0) && collect(ask ? patience : spin_limit);
+    const bool all = !(kLeave && ask) && collect(ask ? patience : spin_limit);
     if (ask && !all && lane == 0) *s_late = 1;
     if (r > 0) __syncthreads();                            // the last round's sums are done
     stage();
@@ -2512,7 +2512,7 @@ __device__ __forceinline__ int attn_merge_share(int tid, int64_t s, int chunk, i
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this block's own arrival is counted
         const uint64_t bit = 1ull << chunk;
         bool leave = left;
-        if (patience > 0) {
+        if constexpr (!kLeave) {
           const int n = (int)(__hip_atomic_fetch_or(met, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 32);
           leave = n > 0 && n < n_chunks;                   // zero again: counted to the end and reset
           if (!leave) __hip_atomic_fetch_and(met, ~bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -3038,7 +3038,7 @@ struct FusedStep {
   int32_t *hand_rows, *hand_nsel;   // [n_slices][budget], [n_slices][kStepMaxBlocks]
   uint64_t* met;                    // per slice, kStepSyncStride ints apart: arrivals << 32 | shares left
   int32_t *grp_counter, *status;
-  int n_blk, chunk_rows, n_pad, spin_limit, patience;
+  int n_blk, chunk_rows, n_pad, spin_limit;
   int local_start, n_local;
   float* part;
   void* out;
@@ -3055,7 +3055,9 @@ constexpr size_t fused_attn_lds(int chunk_rows) {
          (size_t)kSelWaves * G * kHeadDim * sizeof(float) + (size_t)chunk_rows * sizeof(int);
 }
 
-template <int G>
+// kLeave: blocks leave their shares at once (an instantiation of its own: as a
+// setting at run time it cost a step over 32 slices 1%).
+template <int G, bool kLeave>
 __global__ __launch_bounds__(kSelThreads)
 void step_fused_kernel(const FusedStep a) {
   constexpr int NW = kSelWaves;
@@ -3230,7 +3232,7 @@ void step_fused_kernel(const FusedStep a) {
   constexpr int kMetThread = (NW - 2) * 64;
   uint64_t* met = fire || nb == 1 ? nullptr : a.met + s * (kStepSyncStride / 2);
   uint64_t met_old = 0;
-  const uint64_t arrival = (1ull << 32) + (a.patience > 0 ? 0 : 1ull << c);
+  const uint64_t arrival = (1ull << 32) + (kLeave ? 1ull << c : 0);
   if (met && tid == kMetThread) met_old = __hip_atomic_fetch_add(met, arrival, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   for (int t = w; t < n_tiles; t += kInFlight * NW) {
     if (t != w) {
@@ -3260,15 +3262,16 @@ void step_fused_kernel(const FusedStep a) {
   if (nb > 1) {
     auto merge = [&](int share, uint64_t* ask, bool left) {
       const int limit = fire ? a.spin_limit : kStepSpinLimit;
-      const int polls = attn_merge_share<G, NW>(tid, s, share, nb, a.part, a.out, a.out_bf16, a.lse_out, limit, ask,
-                                                a.patience, left, &s_late, reinterpret_cast<float4*>(s_p));
+      const int polls = attn_merge_share<G, NW, kLeave>(tid, s, share, nb, a.part, a.out, a.out_bf16, a.lse_out, limit,
+                                                        ask, min(a.spin_limit, kStepPatience), left, &s_late,
+                                                        reinterpret_cast<float4*>(s_p));
       if (polls >= limit && lane == 0) __hip_atomic_store(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
     bool left = false;
     if (met && tid == kMetThread) {
       const bool last = (int)(met_old >> 32) == nb - 1;
       s_left = last ? (uint32_t)met_old : 0;   // shares left to the last block to start
-      left = !last && a.patience <= 0;
+      left = kLeave && !last;
       if (last)   // back to zero; a bit that is set from here on is taken back by its block
         __hip_atomic_fetch_sub(met, met_old + arrival, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
@@ -4039,8 +4042,8 @@ int step_max_blocks(int64_t S, int budget, int window, int64_t cus = kStepBlocks
 // one-launch step keeps its counters and a status word kStepSyncStride ints
 // apart, the two-launch step its two counters per slice packed at the start),
 // whose place depends on the slices alone; then, for the one-launch step, the
-// words that its blocks hand each other (logits, list entries, list lengths,
-// attention partials), all zero between calls; for the two-launch step its
+// words that its blocks hand each other (logits, maxima, list entries, list
+// lengths, attention partials), all zero between calls; for the two-launch step its
 // scratch, which it does not clear: logits and part maxima, with a cached
 // KV_critical the transfer plan's scratch (fetch slots, rows, counts), and the
 // attention partials.  (Clearing it at the end of the step cost 2-3% of it.)
@@ -4240,7 +4243,6 @@ int decode_step_impl(const void* q, void* q_ref, int32_t dtype, int64_t n_groups
     fa.n_pad = n_pad;
     const int polls = step_spin_limit();
     fa.spin_limit = std::max(polls, 1);
-    fa.patience = std::min(polls, kStepPatience);
     fa.local_start = local_start;
     fa.n_local = n_local;
     fa.part = reinterpret_cast<float*>(ws + lay.hand_part);
@@ -4251,8 +4253,9 @@ int decode_step_impl(const void* q, void* q_ref, int32_t dtype, int64_t n_groups
 #define LKV_STEP_FUSED(G)                                                                                   \
   {                                                                                                         \
     const size_t flds = std::max(lds, fused_attn_lds<G>(chunk_rows));                                       \
-    if ((st = check_lds(reinterpret_cast<const void*>(&step_fused_kernel<G>), flds))) return st;            \
-    step_fused_kernel<G><<<fgrid, kSelThreads, flds, s>>>(fa);                                              \
+    const auto kernel = polls > 0 ? &step_fused_kernel<G, false> : &step_fused_kernel<G, true>;             \
+    if ((st = check_lds(reinterpret_cast<const void*>(kernel), flds))) return st;                           \
+    kernel<<<fgrid, kSelThreads, flds, s>>>(fa);                                                            \
   }
     switch (group_size) {
       case 1: LKV_STEP_FUSED(1); break;
